@@ -56,7 +56,7 @@ struct ConvDev {
     ulonglong2 *d_neg_q = nullptr;     // [nt] (value, Shoup companion) of [-Q_src]_dst_t
     bool f64 = false;                  // primes below 2^50, sources below twice the targets: fp64 tables set
     double *d_qhat_inv_f = nullptr;    // [ns] the values of d_qhat_inv as doubles
-    double *d_qhat_mod_f = nullptr;    // [ns][nt] the values of d_qhat_mod as doubles
+    double *d_qhat_mod_f = nullptr;    // [ns][nt] the values of d_qhat_mod as doubles, centred in (-dst/2, dst/2)
 };
 
 // Kernels timed by the optional event profiler.  Each launch is bracketed by

@@ -275,7 +275,11 @@ static ckks_status make_conv(ckks_ctx *c, const std::vector<uint32_t> &src, cons
     if (out->f64) {
         std::vector<double> fi(qinv.size()), fm(qmod.size());
         for (size_t k = 0; k < qinv.size(); k++) fi[k] = (double)qinv[k].x;
-        for (size_t k = 0; k < qmod.size(); k++) fm[k] = (double)qmod[k].x;
+        // centred: the sums of eight products of two centred factors stay exact under one quotient (GridSum)
+        for (size_t k = 0; k < qmod.size(); k++) {
+            const uint64_t q = c->primes[dst[k % dst.size()]], v = qmod[k].x;
+            fm[k] = v > q / 2 ? -(double)(q - v) : (double)v;
+        }
         CK_TRY(upload((void **)&out->d_qhat_inv_f, fi.data(), fi.size() * sizeof(double)));
         CK_TRY(upload((void **)&out->d_qhat_mod_f, fm.data(), fm.size() * sizeof(double)));
     }

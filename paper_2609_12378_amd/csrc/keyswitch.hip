@@ -106,9 +106,8 @@ __global__ __launch_bounds__(kThreads) void k_conv(const uint64_t *in, uint32_t 
 
 // The same conversion in fp64 (every prime below 2^50): y_i = x_i * qhat_inv_i mod s_i (|mul| < 0.875 s_i for
 // canonical operands) is moved into (-s_i/2, s_i/2] by one add or subtract of s_i, then each target sums the
-// products y_i * [Qhat_i]_t (each below 0.875 t in magnitude, since |y_i| < s_i/2 < t) with a range reduction
-// after every eight terms that more follow (sums stay below 7.5 t < 2^53) and writes the canonical residue: the
-// same integers as k_conv.
+// products y_i * [Qhat_i]_t (both factors centred, below 2^49) eight at a time under one quotient
+// (nttc::GridSum) and writes the canonical residue: the same integers as k_conv.
 // C coefficients per thread (kThreads apart, so every load and store stays coalesced): the per-target constants
 // come from LDS once for all C, and the C product chains are independent.  All source loads issue before the
 // first is used (EXACT: ns == NS_MAX, no guards in the source loop).  blockIdx.z splits the target limbs into
@@ -162,31 +161,28 @@ __global__ __launch_bounds__(kThreads) void k_conv_f64(const uint64_t *in, uint3
         nttc::Ar<true> ar;
         ar.q = s_tq[t].x;
         ar.qinv = s_tq[t].y;
-        double acc[C];
-#pragma unroll
-        for (int c = 0; c < C; c++) acc[c] = 0.0;
+        nttc::GridSum acc[C];
 #pragma unroll
         for (int i = 0; i < NS_MAX; i++) {
             if (EXACT || i < ns) {
                 const double w = s_mod[i * nt + t];
 #pragma unroll
                 for (int c = 0; c < C; c++) {
-                    acc[c] += ar.mul(y[c][i], w);
-                    if ((i & 7) == 7 && i + 1 < ns) acc[c] = ar.red(acc[c]);
+                    acc[c].add(y[c][i], w);
+                    if ((i & 7) == 7 && i + 1 < ns) acc[c].fold(ar);
                 }
             }
         }
         const uint32_t row = t < (int)split ? t : t + skip;
 #pragma unroll
-        for (int c = 0; c < C; c++) dst[((size_t)row << log_n) + c * kThreads] = ar.to_canon(acc[c]);
+        for (int c = 0; c < C; c++) dst[((size_t)row << log_n) + c * kThreads] = ar.to_canon(acc[c].value(ar));
     }
 }
 
 // The fp64 conversion (at most 8 source limbs) fused with the first forward column pass, N = 2^16: block
 // (poly, 16 adjacent columns), 512 threads, 8 points of one 256-point column per thread.  The centred source
 // digits y_i of the block's 4096 coefficients stay in registers; for each target limb in turn the block forms
-// the converted residues with the products and range reductions of k_conv_f64 (reduced to |x| <= t/2 rather
-// than made canonical), runs that limb's column sub-transforms on them (nttc::fwd8_256 with the column pass's
+// the converted residues with the sums of k_conv_f64 (reduced to |x| <= t/2 rather than made canonical), runs that limb's column sub-transforms on them (nttc::fwd8_256 with the column pass's
 // lazy-reduction mask) and writes the rows as raw doubles, the inter-pass form the fused row passes read.  The
 // converted rows thus cross HBM once instead of three times (written, read and written by a separate column
 // pass, read by the ModDown).  Target t + 1's twiddles (Psi[1..255]) are staged into the idle half of a
@@ -250,15 +246,11 @@ __global__ __launch_bounds__(512) void k_conv_col8(const uint64_t *__restrict__ 
         double x[kE8];
 #pragma unroll
         for (int k = 0; k < kE8; k++) {
-            double acc = 0.0;
+            nttc::GridSum acc;
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
-                if (EXACT || i < ns) {
-                    acc += ar.mul(y[k][i], s_mod[i * nt + tt]);
-                    if ((i & 7) == 7 && i + 1 < ns) acc = ar.red(acc);
-                }
-            }
-            x[k] = ar.red(acc);
+            for (int i = 0; i < 8; i++)
+                if (EXACT || i < ns) acc.add(y[k][i], s_mod[i * nt + tt]);
+            x[k] = ar.red(acc.value(ar));
         }
         nttc::fwd8_256<nttc::kColMask8>(x, tws[tt & 1], tr[col], t, ar, 1, next);
         const uint32_t row = tt < (int)split ? tt : tt + skip;

@@ -149,6 +149,38 @@ struct Ar<true> {
     }
 };
 
+// sum_i a_i w_i mod q with one quotient for the whole sum (fp64): 4 instructions a term in place of the 7 of a
+// reduced product and its addition.  hi holds the running sum rounded to the grid u = 2^50 (it starts at 1.5 2^52 u,
+// so while |sum| < 2^51 u its exponent and hence the grid stay fixed): t = fl(a w + hi) moves hi by the multiple
+// h = t - hi of u nearest to a w, and a w - h, an integer of at most u/2, is exact and goes to lo.  With
+// |a|, |w| <= 2^49 (centred residues of primes below 2^50) eight terms keep |sum| <= 2^101 = 2^51 u and
+// |lo| <= 8 2^49 = 2^52.  value(): hi - c q with c = rint(hi / q) is an integer of at most 1.5 q (the quotient, up
+// to 2^51, is estimated within 1), so the result, below 2^52 + 1.5 2^50 < 2^53, is exact.
+struct GridSum {
+    static constexpr double kGrid = 0x1.8p+102;  // 1.5 2^52 u
+    static constexpr int kTerms = 8;
+    double hi, lo;
+    __device__ GridSum() : hi(kGrid), lo(0.0) {}
+    __device__ void add(double a, double w)
+    {
+        const double t = fma(a, w, hi);
+        const double h = t - hi;
+        lo += fma(a, w, -h);
+        hi = t;
+    }
+    __device__ double value(const Ar<true> &ar) const
+    {
+        const double h = hi - kGrid;
+        return fma(-rint(h * ar.qinv), ar.q, h) + lo;
+    }
+    // after kTerms terms, before more: the sum so far as one residue of at most q/2 + 1
+    __device__ void fold(const Ar<true> &ar)
+    {
+        lo = ar.red(value(ar));
+        hi = kGrid;
+    }
+};
+
 // One forward butterfly of stage s: with fp64 arithmetic a stage whose bit in RMASK is clear skips the range
 // reduction of X (ct_lazy); the integer arithmetic keeps its own lazy range [0, 4q) and ignores the mask.
 template <bool F, unsigned RMASK>
