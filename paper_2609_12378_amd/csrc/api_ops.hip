@@ -21,6 +21,9 @@ ckks_status check_buf(const ckks_ctx *ctx, const ckks_buf *b, uint32_t polys, co
 
 size_t words(const ckks_ctx *ctx, size_t rows) { return rows << ctx->log_n; }
 
+// the `n` words at a and the `m` words at b share one
+bool overlap(const uint64_t *a, size_t n, const uint64_t *b, size_t m) { return a < b + m && b < a + n; }
+
 }  // namespace
 
 // Workspace bytes of one call of `op` (ckks_op) with the given shape; SIZE_MAX for an unknown op or shape.
@@ -86,8 +89,8 @@ ckks_status rotate_core(ckks_ctx *ctx, const uint64_t *c, uint32_t level, const 
     const size_t N = ctx->n;
     uint64_t *digits = work;
     uint64_t *rw = digits + ((size_t)nd * ext + ctx->alpha) * N;
-    CK_TRY(ks_modup(ctx, c + (size_t)L * N, level, digits));
     const uint32_t bs = ks_rot_batch(count);
+    CK_TRY(ks_modup(ctx, c + (size_t)L * N, level, digits, ks_stage_rows(ctx, level, bs, 1)));
     std::vector<uint32_t> g(count);
     for (uint32_t r = 0; r < count; r++) g[r] = ckks_galois_elt(ctx, steps[r]);
     std::vector<const uint64_t *> c0s(count, c), digs(count, digits);
@@ -110,8 +113,9 @@ ckks_status rotate_many(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
     uint64_t *digits = work;
     uint64_t *rw = digits + (size_t)count * (dig_ct + (size_t)ctx->alpha * N);
-    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, digits));
     const uint32_t bs = ks_rot_batch(count);
+    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, digits,
+                          ks_stage_rows(ctx, level, bs, count)));
     std::vector<uint32_t> g(count, ckks_galois_elt(ctx, steps));
     std::vector<const uint64_t *> keys(count, key), c0s(count), digs(count);
     for (uint32_t r = 0; r < count; r++) {
@@ -134,8 +138,9 @@ ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
     uint64_t *digits = work;
     uint64_t *rw = digits + (size_t)count * (dig_ct + (size_t)ctx->alpha * N);
-    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, digits));
     const uint32_t bs = ks_rot_batch(count);
+    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, digits,
+                          ks_stage_rows(ctx, level, bs, count)));
     std::vector<uint32_t> g(count);
     std::vector<const uint64_t *> c0s(count), digs(count);
     for (uint32_t r = 0; r < count; r++) {
@@ -151,12 +156,6 @@ ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     return CKKS_OK;
 }
 
-size_t lazy_work_words(const ckks_ctx *ctx, uint32_t level, uint32_t count)
-{
-    const size_t ext = level + 1 + ctx->n_p;
-    return (size_t)count * ((size_t)n_digits(ctx, level) * ext + ctx->alpha) << ctx->log_n;
-}
-
 namespace {
 
 ckks_status rotate_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
@@ -166,7 +165,8 @@ ckks_status rotate_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     if (!count) return CKKS_OK;
     const uint32_t L = level + 1, ext = L + ctx->n_p, nd = n_digits(ctx, level);
     const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
-    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, work));
+    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, work,
+                          ks_stage_rows(ctx, level, ks_rot_batch(count), count)));
     std::vector<uint32_t> g(count);
     std::vector<const uint64_t *> c0s(count), digs(count), ks(count);
     std::vector<uint64_t *> accs(count);
@@ -207,6 +207,7 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
     if (!count) return CKKS_OK;
     const size_t N = ctx->n;
     const uint32_t polys = 2 * count;
+    if (blk_ring(ctx) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, polys, l, out, work);
     uint64_t *top = work, *r = top + (size_t)polys * N;
     // the top limb of every polynomial, then the same steps as one rescale over all of them
     CK_TRY(launch_copy_rows(ctx, top, N, nullptr, 0, c + (size_t)l * N, (size_t)(l + 1) * N, N, polys));
@@ -221,6 +222,7 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
 ckks_status rescale_core(ckks_ctx *ctx, const uint64_t *c, uint32_t l, uint64_t *out, uint64_t *work)
 {
     const size_t N = ctx->n;
+    if (blk_ring(ctx) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, 2, l, out, work);
     uint64_t *top = work, *r = top + 2 * N;
     for (int k = 0; k < 2; k++)
         HIP_TRY(hipMemcpyAsync(top + k * N, c + ((size_t)k * (l + 1) + l) * N, N * 8, hipMemcpyDeviceToDevice,
@@ -266,8 +268,12 @@ ckks_status ckks_decode(ckks_ctx *ctx, const ckks_buf *pt, double *re, double *i
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_DECODE, &pt->n_limbs), &w));
     uint64_t *coef = (uint64_t *)w;
     double2 *work = (double2 *)(coef + words(ctx, lim));
-    HIP_TRY(hipMemcpyAsync(coef, pt->data, words(ctx, lim) * 8, hipMemcpyDeviceToDevice, ctx->stream));
-    CK_TRY(launch_ntt(ctx, coef, lim, limb_range(0, lim), true));
+    if (blk_rows(ctx, lim) && ntt_uses_f64(ctx, lim)) {
+        CK_TRY(blk_ntt(ctx, coef, lim, pt->data, lim, 1, limb_range(0, lim), true));
+    } else {
+        HIP_TRY(hipMemcpyAsync(coef, pt->data, words(ctx, lim) * 8, hipMemcpyDeviceToDevice, ctx->stream));
+        CK_TRY(launch_ntt(ctx, coef, lim, limb_range(0, lim), true));
+    }
     return dec_slots(ctx, coef, lim, pt->scale, work, re, im);
 }
 
@@ -282,6 +288,11 @@ ckks_status ckks_encrypt_sk(ckks_ctx *ctx, const int8_t *s, const ckks_buf *pt, 
     const uint32_t L = pt->n_limbs;
     void *w;
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_ENCRYPT, &L), &w));
+    if (blk_crypt(ctx, L)) {
+        CK_TRY(blk_encrypt(ctx, ct->data, ct->data + words(ctx, L), a, s, e, pt->data, L));
+        ct->scale = pt->scale;
+        return CKKS_OK;
+    }
     uint64_t *sn = (uint64_t *)w, *en = sn + words(ctx, L);
     const LimbMap map = limb_range(0, L);
     CK_TRY(launch_expand_i8(ctx, sn, s, map));
@@ -302,6 +313,11 @@ ckks_status ckks_decrypt(ckks_ctx *ctx, const int8_t *s, const ckks_buf *ct, ckk
     const uint32_t L = ct->n_limbs;
     void *w;
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_DECRYPT, &L), &w));
+    if (blk_crypt(ctx, L)) {
+        CK_TRY(blk_decrypt(ctx, pt->data, ct->data, ct->data + words(ctx, L), s, L));
+        pt->scale = ct->scale;
+        return CKKS_OK;
+    }
     uint64_t *sn = (uint64_t *)w;
     const LimbMap map = limb_range(0, L);
     CK_TRY(launch_expand_i8(ctx, sn, s, map));
@@ -485,12 +501,20 @@ ckks_status ckks_mul_relin(ckks_ctx *ctx, const ckks_buf *a, const ckks_buf *b, 
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_MUL_RELIN, &L), &w));
     uint64_t *d0 = (uint64_t *)w, *d1 = d0 + L * N, *d2 = d1 + L * N;
     uint64_t *digits = d2 + L * N;
-    uint64_t *u = digits + ((size_t)nd * ext + ctx->alpha) * N;
-    uint64_t *cw = u + 2 * (size_t)ext * N;
-    CK_TRY(launch_tensor(ctx, d0, d1, d2, a->data, b->data, L));
-    CK_TRY(ks_modup(ctx, d2, level, digits));
-    CK_TRY(ks_inner_product(ctx, digits, nd, rlk, level, 1, u));
-    CK_TRY(ks_moddown(ctx, u, 2, level, d0, 1, d1, out->data, cw));
+    uint64_t *rw = digits + ((size_t)nd * ext + ctx->alpha) * N;
+    // the whole-row kernels form the tensor product where they read it, unless the output overwrites an input
+    if (blk_switch(ctx, level) && !overlap(out->data, 2 * L * N, a->data, 2 * L * N) &&
+        !overlap(out->data, 2 * L * N, b->data, 2 * L * N)) {
+        CK_TRY(ks_mul_relin_blk(ctx, a->data, b->data, rlk, level, out->data, digits));
+    } else {
+        // the relinearisation is a rotation by the identity: (d0 + u0, d1 + u1), u the key switch of d2
+        CK_TRY(launch_tensor(ctx, d0, d1, d2, a->data, b->data, L));
+        CK_TRY(ks_modup(ctx, d2, level, digits, ks_stage_rows(ctx, level, 1, 1)));
+        const uint64_t *c0 = d0, *add1 = d1, *dig = digits, *key = rlk;
+        const uint32_t g = 1;
+        uint64_t *o = out->data;
+        CK_TRY(ks_rotate_batch(ctx, level, 1, &c0, &dig, &g, &key, &o, rw, nullptr, &add1));
+    }
     out->scale = a->scale * b->scale;
     return CKKS_OK;
 }
@@ -505,8 +529,13 @@ ckks_status ckks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_
     const size_t N = ctx->n;
     void *w;
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_MODUP, &level), &w));
-    CK_TRY(ks_modup(ctx, c, level, (uint64_t *)w));
-    HIP_TRY(hipMemcpyAsync(digits, w, (size_t)nd * ext * N * 8, hipMemcpyDeviceToDevice, ctx->stream));
+    const size_t dig_w = (size_t)nd * ext * N, c_w = (size_t)(level + 1) * N;
+    if (blk_switch(ctx, level) && !overlap(digits, dig_w, c, c_w)) {
+        CK_TRY(blk_modup(ctx, c, 0, nullptr, 1, level, digits, (uint64_t *)w));
+        return CKKS_OK;
+    }
+    CK_TRY(ks_modup(ctx, c, level, (uint64_t *)w, ctx->alpha));
+    HIP_TRY(hipMemcpyAsync(digits, w, dig_w * 8, hipMemcpyDeviceToDevice, ctx->stream));
     return CKKS_OK;
 }
 

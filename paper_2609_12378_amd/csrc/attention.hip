@@ -567,30 +567,30 @@ extern "C" ckks_status ckks_attention_scores(ckks_ctx *ctx, const ckks_buf *q, u
         for (uint32_t d = 1; d < T; d++) outs[d - 1] = A + (size_t)d * ctw;
         CK_TRY(rotate_core(ctx, q[c].data, level, qsteps.data(), qkeys.data(), T - 1, outs.data(), work));
         // 2. products, relinearised in one batch (key switching with sigma = identity and the relinearisation
-        //    key: (d0 + u0, u1), then d1 added)
+        //    key: (d0 + u0, d1 + u1))
         CK_TRY(launch_tensor_batch(ctx, Dt, Dt + L * N, Dt + 2 * L * N, 3 * L * N, A, ctw, B, ctw, T, L));
         {
             const uint32_t ext = L + ctx->n_p, nd = n_digits(ctx, level);
             const size_t dig_ct = (size_t)nd * ext * N;
             uint64_t *digits = work;
             uint64_t *rw = digits + (size_t)T * (dig_ct + (size_t)ctx->alpha * N);
-            CK_TRY(ks_modup_batch(ctx, Dt + 2 * (size_t)L * N, 3 * (size_t)L * N, T, level, digits));
             const uint32_t bs = ks_rot_batch(T);
+            CK_TRY(ks_modup_batch(ctx, Dt + 2 * (size_t)L * N, 3 * (size_t)L * N, T, level, digits,
+                                  ks_stage_rows(ctx, level, bs, T)));
             std::vector<uint32_t> g(T, 1u);
-            std::vector<const uint64_t *> c0s(T), digs(T), rk(T, rlk);
+            std::vector<const uint64_t *> c0s(T), c1s(T), digs(T), rk(T, rlk);
             std::vector<uint64_t *> po(T);
             for (uint32_t d = 0; d < T; d++) {
                 c0s[d] = Dt + (size_t)d * 3 * L * N;
+                c1s[d] = c0s[d] + L * N;
                 digs[d] = digits + (size_t)d * dig_ct;
                 po[d] = Pr + (size_t)d * ctw;
             }
             for (uint32_t r0 = 0; r0 < T; r0 += bs) {
                 const uint32_t cnt = std::min(bs, T - r0);
                 CK_TRY(ks_rotate_batch(ctx, level, cnt, c0s.data() + r0, digs.data() + r0, g.data() + r0,
-                                       rk.data() + r0, po.data() + r0, rw));
+                                       rk.data() + r0, po.data() + r0, rw, nullptr, c1s.data() + r0));
             }
-            CK_TRY(launch_binary_batch(ctx, Pr + (size_t)L * N, ctw, Pr + (size_t)L * N, ctw, Dt + (size_t)L * N,
-                                       3 * (size_t)L * N, T, L, limb_range(0, L), EW_ADD));
         }
         // 3. U_k = sum_delta M_{(delta + k) mod hd} P_delta = z[-k mod hd] for every k, then each rotated by k
         //    (in chunks) and summed
@@ -720,11 +720,11 @@ extern "C" ckks_status ckks_attention_apply(ckks_ctx *ctx, const ckks_buf *p, ui
         {
             const uint32_t ext = Lp + ctx->n_p, nd = n_digits(ctx, lp);
             uint64_t *digits = work;
-            uint64_t *u = digits + ((size_t)nd * ext + ctx->alpha) * N;
-            uint64_t *cw = u + 2 * (size_t)ext * N;
-            CK_TRY(ks_modup(ctx, Dacc + 2 * (size_t)Lp * N, lp, digits));
-            CK_TRY(ks_inner_product(ctx, digits, nd, rlk, lp, 1, u));
-            CK_TRY(ks_moddown(ctx, u, 2, lp, Dacc, 1, Dacc + (size_t)Lp * N, O, cw));
+            uint64_t *rw = digits + ((size_t)nd * ext + ctx->alpha) * N;
+            CK_TRY(ks_modup(ctx, Dacc + 2 * (size_t)Lp * N, lp, digits, ks_stage_rows(ctx, lp, 1, 1)));
+            const uint64_t *c0 = Dacc, *add1 = Dacc + (size_t)Lp * N, *dig = digits;
+            const uint32_t g = 1;
+            CK_TRY(ks_rotate_batch(ctx, lp, 1, &c0, &dig, &g, &rlk, &O, rw, nullptr, &add1));
         }
         CK_TRY(rescale_core(ctx, O, lp, out[c].data, work));
         out[c].scale = p[c].scale * v[vv].scale / (double)ctx->primes[lp];

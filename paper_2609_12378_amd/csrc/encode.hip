@@ -216,10 +216,11 @@ __global__ __launch_bounds__(256) void k_fft_a8(double2 *a, const double2 *__res
 // pass-B outputs v_k, k = 256 u' + c (u' < 128; m_n = round(c Re v_n) for n < M and m_{n+M} = round(c Im v_n)),
 // i.e. pass-B columns c' = k mod 2048 = 256 (u' mod 8) + c at depths h = u' / 8.  Its 512 threads compute those
 // 128 pass-B columns (four threads per column, two stages in registers, an LDS exchange, two more), round into an
-// int64 tile in LDS, and run the 8-residue column transform of every limb from that tile (as ntt_col8_from_i64).
+// tile of integer-valued doubles in LDS, and run the 8-residue column transform of every limb from that tile (as
+// ntt_col8_from_i64).
 // The pass-B butterflies, twist and rounding are the same arithmetic as in k_fft_b, so the coefficients are the
 // same integers, and they never go to HBM.
-__global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restrict__ work, uint64_t *out,
+__global__ __launch_bounds__(512, 4) void ntt_col8_from_fft(const double2 *__restrict__ work, uint64_t *out,
                                                          uint32_t limbs, const ModQ *__restrict__ mods,
                                                          const double *__restrict__ twf,
                                                          const double2 *__restrict__ fw,
@@ -230,7 +231,10 @@ __global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restri
     constexpr uint32_t log_n = 16, M = 1u << 15, MT_PITCH = 17;
     __shared__ double tws[2][256];
     __shared__ double tr[16][nttc::kTr8];  // also the pass-B exchange buffer (2048 double2 with padding)
-    __shared__ int64_t mt[256 * MT_PITCH];
+    // the rounded coefficients (integers as doubles) [256][17], then (each thread's in its registers) the second transpose's region
+    __shared__ double trb[16][nttc::kTr8];
+    double *mt = &trb[0][0];
+    static_assert(256 * MT_PITCH <= 16 * nttc::kTr8, "the tile fits the transpose region");
     const uint32_t b = blockIdx.x >> 4, c0 = (blockIdx.x & 15u) << 4, tid = threadIdx.x;
     // ---- pass B for columns c' = 256 w8 + c0 + cc, ci = 16 w8 + cc, depths h = 4 qq + j
     {
@@ -280,8 +284,8 @@ __global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restri
         for (int j = 0; j < 4; j++) {
             const uint32_t h = qq + 4 * j, k = (h << 11) + cp, u = (h << 3) + w8;
             const double2 v = cmul(twist[k], x[j]);
-            mt[u * MT_PITCH + cc] = (int64_t)round(cs * v.x);
-            mt[(u + 128) * MT_PITCH + cc] = (int64_t)round(cs * v.y);
+            mt[u * MT_PITCH + cc] = round(cs * v.x);
+            mt[(u + 128) * MT_PITCH + cc] = round(cs * v.y);
         }
     }
     if (tid < 255) tws[0][tid + 1] = twf[tid + 1];
@@ -291,12 +295,12 @@ __global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restri
     const size_t coff = c0 + col;
     double vd[kE8];
     bool big = false, wide = false;
+    const double smalld = (double)small;
 #pragma unroll
     for (int k = 0; k < kE8; k++) {
-        const int64_t v = mt[nttc::u8<0>(t, k) * MT_PITCH + col];
-        big |= v > (1ll << 52) || v < -(1ll << 52);
-        wide |= v > small || v < -small;
-        vd[k] = (double)v;
+        vd[k] = mt[nttc::u8<0>(t, k) * MT_PITCH + col];
+        big |= fabs(vd[k]) > 4503599627370496.0;
+        wide |= fabs(vd[k]) > smalld;
     }
     // every coefficient of the wave below every limb's q/2 (weights at the usual scales): its range reduction is
     // the identity, so the wave skips it for all limbs
@@ -304,8 +308,8 @@ __global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restri
     for (uint32_t l = 0; l < limbs; l++) {
         const ModQ md = mods[l];
         const nttc::Ar<true> ar(md);
-        double wnext = 0.0;
-        if (l + 1 < limbs && tid < 255) wnext = twf[((size_t)(l + 1) << log_n) + tid + 1];
+        nttc::StageNext next{tws[(l + 1) & 1], 0.0, l + 1 < limbs && tid < 255};
+        if (next.on) next.v = twf[((size_t)(l + 1) << log_n) + tid + 1];
         double x[kE8];
         if (!reduce) {
 #pragma unroll
@@ -315,31 +319,9 @@ __global__ __launch_bounds__(512) void ntt_col8_from_fft(const double2 *__restri
             for (int k = 0; k < kE8; k++) x[k] = ar.red(vd[k]);
         } else {
 #pragma unroll
-            for (int k = 0; k < kE8; k++) x[k] = ar.from_i64(mt[nttc::u8<0>(t, k) * MT_PITCH + col], md);
+            for (int k = 0; k < kE8; k++) x[k] = ar.from_i64((int64_t)vd[k], md);
         }
-        const double *tw = tws[l & 1];
-        double *trc = tr[col];
-        nttc::fwd8_stage<0, 0, (nttc::kColMask8 >> 0) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<0, 1, (nttc::kColMask8 >> 1) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<0, 2, (nttc::kColMask8 >> 2) & 1>(x, tw, t, ar);
-#pragma unroll
-        for (int k = 0; k < kE8; k++) trc[nttc::pad_ac(nttc::u8<0>(t, k))] = x[k];
-        __syncthreads();
-        if (l + 1 < limbs && tid < 255) tws[(l + 1) & 1][tid + 1] = wnext;
-#pragma unroll
-        for (int k = 0; k < kE8; k++) x[k] = trc[nttc::pad_ac(nttc::u8<1>(t, k))];
-        __syncthreads();
-        nttc::fwd8_stage<1, 3, (nttc::kColMask8 >> 3) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<1, 4, (nttc::kColMask8 >> 4) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<1, 5, (nttc::kColMask8 >> 5) & 1>(x, tw, t, ar);
-#pragma unroll
-        for (int k = 0; k < kE8; k++) trc[nttc::pad_cb(nttc::u8<1>(t, k))] = x[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kE8; k++) x[k] = trc[nttc::pad_cb(nttc::u8<2>(t, k))];
-        __syncthreads();
-        nttc::fwd8_stage<2, 6, (nttc::kColMask8 >> 6) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<2, 7, (nttc::kColMask8 >> 7) & 1>(x, tw, t, ar);
+        nttc::fwd8_256_loop<nttc::kColMask8>(x, tws[l & 1], tr[col], trb[col], t, ar, next);
         uint64_t *dst = out + (((size_t)b * limbs + l) << log_n) + coff;
 #pragma unroll
         for (int k = 0; k < kE8; k++) nttc::st_stream(dst + (size_t)nttc::u8<2>(t, k) * 256, nttc::Ar<true>::to_raw(x[k]));

@@ -22,20 +22,11 @@
 #include "ckks_internal.h"
 #include "ntt_core.h"
 #include "ops.h"
-#include "philox.h"
+#include "ks_args.h"
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRotBatch = 32;  // rotations per batched launch
-
-__device__ __forceinline__ uint32_t auto_index(uint32_t j, uint32_t g, uint32_t log_n)
-{
-    const uint32_t two_n_mask = (2u << log_n) - 1;
-    const uint32_t k = 2u * (__brev(j) >> (32 - log_n)) + 1u;
-    const uint32_t kg = (uint32_t)(((uint64_t)k * g) & two_n_mask);
-    return __brev((kg - 1u) >> 1) >> (32 - log_n);
-}
 
 struct ConvArgs {
     int ns, nt;
@@ -188,32 +179,24 @@ __global__ __launch_bounds__(kThreads) void k_conv_f64(const uint64_t *in, uint3
 // pass, read by the ModDown).  Target t + 1's twiddles (Psi[1..255]) are staged into the idle half of a
 // double-buffered table while target t is transformed.  EXACT: ns == 8 (no guards on the source loop, all
 // source loads issued first).
-struct StageNext {
-    double *dst;
-    double v;
-    bool on;
-    __device__ void operator()() const
-    {
-        if (on) dst[threadIdx.x + 1] = v;
-    }
-};
-
 template <bool EXACT>
 __global__ __launch_bounds__(512) void k_conv_col8(const uint64_t *__restrict__ in, uint32_t in_stride,
                                                    uint64_t *out, uint32_t out_stride, uint32_t split, uint32_t skip,
                                                    ConvArgs a, const double *__restrict__ qhat_inv,
                                                    const double *__restrict__ qhat_mod,
                                                    const ModQ *__restrict__ mods, const double *__restrict__ twf,
-                                                   uint32_t log_n, uint32_t blocks_per_row)
+                                                   uint32_t log_n, uint32_t blocks_per_row, uint32_t t_per)
 {
     using nttc::Ar;
     using nttc::kE8;
     __shared__ double s_mod[8 * kMaxPrimes];
     __shared__ double tws[2][256];
-    __shared__ double tr[16][nttc::kTr8];
+    __shared__ double tr[16][nttc::kTr8], trb[16][nttc::kTr8];
     const int ns = EXACT ? 8 : a.ns, nt = a.nt;
     for (int k = threadIdx.x; k < ns * nt; k += 512) s_mod[k] = qhat_mod[k];
-    if (threadIdx.x < 255) tws[0][threadIdx.x + 1] = twf[((size_t)a.dst[0] << log_n) + threadIdx.x + 1];
+    // blockIdx.y: this block's group of t_per targets
+    const int t0 = (int)(blockIdx.y * t_per), t1 = min(nt, t0 + (int)t_per);
+    if (threadIdx.x < 255) tws[t0 & 1][threadIdx.x + 1] = twf[((size_t)a.dst[t0] << log_n) + threadIdx.x + 1];
     const uint32_t poly = blockIdx.x / blocks_per_row, blk = blockIdx.x % blocks_per_row;
     const uint32_t n2 = 1u << (log_n - 8);
     const uint32_t col = threadIdx.x & 15, t = threadIdx.x >> 4;
@@ -239,9 +222,9 @@ __global__ __launch_bounds__(512) void k_conv_col8(const uint64_t *__restrict__ 
         }
     }
     __syncthreads();
-    for (int tt = 0; tt < nt; tt++) {
+    for (int tt = t0; tt < t1; tt++) {
         const Ar<true> ar(mods[a.dst[tt]]);
-        StageNext next{tws[(tt + 1) & 1], 0.0, tt + 1 < nt && threadIdx.x < 255};
+        nttc::StageNext next{tws[(tt + 1) & 1], 0.0, tt + 1 < t1 && threadIdx.x < 255};
         if (next.on) next.v = twf[((size_t)a.dst[tt + 1] << log_n) + threadIdx.x + 1];
         double x[kE8];
 #pragma unroll
@@ -252,36 +235,12 @@ __global__ __launch_bounds__(512) void k_conv_col8(const uint64_t *__restrict__ 
                 if (EXACT || i < ns) acc.add(y[k][i], s_mod[i * nt + tt]);
             x[k] = ar.red(acc.value(ar));
         }
-        nttc::fwd8_256<nttc::kColMask8>(x, tws[tt & 1], tr[col], t, ar, 1, next);
+        nttc::fwd8_256_loop<nttc::kColMask8>(x, tws[tt & 1], tr[col], trb[col], t, ar, next);
         const uint32_t row = tt < (int)split ? tt : tt + skip;
         uint64_t *dst = out + (((size_t)poly * out_stride + row) << log_n) + coff;
 #pragma unroll
         for (int k = 0; k < kE8; k++) nttc::st_stream(dst + (size_t)nttc::u8<2>(t, k) * n2, Ar<true>::to_raw(x[k]));
     }
-}
-
-// u[k][r][n] = sum_{j<nd} d_j[r][sigma(n)] * key[j][k][krow(r)][n], rows r over Q_level u P
-__global__ __launch_bounds__(kThreads) void k_key_ip(const uint64_t *__restrict__ digits,
-                                                      const uint64_t *__restrict__ key, uint64_t *u, uint32_t nd,
-                                                      uint32_t ext, uint32_t level, uint32_t n_q, uint32_t key_rows,
-                                                      uint32_t g, const ModQ *__restrict__ mods, uint32_t log_n)
-{
-    const uint32_t n = 1u << log_n;
-    const uint32_t col = blockIdx.x * kThreads + threadIdx.x;
-    const uint32_t r = blockIdx.y;
-    if (col >= n) return;
-    const uint32_t prime = r <= level ? r : n_q + (r - level - 1);
-    const ModQ m = mods[prime];
-    const uint32_t sc = g == 1 ? col : auto_index(col, g, log_n);
-    acc128 a0{0, 0}, a1{0, 0};
-    for (uint32_t j = 0; j < nd; j++) {
-        const uint64_t d = digits[(((size_t)j * ext + r) << log_n) + sc];
-        const size_t kb = ((size_t)j * 2 * key_rows + prime) << log_n;
-        mac(a0, d, key[kb + col]);
-        mac(a1, d, key[kb + ((size_t)key_rows << log_n) + col]);
-    }
-    u[((size_t)r << log_n) + col] = reduce128(a0, m);
-    u[(((size_t)ext + r) << log_n) + col] = reduce128(a1, m);
 }
 
 // out[k][i][n] = (u[k][i][n] - c[k][i][n]) * P^-1 + add_k[i][sigma_k(n)], i <= level
@@ -308,49 +267,6 @@ __global__ __launch_bounds__(kThreads) void k_moddown_finish(uint64_t *out, cons
     }
     out[(((size_t)k * L + i) << log_n) + col] = r;
 }
-
-// Batched rotations: rotation r of the batch uses Galois element g[r], key
-// key[r], the ModUp digits dig[r] and c0[r] of its input, and writes out[r];
-// hoisted rotations of one ciphertext share dig and c0.
-struct RotArgs {
-    uint32_t count;
-    uint32_t g[kRotBatch];
-    const uint64_t *key[kRotBatch];
-    uint64_t *out[kRotBatch];
-    const uint64_t *dig[kRotBatch];  // ModUp digits [nd][ext][N] of the rotated ciphertext
-    const uint64_t *c0[kRotBatch];   // its c0 [level+1][N]
-    // seed-expanded keys (the SEEDED kernels): key[r] is the b half [nd][key_rows][N] and seed[r] the seed of a
-    uint64_t seed[kRotBatch][2];
-};
-
-// Where rotation r's key words for digit j, key row `krow`, position `pos` come from: b (and, stored, a) from the
-// key; a seed-expanded key computes a (q = the row's modulus) from its seed, four digits per Philox block.
-template <bool SEEDED>
-struct KeyRow {
-    const uint64_t *key;
-    size_t kstride;      // words between the b and a halves (stored keys)
-    uint32_t key_rows, log_n, prime, pos, shift;
-    uint64_t q, s0, s1;
-    uint64_t blk[4];
-    __device__ KeyRow(const RotArgs &ra, uint32_t r, uint32_t key_rows_, uint32_t log_n_, uint32_t prime_,
-                      uint32_t pos_, uint64_t q_)
-        : key(ra.key[r]), kstride((size_t)key_rows_ << log_n_), key_rows(key_rows_), log_n(log_n_), prime(prime_),
-          pos(pos_), shift(seedk::shift_of(q_)), q(q_), s0(ra.seed[r][0]), s1(ra.seed[r][1])
-    {
-    }
-    __device__ uint64_t b(uint32_t j) const
-    {
-        const size_t row = SEEDED ? (size_t)j * key_rows + prime : (size_t)j * 2 * key_rows + prime;
-        return nttc::ld_stream(key + (row << log_n) + pos);
-    }
-    __device__ uint64_t a(uint32_t j)
-    {
-        if (!SEEDED) return nttc::ld_stream(key + (((size_t)j * 2 * key_rows + prime) << log_n) + kstride + pos);
-        const uint32_t m = j & 3;
-        if (m == 0) seedk::block_residues(s0, s1, pos, prime, j >> 2, q, shift, blk);
-        return m == 0 ? blk[0] : m == 1 ? blk[1] : m == 2 ? blk[2] : blk[3];
-    }
-};
 
 // The key inner products of the 8 positions pos[e] of one thread (fp64, primes below 2^50):
 //   u0[e], u1[e] = sum_j sigma_{g_r}(d_j)[row][pos[e]] * (b_j, a_j)[prime][pos[e]],  sc[e] = sigma^-1 position,
@@ -639,7 +555,7 @@ __global__ __launch_bounds__(64) void k_key_ip_intt8(RotArgs ra, uint64_t *up, u
 // ModDown of a batch of rotations, fused (fp64, 256-point rows)// ModDown of a batch of rotations, fused (fp64, 256-point rows): block (r, q-limb i, two rows h) finishes the
 // forward transform of the converted P part cw[r][k][i] (its first pass already done), computes the q-limb part
 // of the key inner product u_k = sum_j sigma_{g_r}(d_j)[i] * key_r[j][k][i] in registers, and writes
-//   out_r[k][i] = (u_k - NTT(cw[r][k][i])) * P^-1 (+ sigma_{g_r}(c0)[i] for k = 0),
+//   out_r[k][i] = (u_k - NTT(cw[r][k][i])) * P^-1 (+ sigma_{g_r}(c0)[i] for k = 0, + add1[i] if set for k = 1),
 // so neither the q-limb rows of u nor the transformed conversion ever go to HBM.  Magnitudes (units of q):
 // column-pass outputs <= 4.3 (from inputs reduced to q/2), transform outputs <= 2.6, each product <= 0.875 and the
 // sum range-reduced every 4 digits (<= 4), differences <= 6.6, P^-1 products <= 3, plus c0 < 1: all below 8 q = 2^53.
@@ -676,7 +592,7 @@ __global__ __launch_bounds__(64) void k_ks_finish8(RotArgs ra, const uint64_t *_
     }
     const uint32_t g = ra.g[r];
     uint64_t *out = ra.out[r];
-    const uint64_t *digits = ra.dig[r], *c0 = ra.c0[r];
+    const uint64_t *digits = ra.dig[r], *c0 = ra.c0[r], *add1 = ra.add1[r];
     const double pi = (double)pinv[i].x;
     const uint64_t qi = mods[i].q;
 #pragma unroll
@@ -695,7 +611,8 @@ __global__ __launch_bounds__(64) void k_ks_finish8(RotArgs ra, const uint64_t *_
             }
         }
         const double r0 = ar.mul(u0 - v[0][e], pi) + nttc::Ar<true>::from_u64(c0[((size_t)i << log_n) + sc]);
-        const double r1 = ar.mul(u1 - v[1][e], pi);
+        double r1 = ar.mul(u1 - v[1][e], pi);
+        if (add1) r1 += nttc::Ar<true>::from_u64(nttc::ld_stream(add1 + ((size_t)i << log_n) + pos));
         nttc::st_stream(out + ((size_t)i << log_n) + pos, ar.to_canon(r0));
         nttc::st_stream(out + (((size_t)L + i) << log_n) + pos, ar.to_canon(r1));
     }
@@ -760,7 +677,7 @@ __global__ __launch_bounds__(64) void k_ks_finish8_seeded(RotArgs ra, const uint
     }
 }
 
-// out_r[k][i][n] = (u[r][k][i][n] - c[r][k][i][n]) * P^-1 (+ c0[i][sigma_{g_r}(n)] for k = 0)
+// out_r[k][i][n] = (u[r][k][i][n] - c[r][k][i][n]) * P^-1 (+ c0[i][sigma_{g_r}(n)] for k = 0, + add1[i] for k = 1)
 __global__ __launch_bounds__(kThreads) void k_moddown_finish_batch(RotArgs ra, const uint64_t *u, const uint64_t *c,
                                                                     uint32_t ext, uint32_t level,
                                                                     const ulonglong2 *__restrict__ pinv,
@@ -777,6 +694,7 @@ __global__ __launch_bounds__(kThreads) void k_moddown_finish_batch(RotArgs ra, c
     const ulonglong2 w = pinv[i];
     uint64_t res = shoup(submod(x, cv, q), w.x, w.y, q);
     if (k == 0) res = addmod(res, ra.c0[r][((size_t)i << log_n) + auto_index(col, ra.g[r], log_n)], q);
+    else if (ra.add1[r]) res = addmod(res, ra.add1[r][((size_t)i << log_n) + col], q);
     ra.out[r][(((size_t)k * L + i) << log_n) + col] = res;
 }
 
@@ -863,16 +781,21 @@ ckks_status launch_conv_col8(ckks_ctx *ctx, const ConvDev *cd, const uint64_t *i
     for (int t = 0; t < cd->nt; t++) a.dst[t] = cd->dst[t];
     const uint32_t bpr = 1u << (ctx->log_n - 12);
     const double res = (double)polys * ctx->n;
+    // fewer than 256 blocks (one a CU): the targets split over blockIdx.y until the grid has that many, each group
+    // forming the centred digits again (one relinearisation at 13 limbs, 32 blocks: 61 -> 16 us)
+    const uint32_t want = std::max(1u, 256u / (polys * bpr)), ntu = (uint32_t)a.nt;
+    const uint32_t t_per = (ntu + std::min(want, ntu) - 1) / std::min(want, ntu);
+    const dim3 grid(polys * bpr, (ntu + t_per - 1) / t_per);
     // the sources once, the converted rows once; the conversion products and the column pass's butterflies
     prof_begin(ctx, K_CONV, 8.0 * res * (a.ns + a.nt), res * a.nt * (a.ns * 5.0 + kOpsButterflyF64 * 4));
     if (a.ns == 8)
-        hipLaunchKernelGGL(k_conv_col8<true>, dim3(polys * bpr), dim3(512), 0, ctx->stream, in, in_stride, out,
+        hipLaunchKernelGGL(k_conv_col8<true>, grid, dim3(512), 0, ctx->stream, in, in_stride, out,
                            out_stride, split, skip, a, cd->d_qhat_inv_f, cd->d_qhat_mod_f, ctx->d_mod, ctx->d_twf,
-                           ctx->log_n, bpr);
+                           ctx->log_n, bpr, t_per);
     else
-        hipLaunchKernelGGL(k_conv_col8<false>, dim3(polys * bpr), dim3(512), 0, ctx->stream, in, in_stride, out,
+        hipLaunchKernelGGL(k_conv_col8<false>, grid, dim3(512), 0, ctx->stream, in, in_stride, out,
                            out_stride, split, skip, a, cd->d_qhat_inv_f, cd->d_qhat_mod_f, ctx->d_mod, ctx->d_twf,
-                           ctx->log_n, bpr);
+                           ctx->log_n, bpr, t_per);
     prof_end(ctx, K_CONV);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -936,8 +859,10 @@ size_t ks_scratch_words(const ckks_ctx *ctx, uint32_t level, uint32_t batch, uin
 
 ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const uint64_t *const *c0s,
                             const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
-                            uint64_t *const *outs, uint64_t *work, const uint64_t *seeds)
+                            uint64_t *const *outs, uint64_t *work, const uint64_t *seeds,
+                            const uint64_t *const *add1)
 {
+    CK_REQUIRE(!(seeds && add1), CKKS_EINVAL, "rotation batch: an addend with seeded keys");
     CK_REQUIRE(count >= 1 && count <= (uint32_t)kRotBatch, CKKS_EINVAL, "rotation batch of %u", count);
     const uint32_t L = level + 1, K = ctx->n_p, ext = L + K, nd = n_digits(ctx, level);
     const size_t N = ctx->n;
@@ -950,11 +875,13 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
         ra.out[r] = outs[r];
         ra.dig[r] = digs[r];
         ra.c0[r] = c0s[r];
+        ra.add1[r] = add1 ? add1[r] : nullptr;
         if (seeded) {
             ra.seed[r][0] = seeds[2 * r];
             ra.seed[r][1] = seeds[2 * r + 1];
         }
     }
+    if (!seeded && blk_rotations(ctx, level, count)) return blk_rotate_batch(ctx, level, ra, work);
     // a seeded key holds its b half only: key_rows rows per digit instead of 2 key_rows
     const uint32_t kp = ctx->n_primes();
     int s1, s2;
@@ -1094,9 +1021,12 @@ ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, cons
 }
 
 ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, uint32_t count, uint32_t level,
-                           uint64_t *digits)
+                           uint64_t *digits, size_t stage_rows)
 {
     if (!count) return CKKS_OK;
+    if (blk_switch(ctx, level) && (size_t)count * (level + 1) <= stage_rows)
+        return blk_modup(ctx, c1, count == 1 ? 0 : in_stride, nullptr, count, level, digits,
+                         digits + (size_t)count * n_digits(ctx, level) * (level + 1 + ctx->n_p) * ctx->n);
     const uint32_t K = ctx->n_p, ext = level + 1 + K, nd = n_digits(ctx, level), alpha = ctx->alpha;
     const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
     const size_t cstride = count == 1 ? 0 : in_stride;
@@ -1139,23 +1069,25 @@ ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, 
     return CKKS_OK;
 }
 
-ckks_status ks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_t *digits)
+ckks_status ks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_t *digits, size_t stage_rows)
 {
-    return ks_modup_batch(ctx, c, 0, 1, level, digits);
+    return ks_modup_batch(ctx, c, 0, 1, level, digits, stage_rows);
 }
 
-ckks_status ks_inner_product(ckks_ctx *ctx, const uint64_t *digits, uint32_t nd, const uint64_t *key,
-                             uint32_t level, uint32_t g, uint64_t *u)
+ckks_status ks_mul_relin_blk(ckks_ctx *ctx, const uint64_t *a, const uint64_t *b, const uint64_t *rlk, uint32_t level,
+                             uint64_t *out, uint64_t *work)
 {
-    const uint32_t ext = level + 1 + ctx->n_p;
-    const dim3 grid((ctx->n + kThreads - 1) / kThreads, ext), block(kThreads);
-    // digits (nd rows of ext), key rows (nd x 2 x ext), two outputs of ext rows
-    prof_begin(ctx, K_KEYIP, 8.0 * ctx->n * ext * (3.0 * nd + 2.0));
-    hipLaunchKernelGGL(k_key_ip, grid, block, 0, ctx->stream, digits, key, u, nd, ext, level, ctx->n_q,
-                       ctx->n_primes(), g, ctx->d_mod, ctx->log_n);
-    prof_end(ctx, K_KEYIP);
-    HIP_TRY(hipGetLastError());
-    return CKKS_OK;
+    const uint32_t L = level + 1, ext = L + ctx->n_p, nd = n_digits(ctx, level);
+    const size_t N = ctx->n;
+    uint64_t *digits = work, *rest = digits + (size_t)nd * ext * N;
+    CK_TRY(blk_modup(ctx, a + (size_t)L * N, 0, b, 1, level, digits, rest));
+    RotArgs ra{};
+    ra.count = 1;
+    ra.g[0] = 1;
+    ra.key[0] = rlk;
+    ra.out[0] = out;
+    ra.dig[0] = digits;
+    return blk_rotate_batch(ctx, level, ra, rest, a, b);
 }
 
 ckks_status ks_moddown(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t level, const uint64_t *add0,
@@ -1163,6 +1095,7 @@ ckks_status ks_moddown(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t leve
 {
     const uint32_t K = ctx->n_p, ext = level + 1 + K, L = level + 1;
     const size_t N = ctx->n;
+    if (blk_switch(ctx, level)) return blk_moddown(ctx, u, polys, level, add0, add0_g, add1, out);
     // INTT of the P rows of every polynomial, in place
     LimbMap pm = limb_range(ctx->n_q, K);
     CK_TRY(launch_ntt_strided(ctx, u + (size_t)L * N, polys, ext, pm, true));

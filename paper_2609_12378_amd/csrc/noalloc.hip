@@ -73,7 +73,7 @@ extern "C" ckks_status ckks_rotate_noalloc(ckks_ctx *ctx, const ckks_buf *in, in
     const uint64_t *c0 = in->data, *dig = digits;
     const uint32_t g = ckks_galois_elt(ctx, steps);
     uint64_t *o = out->data;
-    ckks_status st = ks_modup(ctx, in->data + (size_t)L * ctx->n, level, digits);
+    ckks_status st = ks_modup(ctx, in->data + (size_t)L * ctx->n, level, digits, ks_stage_rows(ctx, level, 1, 1));
     if (st == CKKS_OK) st = ks_rotate_batch(ctx, level, 1, &c0, &dig, &g, &key, &o, rw);
     ctx->profiling = profiling;
     if (st == CKKS_OK) out->scale = in->scale;

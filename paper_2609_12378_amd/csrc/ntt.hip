@@ -34,6 +34,7 @@
 //    below 2^53.  The inverse's last stage carries N^-1 (Ar<true>::gs_scaled).
 // Between the two passes the row holds lazy values (integer) or raw double
 // bits (fp64); the last pass writes canonical residues in [0, q).
+#include <algorithm>
 #include <type_traits>
 
 #include "ckks_internal.h"
@@ -142,7 +143,7 @@ template <int LOGS, bool F>
 __global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restrict__ m, uint64_t *out, uint32_t limbs,
                                                         const ModQ *mods, const void *tw_all, uint32_t log_n,
                                                         uint32_t cols_per_block, uint32_t blocks_per_row,
-                                                        int64_t small)
+                                                        int64_t small, uint32_t l_per)
 {
     using E = typename Ar<F>::E;
     constexpr uint32_t TS = (1u << LOGS) / 16;
@@ -173,7 +174,9 @@ __global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restric
         for (int k = 0; k < kE; k++) wide |= v[k] > small || v[k] < -small;
     }
     const bool reduce = __any(wide);
-    for (uint32_t l = 0; l < limbs; l++) {
+    // blockIdx.y: this block's group of l_per limbs
+    const uint32_t l0 = blockIdx.y * l_per, l1 = min(limbs, l0 + l_per);
+    for (uint32_t l = l0; l < l1; l++) {
         const ModQ md = mods[l];
         const Ar<F> ar(md);
         const typename Ar<F>::W *tw = twp<F>(tw_all, l, log_n);
@@ -215,11 +218,12 @@ __global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restric
 // table while limb l is transformed.
 __global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restrict__ m, uint64_t *out,
                                                          uint32_t limbs, const ModQ *mods, const double *twf,
-                                                         uint32_t log_n, uint32_t blocks_per_row, int64_t small)
+                                                         uint32_t log_n, uint32_t blocks_per_row, int64_t small,
+                                                         uint32_t l_per)
 {
     using nttc::kE8;
     __shared__ double tws[2][256];
-    __shared__ double tr[16][nttc::kTr8];
+    __shared__ double tr[16][nttc::kTr8], trb[16][nttc::kTr8];
     const uint32_t b = blockIdx.x / blocks_per_row, blk = blockIdx.x % blocks_per_row;
     const uint32_t n2 = 1u << (log_n - 8);
     const uint32_t col = threadIdx.x & 15, t = threadIdx.x >> 4;
@@ -238,15 +242,17 @@ __global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restri
     }
     // coefficients below every limb's q/2 throughout the wave: the range reduction is the identity, skipped
     const bool reduce = __any(wide);
-    if (threadIdx.x < 255) tws[0][threadIdx.x + 1] = twf[threadIdx.x + 1];
+    // blockIdx.y: this block's group of l_per limbs
+    const uint32_t l0 = blockIdx.y * l_per, l1 = min(limbs, l0 + l_per);
+    if (threadIdx.x < 255) tws[l0 & 1][threadIdx.x + 1] = twf[((size_t)l0 << log_n) + threadIdx.x + 1];
     __syncthreads();
-    for (uint32_t l = 0; l < limbs; l++) {
+    for (uint32_t l = l0; l < l1; l++) {
         const ModQ md = mods[l];
         const Ar<true> ar(md);
         // next limb's twiddle, written to the other table after the first barrier of this limb (when every
         // thread has finished reading it for limb l - 1)
-        double wnext = 0.0;
-        if (l + 1 < limbs && threadIdx.x < 255) wnext = twf[((size_t)(l + 1) << log_n) + threadIdx.x + 1];
+        nttc::StageNext next{tws[(l + 1) & 1], 0.0, l + 1 < l1 && threadIdx.x < 255};
+        if (next.on) next.v = twf[((size_t)(l + 1) << log_n) + threadIdx.x + 1];
         double x[kE8];
         if (!reduce) {
 #pragma unroll
@@ -260,29 +266,7 @@ __global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restri
 #pragma unroll
             for (int k = 0; k < kE8; k++) x[k] = ar.from_i64(sg[(size_t)nttc::u8<0>(t, k) * n2], md);
         }
-        const double *tw = tws[l & 1];
-        double *trc = tr[col];
-        nttc::fwd8_stage<0, 0, (nttc::kColMask8 >> 0) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<0, 1, (nttc::kColMask8 >> 1) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<0, 2, (nttc::kColMask8 >> 2) & 1>(x, tw, t, ar);
-#pragma unroll
-        for (int k = 0; k < kE8; k++) trc[nttc::pad_ac(nttc::u8<0>(t, k))] = x[k];
-        __syncthreads();
-        if (l + 1 < limbs && threadIdx.x < 255) tws[(l + 1) & 1][threadIdx.x + 1] = wnext;
-#pragma unroll
-        for (int k = 0; k < kE8; k++) x[k] = trc[nttc::pad_ac(nttc::u8<1>(t, k))];
-        __syncthreads();
-        nttc::fwd8_stage<1, 3, (nttc::kColMask8 >> 3) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<1, 4, (nttc::kColMask8 >> 4) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<1, 5, (nttc::kColMask8 >> 5) & 1>(x, tw, t, ar);
-#pragma unroll
-        for (int k = 0; k < kE8; k++) trc[nttc::pad_cb(nttc::u8<1>(t, k))] = x[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kE8; k++) x[k] = trc[nttc::pad_cb(nttc::u8<2>(t, k))];
-        __syncthreads();
-        nttc::fwd8_stage<2, 6, (nttc::kColMask8 >> 6) & 1>(x, tw, t, ar);
-        nttc::fwd8_stage<2, 7, (nttc::kColMask8 >> 7) & 1>(x, tw, t, ar);
+        nttc::fwd8_256_loop<nttc::kColMask8>(x, tws[l & 1], tr[col], trb[col], t, ar, next);
         uint64_t *dst = out + (((size_t)b * limbs + l) << log_n) + coff;
 #pragma unroll
         for (int k = 0; k < kE8; k++) dst[(size_t)nttc::u8<2>(t, k) * n2] = Ar<true>::to_raw(x[k]);
@@ -415,6 +399,15 @@ hipError_t launch_row(ckks_ctx *ctx, uint64_t *data, uint32_t batch, uint32_t bs
     return hipGetLastError();
 }
 
+// limbs per block of a first pass over signed coefficients: all of them (the coefficients read and converted once)
+// while the blocks alone fill the chip; with fewer than `fill` blocks the limbs are split over blockIdx.y until the
+// grid has that many (one plaintext of 13 limbs at N = 2^16, 16 blocks: 34 -> 10 us)
+uint32_t limbs_per_block(uint32_t blocks, uint32_t limbs, uint32_t fill)
+{
+    const uint32_t groups = std::min(limbs, std::max(1u, fill / blocks));
+    return (limbs + groups - 1) / groups;
+}
+
 template <int LOGS, bool F>
 hipError_t launch_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32_t batch, uint32_t limbs)
 {
@@ -423,11 +416,13 @@ hipError_t launch_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32
     uint32_t cols = 4096u >> LOGS;
     if (cols > n2) cols = n2;
     const uint32_t bpr = n2 / cols;
-    const dim3 grid(batch * bpr), block(cols * TS);
+    // blocks of at most 256 threads: two a CU
+    const uint32_t l_per = limbs_per_block(batch * bpr, limbs, 512);
+    const dim3 grid(batch * bpr, (limbs + l_per - 1) / l_per), block(cols * TS);
     uint64_t qmin = ~0ull;
     for (uint32_t l = 0; l < limbs; l++) qmin = ctx->primes[l] < qmin ? ctx->primes[l] : qmin;
     hipLaunchKernelGGL((ntt_col_from_i64<LOGS, F>), grid, block, lds_bytes<LOGS>(cols), ctx->stream, m, out, limbs,
-                       ctx->d_mod, fwd_table<F>(ctx), ctx->log_n, cols, bpr, (int64_t)(qmin - 1));
+                       ctx->d_mod, fwd_table<F>(ctx), ctx->log_n, cols, bpr, (int64_t)(qmin - 1), l_per);
     return hipGetLastError();
 }
 
@@ -542,6 +537,8 @@ ckks_status launch_ntt_strided(ckks_ctx *ctx, uint64_t *data, uint32_t batch, ui
 {
     if (batch == 0 || map.n == 0) return CKKS_OK;
     CK_REQUIRE(map.n <= (uint32_t)kMaxLimbMap && bstride >= map.n, CKKS_EINVAL, "ntt: bad limb map");
+    if (blk_rows(ctx, (size_t)batch * map.n) && use_f64(ctx, map))
+        return blk_ntt(ctx, data, bstride, data, bstride, batch, map, inverse);
     const hipError_t e = use_f64(ctx, map) ? ntt_passes<true>(ctx, data, batch, bstride, map, inverse)
                                            : ntt_passes<false>(ctx, data, batch, bstride, map, inverse);
     if (e != hipSuccess) return set_error(CKKS_EHIP, "ntt launch failed: %s", hipGetErrorString(e));
@@ -613,8 +610,10 @@ ckks_status launch_ntt_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, u
     hipError_t e;
     if (f && s1 == 8) {
         const uint32_t bpr = (ctx->n >> 8) / 16;
-        hipLaunchKernelGGL(ntt_col8_from_i64, dim3(batch * bpr), dim3(512), 0, ctx->stream, m, out, limbs,
-                           ctx->d_mod, ctx->d_twf, ctx->log_n, bpr, identity_reduction_bound(ctx, limbs));
+        const uint32_t l_per = limbs_per_block(batch * bpr, limbs, 256);
+        hipLaunchKernelGGL(ntt_col8_from_i64, dim3(batch * bpr, (limbs + l_per - 1) / l_per), dim3(512), 0, ctx->stream,
+                           m, out, limbs, ctx->d_mod, ctx->d_twf, ctx->log_n, bpr,
+                           identity_reduction_bound(ctx, limbs), l_per);
         e = hipGetLastError();
     } else {
         e = f ? dispatch_col_i64<true>(s1, ctx, m, out, batch, limbs)
@@ -637,9 +636,10 @@ ckks_status launch_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, 
         CK_TRY(enc_to_rns(ctx, m, batch, limbs, out));
         return launch_ntt(ctx, out, batch * limbs, limb_range(0, limbs), false);
     }
-    CK_TRY(launch_ntt_col_i64(ctx, m, out, batch, limbs));
     const LimbMap map = limb_range(0, limbs);
     const bool f = use_f64(ctx, map);
+    if (f && blk_rows(ctx, (size_t)batch * limbs)) return blk_ntt_from_i64(ctx, m, out, batch, limbs);
+    CK_TRY(launch_ntt_col_i64(ctx, m, out, batch, limbs));
     const double res = (double)batch * limbs * ctx->n, bf = f ? kOpsButterflyF64 : kOpsButterflyInt;
     prof_begin(ctx, K_NTT_FWD_ROW, 16.0 * batch * limbs * ctx->n, res * bf * s2 / 2);
     const hipError_t e = f ? dispatch_row<false, false, true, true>(s2, ctx, out, batch, limbs, map)

@@ -374,6 +374,16 @@ __device__ __forceinline__ uint32_t pad_cb(uint32_t u) { return u + (u >> 3); }
 struct NoHook {
     __device__ void operator()() const {}
 };
+// stores this thread's twiddle of the next limb into the idle half of a double-buffered table
+struct StageNext {
+    double *dst;
+    double v;
+    bool on;
+    __device__ void operator()() const
+    {
+        if (on) dst[threadIdx.x + 1] = v;
+    }
+};
 
 // all eight forward stages of the sub-transform held by thread t (layout A in,
 // layout B out), reducing X at the stages set in RMASK; tr: this sub-transform's
@@ -406,6 +416,37 @@ __device__ __forceinline__ void fwd8_256(double (&x)[kE8], const double *tws, do
     __syncthreads();
     fwd8_stage<2, 6, (RMASK >> 6) & 1>(x, tws, t, ar, Bm);
     fwd8_stage<2, 7, (RMASK >> 7) & 1>(x, tws, t, ar, Bm);
+}
+
+// fwd8_256 for a block that runs it again and again (one call per limb or target): the second transpose has an
+// LDS region of its own (trb, like tr), so a call takes two barriers instead of four.  Nothing is overwritten
+// early: a call writes tr after the previous call's second barrier, which every thread reaches with its reads of tr
+// done, and trb after its own first barrier, which every thread reaches with the previous call's reads of trb
+// done.  hook() runs right after the first barrier, when the previous call's reads of its twiddle table are done;
+// the second barrier orders what it writes before the next call's reads.
+template <unsigned RMASK, typename Hook = NoHook>
+__device__ __forceinline__ void fwd8_256_loop(double (&x)[kE8], const double *tws, double *tr, double *trb, uint32_t t,
+                                              const Ar<true> &ar, Hook hook = Hook())
+{
+    fwd8_stage<0, 0, (RMASK >> 0) & 1>(x, tws, t, ar);
+    fwd8_stage<0, 1, (RMASK >> 1) & 1>(x, tws, t, ar);
+    fwd8_stage<0, 2, (RMASK >> 2) & 1>(x, tws, t, ar);
+#pragma unroll
+    for (int k = 0; k < kE8; k++) tr[pad_ac(u8<0>(t, k))] = x[k];
+    __syncthreads();
+    hook();
+#pragma unroll
+    for (int k = 0; k < kE8; k++) x[k] = tr[pad_ac(u8<1>(t, k))];
+    fwd8_stage<1, 3, (RMASK >> 3) & 1>(x, tws, t, ar);
+    fwd8_stage<1, 4, (RMASK >> 4) & 1>(x, tws, t, ar);
+    fwd8_stage<1, 5, (RMASK >> 5) & 1>(x, tws, t, ar);
+#pragma unroll
+    for (int k = 0; k < kE8; k++) trb[pad_cb(u8<1>(t, k))] = x[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kE8; k++) x[k] = trb[pad_cb(u8<2>(t, k))];
+    fwd8_stage<2, 6, (RMASK >> 6) & 1>(x, tws, t, ar);
+    fwd8_stage<2, 7, (RMASK >> 7) & 1>(x, tws, t, ar);
 }
 
 // layout B -> layout A through LDS (a word of padding every 32), so that

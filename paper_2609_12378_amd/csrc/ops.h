@@ -37,16 +37,19 @@ ckks_status launch_rescale_finish(ckks_ctx *ctx, uint64_t *out, const uint64_t *
                                   uint32_t polys, uint32_t l);
 
 // key switching (keyswitch.hip)
-// digits: [nd][level+1+K][N] from c ([level+1][N]); the buffer must hold alpha more rows
-// after the digits (staging for the INTT of a digit's limbs)
-ckks_status ks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_t *digits);
+// digits: [nd][level+1+K][N] from c ([level+1][N]), followed by stage_rows >= alpha staging rows (as ks_modup_batch)
+ckks_status ks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_t *digits, size_t stage_rows);
+// rows after the digits of `count` ciphertexts in a region of ks_scratch_words(ctx, level, batch, count) words: the
+// staging rows and the rotations' own scratch, which a ModUp may use before the rotations run
+inline size_t ks_stage_rows(const ckks_ctx *ctx, uint32_t level, uint32_t batch, uint32_t count)
+{
+    return (size_t)count * ctx->alpha + (size_t)batch * (2 * (level + 1 + ctx->n_p) + 2 * (level + 1));
+}
 // ModUp of `count` ciphertexts at once: c1 of ciphertext r at c1 + r * in_stride (words); digits: [count][nd][ext][N]
-// followed by count * alpha staging rows
+// followed by stage_rows staging rows: at least count * alpha; with count * (level+1) the whole-row kernels run
+// where the ring has them
 ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, uint32_t count, uint32_t level,
-                           uint64_t *digits);
-// (u0, u1) = sum_j sigma_g(d_j) (b_j, a_j); g = 1 for no automorphism; u: [2][level+1+K][N]
-ckks_status ks_inner_product(ckks_ctx *ctx, const uint64_t *digits, uint32_t nd, const uint64_t *key,
-                             uint32_t level, uint32_t g, uint64_t *u);
+                           uint64_t *digits, size_t stage_rows);
 // out_k = (u_k - Conv(INTT([u_k]_P))) P^-1 (+ add_k), k < polys; u ([polys][level+1+K][N]) is clobbered.
 // add0/add1: [level+1][N] or null, add0 read through the automorphism add0_g (1 = none);
 // out: [polys][level+1][N]; work: [polys][level+1][N]
@@ -62,10 +65,12 @@ ckks_status launch_expand_key_a(ckks_ctx *ctx, uint64_t s0, uint64_t s1, uint64_
 // c0 is c0s[r] and whose ModUp digits are digs[r] (hoisted rotations of one ciphertext share both): key inner
 // product, ModDown and the sigma_{g_r}(c0) addition, each stage one launch for all r.
 // work: count * (2 ext + 2 (level+1)) N words.  seeds (nullable, [count][2]): seed-expanded keys, keys[r] then holds
-// the b half [dnum][n_q + n_p][N] and the a half comes from seeds[2r], seeds[2r + 1] (philox.h)
+// the b half [dnum][n_q + n_p][N] and the a half comes from seeds[2r], seeds[2r + 1] (philox.h).  add1 (nullable):
+// add1[r] ([level+1][N]) is added to the second component of output r
 ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const uint64_t *const *c0s,
                             const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
-                            uint64_t *const *outs, uint64_t *work, const uint64_t *seeds = nullptr);
+                            uint64_t *const *outs, uint64_t *work, const uint64_t *seeds = nullptr,
+                            const uint64_t *const *add1 = nullptr);
 
 // lazy ModDown: accs[r] (or accs[0] for all r when sum_all; [2][level+1+K][N]) (+)= the key inner product of
 // rotation r over Q_level u P plus P * sigma_{g_r}(c0_r) on the q rows; count <= 32.  ks_moddown of the accumulator
@@ -73,6 +78,48 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
 ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, const uint64_t *const *c0s,
                              const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
                              uint64_t *const *accs, bool sum_all, bool accumulate);
+
+// Whole rows per block (ring_block.hip): N = 2^12 .. 2^14, fp64 primes.
+// the ring has them and the fp64 arithmetic is not switched off
+bool blk_ring(const ckks_ctx *ctx);
+// they are the faster transform for a launch of `rows` rows
+bool blk_rows(const ckks_ctx *ctx, size_t rows);
+// they are the faster encryption and decryption of `limbs` limbs
+bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs);
+// they are the faster key switching for a batch of `count` rotations at `level`
+bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count);
+// they take every key-switching step at `level` (computed once per context: ckks_ctx::blk_level)
+bool blk_level_ok(const ckks_ctx *ctx, uint32_t level);
+inline bool blk_switch(const ckks_ctx *ctx, uint32_t level)
+{
+    return !ctx->int_only && level < ctx->blk_level.size() && ctx->blk_level[level];
+}
+// transform of `batch` groups of map.n rows from src (group stride src_stride rows) to dst; dst may be src
+ckks_status blk_ntt(ckks_ctx *ctx, uint64_t *dst, uint32_t dst_stride, const uint64_t *src, uint32_t src_stride,
+                    uint32_t batch, const LimbMap &map, bool inverse);
+ckks_status blk_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32_t batch, uint32_t limbs);
+ckks_status blk_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_t *a, const int8_t *s,
+                        const int32_t *e, const uint64_t *m, uint32_t limbs);
+ckks_status blk_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const uint64_t *c1, const int8_t *s,
+                        uint32_t limbs);
+// rescale of `polys` polynomials c ([polys][l+1][N]) into out ([polys][l][N]); work: polys N words
+ckks_status blk_rescale(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint32_t l, uint64_t *out, uint64_t *work);
+// ModUp of `count` polynomials at c1 + r stride, or (b set, count 1) of the product of the second components of the
+// ciphertexts whose second components start at c1 and at b + (level+1) N; stage: count (level+1) N words
+ckks_status blk_modup(ckks_ctx *ctx, const uint64_t *c1, size_t stride, const uint64_t *b, uint32_t count,
+                      uint32_t level, uint64_t *digits, uint64_t *stage);
+// a rotation batch; with ta, tb2 (ciphertexts) the addends are the first two components of their tensor product.
+// work: count 2 (level+1+n_p) N words
+struct RotArgs;
+ckks_status blk_rotate_batch(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, uint64_t *work,
+                             const uint64_t *ta = nullptr, const uint64_t *tb2 = nullptr);
+// as ks_moddown
+ckks_status blk_moddown(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t level, const uint64_t *add0,
+                        uint32_t add0_g, const uint64_t *add1, uint64_t *out);
+// a, b [2][level+1][N]: out = a b relinearised with rlk, every step in the kernels above; out must overlap neither
+// input.  work: ks_scratch_words(level, 1) words
+ckks_status ks_mul_relin_blk(ckks_ctx *ctx, const uint64_t *a, const uint64_t *b, const uint64_t *rlk, uint32_t level,
+                             uint64_t *out, uint64_t *work);
 
 // encoding (encode.hip)
 struct SlotSource {
@@ -158,13 +205,12 @@ ckks_status launch_enc_vectors(ckks_ctx *ctx, const double *U, uint32_t D, uint3
 // Lazy sums of rotations (one ModDown per output).  rotate_many_lazy: ciphertext r (at cs + r * stride) rotated by
 // `steps` is added to accumulator uacc + r * 2 ext N; rotate_each_lazy: ciphertext r rotated by steps[r], all
 // added to the one accumulator uacc.  accumulate = false starts the accumulators.
-// work: count * (nd ext + alpha) N words (the ModUp digits)
+// work: ks_scratch_words(ctx, level, ks_rot_batch(count), count) words
 ckks_status rotate_many_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
                              int32_t steps, const uint64_t *key, uint64_t *uacc, bool accumulate, uint64_t *work);
 ckks_status rotate_each_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
                              const int32_t *steps, const uint64_t *const *keys, uint64_t *uacc, bool accumulate,
                              uint64_t *work);
-size_t lazy_work_words(const ckks_ctx *ctx, uint32_t level, uint32_t count);
 
 // decode: coef = coefficient form of limbs 0..min(limbs,2)-1 ([limbs][N]); writes N/2 slots
 ckks_status dec_slots(ckks_ctx *ctx, const uint64_t *coef, uint32_t limbs, double scale, double2 *work, double *re,
