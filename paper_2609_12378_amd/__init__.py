@@ -271,6 +271,14 @@ class Context:
     def zeros(self, n_polys: int, n_limbs: int) -> torch.Tensor:
         return torch.zeros((n_polys, n_limbs, self.n), dtype=torch.uint64, device="cuda")
 
+    def _empty(self, n_polys: int, n_limbs: int) -> torch.Tensor:
+        """An output buffer: the call it is for writes every word, so it is not cleared first (a fill of a level-12
+        ciphertext costs 6 us, of the 32 outputs of a hoisted batch a tenth of the batch).  A program that replaced
+        `zeros` by its own allocation gets that."""
+        if "zeros" in self.__dict__ or type(self).zeros is not Context.zeros:
+            return self.zeros(n_polys, n_limbs)
+        return torch.empty((n_polys, n_limbs, self.n), dtype=torch.uint64, device="cuda")
+
     # ---------------- transforms ----------------
     def ntt(self, t: torch.Tensor, limb0: int = 0, inverse: bool = False):
         """In-place (inverse) NTT of t viewed as [batch][limbs][N]; limbs use primes limb0.."""
@@ -289,7 +297,7 @@ class Context:
     # ---------------- encoding ----------------
     def encode(self, re: torch.Tensor, im: Optional[torch.Tensor], scale: float, n_limbs: int,
                out: Optional[torch.Tensor] = None) -> Buf:
-        out = self.zeros(1, n_limbs) if out is None else out
+        out = self._empty(1, n_limbs) if out is None else out
         b = Buf(out, scale)
         cb = b.c(self.n)
         if out.shape[1] != n_limbs or out.shape[0] != 1:
@@ -308,18 +316,20 @@ class Context:
 
     # ---------------- encryption ----------------
     def encrypt(self, s: torch.Tensor, pt: Buf, a: torch.Tensor, e: torch.Tensor) -> Buf:
-        out = Buf(self.zeros(2, pt.n_limbs), pt.scale)
-        cp, co = pt.c(self.n), out.c(self.n)
+        cp = pt.c(self.n)
         ps = _arg(s, "secret", torch.int8, numel=self.n)
         pa = _arg(a, "encryption a", torch.uint64, numel=pt.n_limbs * self.n)
         pe = _arg(e, "encryption error", torch.int32, numel=self.n)
+        out = Buf(self._empty(2, pt.n_limbs), pt.scale)
+        co = out.c(self.n)
         _check(self.lib.ckks_encrypt_sk(self.h, ps, ctypes.byref(cp), pa, pe, ctypes.byref(co)), "ckks_encrypt_sk")
         return out
 
     def decrypt(self, s: torch.Tensor, ct: Buf) -> Buf:
-        out = Buf(self.zeros(1, ct.n_limbs), ct.scale)
-        ci, co = ct.c(self.n), out.c(self.n)
+        ci = ct.c(self.n)
         ps = _arg(s, "secret", torch.int8, numel=self.n)
+        out = Buf(self._empty(1, ct.n_limbs), ct.scale)
+        co = out.c(self.n)
         _check(self.lib.ckks_decrypt(self.h, ps, ctypes.byref(ci), ctypes.byref(co)), "ckks_decrypt")
         return out
 
@@ -372,7 +382,7 @@ class Context:
         if any(len(sd_) != 2 for sd_ in seeds):
             raise CkksError("a key seed is two 64-bit words")
         if outs is None:
-            outs = [Buf(self.zeros(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
+            outs = [Buf(self._empty(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
         st = (ctypes.c_int32 * max(1, cnt))(*steps)
         ob = (_Buf * max(1, cnt))(*[o.c(self.n) for o in outs])
         ci = ct.c(self.n)
@@ -400,8 +410,9 @@ class Context:
 
     # ---------------- ciphertext operations ----------------
     def _binop(self, name, a: Buf, b: Buf, out_scale: float, out_limbs: int) -> Buf:
-        out = Buf(self.zeros(2, out_limbs), out_scale)
-        ca, cb, co = a.c(self.n), b.c(self.n), out.c(self.n)
+        ca, cb = a.c(self.n), b.c(self.n)
+        out = Buf(self._empty(2, out_limbs), out_scale)
+        co = out.c(self.n)
         _check(getattr(self.lib, name)(self.h, ctypes.byref(ca), ctypes.byref(cb), ctypes.byref(co)), name)
         return out
 
@@ -412,22 +423,25 @@ class Context:
         return self._binop("ckks_mul_plain", ct, pt, ct.scale * pt.scale, ct.n_limbs)
 
     def mul_relin(self, a: Buf, b: Buf, rlk: torch.Tensor) -> Buf:
-        out = Buf(self.zeros(2, a.n_limbs), a.scale * b.scale)
-        ca, cb, co = a.c(self.n), b.c(self.n), out.c(self.n)
-        _check(self.lib.ckks_mul_relin(self.h, ctypes.byref(ca), ctypes.byref(cb), self._key(rlk, "relinearisation key"),
-                                       ctypes.byref(co)), "ckks_mul_relin")
+        ca, cb, pk = a.c(self.n), b.c(self.n), self._key(rlk, "relinearisation key")
+        out = Buf(self._empty(2, a.n_limbs), a.scale * b.scale)
+        co = out.c(self.n)
+        _check(self.lib.ckks_mul_relin(self.h, ctypes.byref(ca), ctypes.byref(cb), pk, ctypes.byref(co)),
+               "ckks_mul_relin")
         return out
 
     def rescale(self, ct: Buf) -> Buf:
-        out = Buf(self.zeros(2, ct.n_limbs - 1), ct.scale / self.q[ct.level])
-        ci, co = ct.c(self.n), out.c(self.n)
+        ci = ct.c(self.n)
+        out = Buf(self._empty(2, ct.n_limbs - 1), ct.scale / self.q[ct.level])
+        co = out.c(self.n)
         _check(self.lib.ckks_rescale(self.h, ctypes.byref(ci), ctypes.byref(co)), "ckks_rescale")
         return out
 
     def rotate(self, ct: Buf, steps: int, key: torch.Tensor) -> Buf:
-        out = Buf(self.zeros(2, ct.n_limbs), ct.scale)
-        ci, co = ct.c(self.n), out.c(self.n)
-        _check(self.lib.ckks_rotate(self.h, ctypes.byref(ci), steps, self._key(key), ctypes.byref(co)), "ckks_rotate")
+        ci, pk = ct.c(self.n), self._key(key)
+        out = Buf(self._empty(2, ct.n_limbs), ct.scale)
+        co = out.c(self.n)
+        _check(self.lib.ckks_rotate(self.h, ctypes.byref(ci), steps, pk, ctypes.byref(co)), "ckks_rotate")
         return out
 
     def rotate_noalloc(self, ct: Buf, steps: int, key: torch.Tensor, out: Buf) -> Buf:
@@ -445,12 +459,12 @@ class Context:
             raise CkksError("rotate_hoisted: %d steps but %d keys" % (cnt, len(keys)))
         if outs is not None and len(outs) < cnt:
             raise CkksError("rotate_hoisted: %d outputs for %d steps" % (len(outs), cnt))
-        if outs is None:
-            outs = [Buf(self.zeros(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
         st = (ctypes.c_int32 * cnt)(*steps)
         kp = (ctypes.c_void_p * cnt)(*[self._key(k).value for k in keys])
-        ob = (_Buf * cnt)(*[o.c(self.n) for o in outs])
         ci = ct.c(self.n)
+        if outs is None:
+            outs = [Buf(self._empty(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
+        ob = (_Buf * cnt)(*[o.c(self.n) for o in outs])
         _check(self.lib.ckks_rotate_hoisted(self.h, ctypes.byref(ci), st, cnt, kp, ob), "ckks_rotate_hoisted")
         return list(outs)
 
@@ -487,7 +501,7 @@ class Context:
         n_out = d_out // D
         level = cts[0].level
         if outs is None:
-            outs = [Buf(self.zeros(2, level), cts[0].scale) for _ in range(n_out)]
+            outs = [Buf(self._empty(2, level), cts[0].scale) for _ in range(n_out)]
         # the library reads d_in/D input and d_out/D output descriptors: never hand it shorter arrays
         if D > 0 and d_in % D == 0 and d_out % D == 0 and (len(cts) < d_in // D or len(outs) < n_out):
             raise ValueError("linear_project: %d inputs and %d outputs given, the shape needs %d and %d"
@@ -511,7 +525,7 @@ class Context:
         if len(b_of_a) != len(a_cts):
             raise ValueError("%s: %d ciphertexts but %d indices" % (fn, len(a_cts), len(b_of_a)))
         if outs is None:
-            outs = [Buf(self.zeros(2, a_cts[0].n_limbs - (2 if fn == "ckks_attention_scores" else 1)), 0.0)
+            outs = [Buf(self._empty(2, a_cts[0].n_limbs - (2 if fn == "ckks_attention_scores" else 1)), 0.0)
                     for _ in a_cts]
         if len(outs) < len(a_cts):
             raise ValueError("%s: %d outputs for %d inputs" % (fn, len(outs), len(a_cts)))
