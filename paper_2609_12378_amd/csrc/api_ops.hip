@@ -102,34 +102,6 @@ ckks_status rotate_core(ckks_ctx *ctx, const uint64_t *c, uint32_t level, const 
     return CKKS_OK;
 }
 
-// The same rotation (steps, key) of `count` ciphertexts: ciphertext r at cs + r * stride (words, [2][level+1][N]),
-// output r at outs[r]; one batched ModUp, key switching in batches of up to 32.
-// work: ks_scratch_words(ctx, level, ks_rot_batch(count), count) words
-ckks_status rotate_many(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                        int32_t steps, const uint64_t *key, uint64_t *const *outs, uint64_t *work)
-{
-    if (!count) return CKKS_OK;
-    const uint32_t L = level + 1, ext = L + ctx->n_p, nd = n_digits(ctx, level);
-    const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
-    uint64_t *digits = work;
-    uint64_t *rw = digits + (size_t)count * (dig_ct + (size_t)ctx->alpha * N);
-    const uint32_t bs = ks_rot_batch(count);
-    CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, digits,
-                          ks_stage_rows(ctx, level, bs, count)));
-    std::vector<uint32_t> g(count, ckks_galois_elt(ctx, steps));
-    std::vector<const uint64_t *> keys(count, key), c0s(count), digs(count);
-    for (uint32_t r = 0; r < count; r++) {
-        c0s[r] = cs + (size_t)r * stride;
-        digs[r] = digits + (size_t)r * dig_ct;
-    }
-    for (uint32_t r0 = 0; r0 < count; r0 += bs) {
-        const uint32_t cnt = count - r0 < bs ? count - r0 : bs;
-        CK_TRY(ks_rotate_batch(ctx, level, cnt, c0s.data() + r0, digs.data() + r0, g.data() + r0, keys.data() + r0,
-                               outs + r0, rw));
-    }
-    return CKKS_OK;
-}
-
 ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
                         const int32_t *steps, const uint64_t *const *keys, uint64_t *const *outs, uint64_t *work)
 {
@@ -156,11 +128,9 @@ ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     return CKKS_OK;
 }
 
-namespace {
-
-ckks_status rotate_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                        const int32_t *steps, const uint64_t *const *keys, bool same_step, uint64_t *uacc,
-                        bool sum_all, bool accumulate, uint64_t *work)
+ckks_status rotate_each_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
+                             const int32_t *steps, const uint64_t *const *keys, uint64_t *uacc, uint32_t n_accs,
+                             bool accumulate, uint64_t *work)
 {
     if (!count) return CKKS_OK;
     const uint32_t L = level + 1, ext = L + ctx->n_p, nd = n_digits(ctx, level);
@@ -168,37 +138,50 @@ ckks_status rotate_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
     CK_TRY(ks_modup_batch(ctx, cs + (size_t)L * N, stride, count, level, work,
                           ks_stage_rows(ctx, level, ks_rot_batch(count), count)));
     std::vector<uint32_t> g(count);
-    std::vector<const uint64_t *> c0s(count), digs(count), ks(count);
-    std::vector<uint64_t *> accs(count);
+    std::vector<const uint64_t *> c0s(count), digs(count);
+    std::vector<uint64_t *> accs(n_accs);
     for (uint32_t r = 0; r < count; r++) {
-        g[r] = ckks_galois_elt(ctx, same_step ? steps[0] : steps[r]);
-        ks[r] = same_step ? keys[0] : keys[r];
+        g[r] = ckks_galois_elt(ctx, steps[r]);
         c0s[r] = cs + (size_t)r * stride;
         digs[r] = work + (size_t)r * dig_ct;
-        accs[r] = uacc + (sum_all ? 0 : (size_t)r * 2 * ext * N);
     }
-    const uint32_t bs = ks_rot_batch(count);
+    for (uint32_t z = 0; z < n_accs; z++) accs[z] = uacc + (size_t)z * 2 * ext * N;
+    // whole groups of n_accs rotations per launch
+    const uint32_t bs = ks_rot_batch(count) / n_accs * n_accs;
     for (uint32_t r0 = 0; r0 < count; r0 += bs) {
         const uint32_t cnt = count - r0 < bs ? count - r0 : bs;
-        CK_TRY(ks_ip_accumulate(ctx, level, cnt, c0s.data() + r0, digs.data() + r0, g.data() + r0, ks.data() + r0,
-                                accs.data() + r0, sum_all, accumulate || (sum_all && r0 > 0)));
+        CK_TRY(ks_ip_accumulate(ctx, level, cnt, c0s.data() + r0, digs.data() + r0, g.data() + r0, keys + r0,
+                                accs.data(), n_accs, accumulate || r0 > 0));
     }
     return CKKS_OK;
 }
 
-}  // namespace
-
-ckks_status rotate_many_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                             int32_t steps, const uint64_t *key, uint64_t *uacc, bool accumulate, uint64_t *work)
+ckks_status giant_steps(ckks_ctx *ctx, const uint64_t *acc, uint64_t *tot, uint64_t *rot, uint64_t *uacc, uint32_t jc,
+                        uint32_t g, uint32_t gc, int32_t step, const uint64_t *const *gkeys, uint32_t level, bool lazy,
+                        uint64_t *work)
 {
-    return rotate_lazy(ctx, cs, stride, count, level, &steps, &key, true, uacc, false, accumulate, work);
-}
-
-ckks_status rotate_each_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                             const int32_t *steps, const uint64_t *const *keys, uint64_t *uacc, bool accumulate,
-                             uint64_t *work)
-{
-    return rotate_lazy(ctx, cs, stride, count, level, steps, keys, false, uacc, true, accumulate, work);
+    const uint32_t L = level + 1;
+    const size_t ctw = 2 * (size_t)L * ctx->n;
+    const uint32_t first = g == 0 ? 1 : 0;
+    if (first) HIP_TRY(hipMemcpyAsync(tot, acc, jc * ctw * 8, hipMemcpyDeviceToDevice, ctx->stream));
+    const uint32_t count = (gc - first) * jc;
+    if (!count) return CKKS_OK;
+    std::vector<int32_t> steps(count);
+    std::vector<const uint64_t *> keys(count);
+    std::vector<uint64_t *> outs(count);
+    for (uint32_t r = 0; r < count; r++) {
+        const uint32_t gg = g + first + r / jc;
+        steps[r] = step * (int32_t)gg;
+        keys[r] = gkeys[gg];
+        outs[r] = rot + (size_t)r * ctw;
+    }
+    const uint64_t *cs = acc + first * jc * ctw;
+    if (lazy)
+        return rotate_each_lazy(ctx, cs, ctw, count, level, steps.data(), keys.data(), uacc, jc, g + first > 1, work);
+    CK_TRY(rotate_each(ctx, cs, ctw, count, level, steps.data(), keys.data(), outs.data(), work));
+    for (uint32_t r = 0; r < count; r += jc)
+        CK_TRY(launch_binary(ctx, tot, tot, rot + r * ctw, jc * 2 * L, limb_range(0, L), EW_ADD));
+    return CKKS_OK;
 }
 
 ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint32_t l, uint64_t *out,

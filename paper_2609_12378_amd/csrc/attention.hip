@@ -600,7 +600,7 @@ extern "C" ckks_status ckks_attention_scores(ckks_ctx *ctx, const ckks_buf *q, u
             for (uint32_t k0 = 1; k0 < hd; k0 += ss.Jt) {
                 const uint32_t cnt = std::min(ss.Jt, hd - k0);
                 CK_TRY(rotate_each_lazy(ctx, Ub + (size_t)k0 * ctw, ctw, cnt, level, osteps.data() + (k0 - 1),
-                                        okeys.data() + (k0 - 1), uacc, k0 > 1, work));
+                                        okeys.data() + (k0 - 1), uacc, 1, k0 > 1, work));
             }
             CK_TRY(ks_moddown(ctx, uacc, 2, level, Ub, 1, Ub + (size_t)L * N, tot, work));
         } else {

@@ -50,12 +50,12 @@ __device__ __forceinline__ double2 slot_value(const SlotSource &s, uint32_t p, u
     // feature-major slot j = f*T + t holds D_{n1 g + b}(A_{jb,i})[(f - n1 g) mod D] with
     // A = W^T, A_{jb,i}[o][c] = W[i D + c][jb D + o], D_k(A)[o] = A[o][(o + k) mod D]
     const uint32_t D = s.feats;
-    const uint32_t jb = s.j0 + p / s.pairs;
+    const uint32_t jr = p / s.pairs, jb = s.j0 + jr % s.jc, n1g = s.n1g + s.n1 * (jr / s.jc);
     const uint32_t pair = s.ib0 + p % s.pairs;
     const uint32_t i = pair / s.bcount, b = pair % s.bcount;
     const uint32_t f = j / s.tokens;
-    const uint32_t o = (f + D - s.n1g % D) % D;
-    const uint32_t c = (o + s.n1g + b) % D;
+    const uint32_t o = (f + D - n1g % D) % D;
+    const uint32_t c = (o + n1g + b) % D;
     return make_double2(s.W[(size_t)(i * D + c) * s.d_out + (size_t)jb * D + o], 0.0);
 }
 
@@ -173,13 +173,14 @@ __global__ __launch_bounds__(256) void k_fft_a8(double2 *a, const double2 *__res
     const uint32_t M = 1u << logm, blocks_per = M >> 11;
     const uint32_t p = blockIdx.x / blocks_per, blk = blockIdx.x % blocks_per, t = threadIdx.x;
     const uint32_t D = ss.feats;
-    const uint32_t jb = ss.j0 + p / ss.pairs, pair = ss.ib0 + p % ss.pairs;
+    const uint32_t jr = p / ss.pairs, jb = ss.j0 + jr % ss.jc, n1g = ss.n1g + ss.n1 * (jr / ss.jc);
+    const uint32_t pair = ss.ib0 + p % ss.pairs;
     const uint32_t i = pair / ss.bcount, b = pair % ss.bcount;
-    const double *dg = ss.Wd + (((size_t)jb * ss.n_in + i) * D + ss.n1g + b) * D;
+    const double *dg = ss.Wd + (((size_t)jb * ss.n_in + i) * D + n1g + b) * D;
     for (uint32_t o = t; o < D; o += 256) vals[o] = dg[o];
     __syncthreads();
     // slot f*T + t' holds diagonal entry (f - n1 g) mod D
-    const uint32_t shift = D - ss.n1g % D, mask = D - 1;
+    const uint32_t shift = D - n1g % D, mask = D - 1;
     const uint32_t *fp = ss.feat_of_pos + ((size_t)blk << 11);
     double2 v[8];
 #pragma unroll

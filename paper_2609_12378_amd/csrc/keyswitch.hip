@@ -411,21 +411,21 @@ void launch_key_ip_batch_stored(dim3 grid, dim3 block, hipStream_t st, const Rot
 // Lazy ModDown: the key inner products of several rotations summed over Q_level u P before one division by P.
 // For rotation r: t_k = sum_j sigma_{g_r}(d_j) * key_r[j][k] on every row, plus P * sigma_{g_r}(c0_r) on the q rows of
 // component 0 (P is 0 modulo the special primes, and ModDown(x + P y) = ModDown(x) + y, so the c0 term passes the
-// division unchanged).  sum_all: one accumulator ra.out[0] takes the sum over all r of the batch; else ra.out[r]
-// takes rotation r's.  Accumulators [2][ext][N], added to when `accumulate`.  The 128-bit sums hold at most
-// 32 (nd + 1) products below 2^100.
+// division unchanged).  Accumulator ra.out[z] (z < accs) takes the sum over rotations z, z + accs, ... of the batch
+// (accs = 1: one takes them all; accs = count: each its own).  Accumulators [2][ext][N], added to when `accumulate`.
+// The 128-bit sums hold at most 32 (nd + 1) products below 2^100.
 template <int ND>
 __global__ __launch_bounds__(kThreads) void k_key_ip_acc(RotArgs ra, uint32_t nd, uint32_t ext, uint32_t level,
                                                          uint32_t n_q, uint32_t key_rows,
                                                          const ulonglong2 *__restrict__ pmodq,
-                                                         const ModQ *__restrict__ mods, uint32_t log_n, int sum_all,
+                                                         const ModQ *__restrict__ mods, uint32_t log_n, uint32_t accs,
                                                          int accumulate)
 {
     const uint32_t n = 1u << log_n;
     const uint32_t col = blockIdx.x * kThreads + threadIdx.x;
     const uint32_t row = blockIdx.y;
     if (col >= n) return;
-    const uint32_t r0 = sum_all ? 0 : blockIdx.z, r1 = sum_all ? ra.count : blockIdx.z + 1;
+    const uint32_t r0 = blockIdx.z, r1 = ra.count;
     const uint32_t prime = row <= level ? row : n_q + (row - level - 1);
     const ModQ m = mods[prime];
     const uint64_t pq = row <= level ? pmodq[row].x : 0;
@@ -464,21 +464,21 @@ __global__ __launch_bounds__(kThreads) void k_key_ip_acc(RotArgs ra, uint32_t nd
         Words w0, w1;
         load(r0, w0);
         uint32_t r = r0;
-        for (; r + 2 < r1; r += 2) {
-            load(r + 1, w1);
+        for (; r + 2 * accs < r1; r += 2 * accs) {
+            load(r + accs, w1);
             use(w0);
-            load(r + 2, w0);
+            load(r + 2 * accs, w0);
             use(w1);
         }
-        if (r + 1 < r1) {
-            load(r + 1, w1);
+        if (r + accs < r1) {
+            load(r + accs, w1);
             use(w0);
             use(w1);
         } else {
             use(w0);
         }
     } else {
-        for (uint32_t r = r0; r < r1; r++) {
+        for (uint32_t r = r0; r < r1; r += accs) {
             const uint32_t sc = auto_index(col, ra.g[r], log_n);
             const uint64_t *key = ra.key[r];
             const uint64_t *digits = ra.dig[r];
@@ -981,18 +981,19 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
 
 ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, const uint64_t *const *c0s,
                              const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
-                             uint64_t *const *accs, bool sum_all, bool accumulate)
+                             uint64_t *const *accs, uint32_t n_accs, bool accumulate)
 {
     CK_REQUIRE(count >= 1 && count <= (uint32_t)kRotBatch, CKKS_EINVAL, "rotation batch of %u", count);
     const uint32_t L = level + 1, ext = L + ctx->n_p, nd = n_digits(ctx, level);
-    // one accumulator summing every rotation takes count (nd + 1) products in its exact 128-bit sum: with large
+    CK_REQUIRE(n_accs >= 1 && n_accs <= count, CKKS_EINVAL, "%u accumulators for %u rotations", n_accs, count);
+    // an accumulator summing `per` rotations takes per (nd + 1) products in its exact 128-bit sum: with large
     // primes, fewer rotations per launch, the later launches adding to the reduced sum
-    const uint32_t per = std::max(1u, ctx->sum128_terms / (nd + 1));
-    if (sum_all && count > per) {
-        for (uint32_t r0 = 0; r0 < count; r0 += per) {
-            const uint32_t cnt = std::min(per, count - r0);
-            CK_TRY(ks_ip_accumulate(ctx, level, cnt, c0s + r0, digs + r0, g + r0, keys + r0, accs, true,
-                                    accumulate || r0 > 0));
+    const uint64_t per = (uint64_t)std::max(1u, ctx->sum128_terms / (nd + 1)) * n_accs;
+    if (count > per) {
+        for (uint32_t r0 = 0; r0 < count; r0 += (uint32_t)per) {
+            const uint32_t cnt = (uint32_t)std::min<uint64_t>(per, count - r0);
+            CK_TRY(ks_ip_accumulate(ctx, level, cnt, c0s + r0, digs + r0, g + r0, keys + r0, accs,
+                                    std::min(n_accs, cnt), accumulate || r0 > 0));
         }
         return CKKS_OK;
     }
@@ -1001,18 +1002,18 @@ ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, cons
     for (uint32_t r = 0; r < count; r++) {
         ra.g[r] = g[r];
         ra.key[r] = keys[r];
-        ra.out[r] = accs[sum_all ? 0 : r];
+        ra.out[r] = accs[r % n_accs];
         ra.dig[r] = digs[r];
         ra.c0[r] = c0s[r];
     }
-    const dim3 grid((ctx->n + kThreads - 1) / kThreads, ext, sum_all ? 1 : count), block(kThreads);
-    const double outs = sum_all ? 1.0 : count;
+    const dim3 grid((ctx->n + kThreads - 1) / kThreads, ext, n_accs), block(kThreads);
+    const double outs = n_accs;
     // digits and keys of every rotation, c0, the accumulators read (when accumulating) and written
     prof_begin(ctx, K_KEYIP, 8.0 * ctx->n * ext * (count * (3.0 * nd) + (double)L / ext * count +
                                                    outs * 2.0 * (accumulate ? 2 : 1)));
 #define CK_ACC(SD, ND)                                                                                             \
     hipLaunchKernelGGL(k_key_ip_acc<ND>, grid, block, 0, ctx->stream, ra, nd, ext, level, ctx->n_q,                  \
-                       ctx->n_primes(), ctx->d_pmodq, ctx->d_mod, ctx->log_n, (int)sum_all, (int)accumulate)
+                       ctx->n_primes(), ctx->d_pmodq, ctx->d_mod, ctx->log_n, n_accs, (int)accumulate)
     CK_ND_DISPATCH(nd, CK_ACC, 0);
 #undef CK_ACC
     prof_end(ctx, K_KEYIP);

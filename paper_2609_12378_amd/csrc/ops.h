@@ -72,12 +72,12 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
                             uint64_t *const *outs, uint64_t *work, const uint64_t *seeds = nullptr,
                             const uint64_t *const *add1 = nullptr);
 
-// lazy ModDown: accs[r] (or accs[0] for all r when sum_all; [2][level+1+K][N]) (+)= the key inner product of
+// lazy ModDown: accs[r mod n_accs] ([2][level+1+K][N]) (+)= the key inner product of
 // rotation r over Q_level u P plus P * sigma_{g_r}(c0_r) on the q rows; count <= 32.  ks_moddown of the accumulator
 // then gives the sum of the rotations.
 ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, const uint64_t *const *c0s,
                              const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
-                             uint64_t *const *accs, bool sum_all, bool accumulate);
+                             uint64_t *const *accs, uint32_t n_accs, bool accumulate);
 
 // Whole rows per block (ring_block.hip): N = 2^12 .. 2^14, fp64 primes.
 // the ring has them and the fp64 arithmetic is not switched off
@@ -126,11 +126,14 @@ struct SlotSource {
     // explicit slots: re/im [batch][N/2] (im may be null)
     const double *re = nullptr, *im = nullptr;
     // or the projection's weight plaintexts, generated from W (d_in x d_out, row-major):
-    // plaintext p of the batch is (output block j0 + p / pairs, pair ib0 + p % pairs), where
+    // plaintext p of the batch is (output block j0 + (p / pairs) % jc, pair ib0 + p % pairs), where
     // pair = i * bcount + b names input block i and baby step b of giant step g (n1g = n1 * g)
     const double *W = nullptr;
     uint32_t d_out = 0, tokens = 0, feats = 0;
     uint32_t n1g = 0, bcount = 0;
+    // several giant steps in one batch: plaintext p belongs to block jr = p / pairs, output j0 + jr % jc of giant step
+    // g + jr / jc (n1g + n1 (jr / jc))
+    uint32_t jc = 1, n1 = 0;
     uint32_t j0 = 0, ib0 = 0, pairs = 1;
     // optional, for feats <= 256 and N >= 2^12: W re-laid as its cyclic diagonals,
     // Wd[((jb * n_in + i) * D + k) * D + o] = D_k(A_{jb,i})[o], and feat_of_pos[x] = (slot at FFT position x) / tokens
@@ -168,16 +171,19 @@ ckks_status launch_diag_layout(ckks_ctx *ctx, double *Wd, const double *W, uint3
 ckks_status launch_to_f64(ckks_ctx *ctx, uint64_t *v, size_t words);
 
 // ciphertext-level steps shared by the API calls and the projections (api_ops.hip)
+// The gc giant steps g, g + 1, ... of a projection's tile of jc outputs, their partial sums at acc ([gc][jc]
+// ciphertexts): that of step 0 to tot ([jc]), the others rotated by step * (g + gg) with gkeys[g + gg] and added to
+// tot, or (lazy) their key-switching sums to uacc ([jc][2][level+1+n_p][N]).  rot: gc jc ciphertexts; work:
+// ks_scratch_words(ctx, level, ks_rot_batch(gc jc), gc jc) words; gc jc <= 32
+ckks_status giant_steps(ckks_ctx *ctx, const uint64_t *acc, uint64_t *tot, uint64_t *rot, uint64_t *uacc, uint32_t jc,
+                        uint32_t g, uint32_t gc, int32_t step, const uint64_t *const *gkeys, uint32_t level, bool lazy,
+                        uint64_t *work);
 // rotations of one ciphertext sharing a single ModUp; work: ks_scratch_words(level, ks_rot_batch(count))
 ckks_status rotate_core(ckks_ctx *ctx, const uint64_t *c, uint32_t level, const int32_t *steps,
                         const uint64_t *const *keys, uint32_t count, uint64_t *const *outs, uint64_t *work,
                         const uint64_t *seeds = nullptr);
 // rescale of one ciphertext at level l; work: (2 + 2 l) N words
 ckks_status rescale_core(ckks_ctx *ctx, const uint64_t *c, uint32_t l, uint64_t *out, uint64_t *work);
-// `count` ciphertexts (at cs + r * stride) rotated by the same step; work: ks_scratch_words(level,
-// ks_rot_batch(count), count)
-ckks_status rotate_many(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                        int32_t steps, const uint64_t *key, uint64_t *const *outs, uint64_t *work);
 // `count` ciphertexts (at cs + r * stride) each rotated by its own step with its own key; one batched ModUp.
 // work: ks_scratch_words(ctx, level, ks_rot_batch(count), count) words
 ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
@@ -202,15 +208,12 @@ ckks_status launch_mac_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, cons
 ckks_status launch_enc_vectors(ckks_ctx *ctx, const double *U, uint32_t D, uint32_t count, double delta, uint32_t L,
                                double *Q);
 
-// Lazy sums of rotations (one ModDown per output).  rotate_many_lazy: ciphertext r (at cs + r * stride) rotated by
-// `steps` is added to accumulator uacc + r * 2 ext N; rotate_each_lazy: ciphertext r rotated by steps[r], all
-// added to the one accumulator uacc.  accumulate = false starts the accumulators.
-// work: ks_scratch_words(ctx, level, ks_rot_batch(count), count) words
-ckks_status rotate_many_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                             int32_t steps, const uint64_t *key, uint64_t *uacc, bool accumulate, uint64_t *work);
+// Lazy sums of rotations (one ModDown per output): ciphertext r (at cs + r * stride) rotated by steps[r] with keys[r]
+// is added to accumulator uacc + (r mod n_accs) * 2 ext N; accumulate = false starts the accumulators.  count is a
+// multiple of n_accs <= 32.  work: ks_scratch_words(ctx, level, ks_rot_batch(count), count) words
 ckks_status rotate_each_lazy(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32_t count, uint32_t level,
-                             const int32_t *steps, const uint64_t *const *keys, uint64_t *uacc, bool accumulate,
-                             uint64_t *work);
+                             const int32_t *steps, const uint64_t *const *keys, uint64_t *uacc, uint32_t n_accs,
+                             bool accumulate, uint64_t *work);
 
 // decode: coef = coefficient form of limbs 0..min(limbs,2)-1 ([limbs][N]); writes N/2 slots
 ckks_status dec_slots(ckks_ctx *ctx, const uint64_t *coef, uint32_t limbs, double scale, double2 *work, double *re,

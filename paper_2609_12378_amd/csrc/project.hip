@@ -517,8 +517,11 @@ extern "C" ckks_status ckks_linear_project(ckks_ctx *ctx, const ckks_buf *in, co
     const double delta_w = (double)ctx->primes[level];
     for (uint32_t j0 = 0; j0 < n_out; j0 += Jt) {
         const uint32_t jc = std::min<uint32_t>(Jt, n_out - j0);
-        for (uint32_t g = 0; g < n2; g++) {
+        // with few outputs several giant steps share the launches (kernels and key switching alike): as many as fill the
+        // tile, all but a shorter last one over the same baby steps
+        for (uint32_t g = 0, gc = 1; g < n2; g += gc) {
             const uint32_t bcount = std::min<uint32_t>(n1, D - n1 * g);
+            gc = bcount < n1 ? 1 : std::max(1u, std::min(Jt / jc, (D - n1 * g) / n1));
             const uint32_t pairs = n_in * bcount;
             // sub-batches of equal size (within one pair): no short tail launch
             const uint32_t nsub = (pairs + Pb - 1) / Pb;
@@ -534,38 +537,32 @@ extern "C" ckks_status ckks_linear_project(ckks_ctx *ctx, const ckks_buf *in, co
                 src.j0 = j0;
                 src.ib0 = pb0;
                 src.pairs = P;
+                src.jc = jc;
+                src.n1 = n1;
                 if (diag) {
                     src.Wd = Wd;
                     src.feat_of_pos = fop;
                     src.n_in = n_in;
                 }
-                const uint32_t batch = jc * P;
+                const uint32_t rows = gc * jc, batch = rows * P;
                 if (fused && enc_fused_ok(ctx, L)) {
                     CK_TRY(enc_ntt_first_pass(ctx, src, batch, delta_w, fft, L, pts));
-                    CK_TRY(launch_row_mac(ctx, acc, pts, (const double *)xrot, P, jc, pb0, bcount, n1, L, pb0 > 0));
+                    CK_TRY(launch_row_mac(ctx, acc, pts, (const double *)xrot, P, rows, pb0, bcount, n1, L, pb0 > 0));
                 } else if (fused) {
                     CK_TRY(enc_coeffs(ctx, src, batch, delta_w, fft, mint));
                     CK_TRY(launch_ntt_col_i64(ctx, mint, pts, batch, L));
-                    CK_TRY(launch_row_mac(ctx, acc, pts, (const double *)xrot, P, jc, pb0, bcount, n1, L, pb0 > 0));
+                    CK_TRY(launch_row_mac(ctx, acc, pts, (const double *)xrot, P, rows, pb0, bcount, n1, L, pb0 > 0));
                 } else {
                     CK_TRY(enc_coeffs(ctx, src, batch, delta_w, fft, mint));
                     CK_TRY(launch_ntt_from_i64(ctx, mint, pts, batch, L));
-                    CK_TRY(launch_mac(ctx, acc, pts, xrot, P, jc, pb0, bcount, n1, L, pb0 > 0));
+                    CK_TRY(launch_mac(ctx, acc, pts, xrot, P, rows, pb0, bcount, n1, L, pb0 > 0));
                 }
                 pb0 += P;
             }
-            // giant step: the tile's jc partial sums rotated together, then added to the totals (lazy: their
-            // key-switching sums accumulated over Q u P, divided by P once after the last giant step)
-            if (g == 0) {
-                HIP_TRY(hipMemcpyAsync(tot, acc, jc * ctw * 8, hipMemcpyDeviceToDevice, ctx->stream));
-            } else if (lazy) {
-                CK_TRY(rotate_many_lazy(ctx, acc, ctw, jc, level, (int32_t)(T * n1 * g), gkeys[g], uacc, g > 1, ksw));
-            } else {
-                std::vector<uint64_t *> outs(jc);
-                for (uint32_t jj = 0; jj < jc; jj++) outs[jj] = rot + (size_t)jj * ctw;
-                CK_TRY(rotate_many(ctx, acc, ctw, jc, level, (int32_t)(T * n1 * g), gkeys[g], outs.data(), ksw));
-                CK_TRY(launch_binary(ctx, tot, tot, rot, jc * 2 * L, limb_range(0, L), EW_ADD));
-            }
+            // giant steps: their partial sums rotated together, then added to the totals (lazy: their key-switching
+            // sums accumulated over Q u P, divided by P once after the last giant step)
+            CK_TRY(giant_steps(ctx, acc, tot, rot, uacc, jc, g, gc, (int32_t)(T * n1), gkeys.data(), level, lazy,
+                               ksw));
         }
         if (lazy && n2 > 1) {
             CK_TRY(ks_moddown(ctx, uacc, 2 * jc, level, nullptr, 1, nullptr, rot, ksw));

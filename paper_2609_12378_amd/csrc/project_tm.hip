@@ -47,8 +47,9 @@ struct TmArgs {
     const double *U;    // or explicit period vectors: plaintext pt's D values at U[pt D ..] (then Wd is unused)
     uint32_t D, logD, n_in, n1g, bcount;
     uint32_t j0, jc;    // first output of the tile, outputs in the tile
+    uint32_t n1, rows;  // giant steps g, g + 1, ... of the launch (n1g + n1, ...), rows = jc times their count
     uint32_t pb0, P;    // first (input, baby step) pair of the sub-batch, pairs in it
-    uint32_t npt;       // plaintexts in the sub-batch: P * 2 * jc, index (p * 2 + uv) * jc + jj
+    uint32_t npt;       // plaintexts in the sub-batch: P * 2 * rows, index (p * 2 + uv) * rows + gg * jc + jj
 };
 
 // Encode kPE periodic weight plaintexts per block and transform them: Q[l][x][pt] (x < 2D) holds the
@@ -76,9 +77,10 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
         if (pt < a.npt && a.U) {
             v = a.U[(size_t)pt * D + j];
         } else if (pt < a.npt) {
-            const uint32_t jj = pt % a.jc, uv = (pt / a.jc) & 1, pr = a.pb0 + pt / (2 * a.jc);
-            const uint32_t i = pr / a.bcount, b = pr % a.bcount, k = a.n1g + b;
-            const uint32_t o = (j + D - a.n1g % D) % D;   // feature before the giant-step shift
+            const uint32_t jr = pt % a.rows, jj = jr % a.jc, n1g = a.n1g + a.n1 * (jr / a.jc);
+            const uint32_t uv = (pt / a.rows) & 1, pr = a.pb0 + pt / (2 * a.rows);
+            const uint32_t i = pr / a.bcount, b = pr % a.bcount, k = n1g + b;
+            const uint32_t o = (j + D - n1g % D) % D;   // feature before the giant-step shift
             const bool wraps = o + k >= D;
             if (wraps == (uv == 1))
                 v = a.Wd[(((size_t)(a.j0 + jj) * a.n_in + i) * D + k) * D + o];
@@ -239,8 +241,9 @@ __global__ __launch_bounds__(kThreads) void k_mac_tm(uint64_t *acc, const double
 // so that with C_s = sum_{a + b = s} sum_kappa Qd_a Xd_b (13 groups, each a sum of int8 x int8 products that
 // v_mfma_i32_16x16x64_i8 accumulates exactly in int32 while K <= 4096: |C_s| < 7 * 4096 * 2^14 < 2^31)
 //   sum_kappa Q X = sum_s 256^s C_s   (an integer identity, reduced mod q_l in the epilogue).
-// The ciphertext digits are laid out once per projection as Xd[digit][l][poly N + pos][kappa] (kappa
-// contiguous, 16 bytes per MFMA lane); the plaintext digits of a 64-kappa block are formed in LDS from Q.
+// The ciphertext digits are laid out once per projection as Xd[digit][l][kappa / 64][poly N + pos][kappa mod 64]: a
+// wave's MFMA operand, 16 positions of 64 kappa, is 1 KB in a row (with kappa running over the whole row instead, its
+// 64-byte pieces lay kt_pad bytes apart: 3 TB/s); the plaintext digits of a 64-kappa block are formed in LDS from Q.
 // Operand layouts (checked on the hardware): A 16x64, lane i holds row i % 16, bytes k = 16 (i / 16) + 0..15;
 // B 64x16, lane i holds column i % 16, the same k; C 16x16, lane i holds column i % 16, rows 4 (i / 16) + r.
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -260,8 +263,8 @@ __device__ __forceinline__ void digits7(uint64_t v, int8_t *d, size_t stride)
     }
 }
 
-// x2 ([n_in][n1][xr, xw][2][L][N] canonical) -> Xd[a][l][poly N + pos][kappa], kappa = 2 (i n1 + b) + uv < kt
-// (rows padded to kt_pad bytes with zeros).  Block: (l, 64 columns, 64 kappa), staged through LDS.
+// x2 ([n_in][n1][xr, xw][2][L][N] canonical) -> Xd[a][l][kappa / 64][poly N + pos][kappa mod 64],
+// kappa = 2 (i n1 + b) + uv < kt (zeros from kt to kt_pad).  Block: (l, 64 columns, 64 kappa), staged through LDS.
 __global__ __launch_bounds__(kThreads) void k_xdigits(const uint64_t *__restrict__ x2, int8_t *Xd, uint32_t L,
                                                       uint32_t log_n, uint32_t kt, uint32_t kt_pad)
 {
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(kThreads) void k_xdigits(const uint64_t *__restrict
             w[a][i >> 2] |= (uint32_t)(uint8_t)t << (8 * (i & 3));
         }
     }
-    int8_t *dst = Xd + ((size_t)l * cols + c0 + cc) * kt_pad + k0 + kq;
+    int8_t *dst = Xd + (((size_t)l * kblocks + kb) * cols + c0 + cc) * 64 + kq;
 #pragma unroll
     for (int a = 0; a < kDig; a++)
         *(uint4 *)(dst + (size_t)a * plane) = make_uint4(w[a][0], w[a][1], w[a][2], w[a][3]);
@@ -335,7 +338,12 @@ __global__ __launch_bounds__(64 * NW) void k_mac_tm_mfma(uint64_t *acc, const in
     const uint32_t pos = (x << logT) + 16 * (part * NW + w) + (lane & 15);
     const size_t n = (size_t)1 << log_n, cols = 2 * n;
     const size_t plane = (size_t)L * cols * kt_pad;
-    const int8_t *xb = Xd + ((size_t)l * cols + (size_t)poly * n + pos) * kt_pad + kappa_base + 16 * (lane >> 4);
+    // this lane's 16 kappa of block k0 (kappa_base is a multiple of 16, so they lie in one 64-kappa block)
+    const int8_t *xb = Xd + ((size_t)l * cols * (kt_pad / 64) + (size_t)poly * n + pos) * 64;
+    auto xoff = [&](uint32_t k0) {
+        const uint32_t kap = kappa_base + k0 + 16 * (lane >> 4);
+        return (size_t)(kap >> 6) * cols * 64 + (kap & 63u);
+    };
     const double *qx = Q + ((size_t)l * D2 + x) * (size_t)K * jc;
     v4i c[MT][kGroups];
 #pragma unroll
@@ -359,7 +367,7 @@ __global__ __launch_bounds__(64 * NW) void k_mac_tm_mfma(uint64_t *acc, const in
     v4i bn[kDig];
     double qn[QPT][4];
 #pragma unroll
-    for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane);
+    for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane + xoff(0));
     load_q(0, qn);
     for (uint32_t k0 = 0; k0 < K; k0 += kKB) {
         v4i b[kDig];
@@ -372,7 +380,7 @@ __global__ __launch_bounds__(64 * NW) void k_mac_tm_mfma(uint64_t *acc, const in
             for (int t = 0; t < 4; t++) qc[i][t] = qn[i][t];
         if (k0 + kKB < K) {
 #pragma unroll
-            for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane + k0 + kKB);
+            for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane + xoff(k0 + kKB));
             load_q(k0 + kKB, qn);
         }
         __syncthreads();
@@ -435,6 +443,7 @@ __global__ __launch_bounds__(64 * NW) void k_mac_tm_mfma(uint64_t *acc, const in
 
 struct TmScratch {
     uint32_t Jt, Pb;
+    uint32_t G;            // giant steps per launch
     bool mfma;             // the multiply-accumulate runs on the matrix cores
     uint32_t kt, kt_pad;   // kappa count (2 n_in n1) and the padded digit-row length in bytes
     size_t x2_w, acc_w, tot_w, rot_w, q_w, ks_w, wd_w, xd_w, ua_w, total;
@@ -453,9 +462,13 @@ TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in,
     const uint32_t jmax = ts.mfma ? kMaxJtMfma : kJT;
     const uint32_t tiles = (n_out + jmax - 1) / jmax;
     ts.Jt = (n_out + tiles - 1) / tiles;
+    // with few outputs several giant steps share a launch (their plaintexts are rows of the same product): the digit
+    // planes are read once for all of them, and their sums' key switching is one batch
+    ts.G = ts.mfma ? std::max(1u, std::min((D + n1 - 1) / n1, (uint32_t)kMaxJtMfma / ts.Jt)) : 1;
+    const uint32_t rows = ts.G * ts.Jt;
     // pairs per sub-batch: the tile's weight tables within 2 GiB, a multiple of 8 (16-byte aligned digit rows),
     // at most 2048 (int32 digit sums stay exact)
-    const size_t per_pair = (size_t)2 * ts.Jt * L * 2 * D * sizeof(double);
+    const size_t per_pair = (size_t)2 * rows * L * 2 * D * sizeof(double);
     const uint32_t maxpairs = n_in * n1;
     uint32_t Pb = (uint32_t)std::min<size_t>(2048, std::max<size_t>(8, ((size_t)1 << 31) / per_pair));
     if (ctx->proj_max_pairs) Pb = std::min(Pb, std::max<uint32_t>(8, ctx->proj_max_pairs));
@@ -464,10 +477,11 @@ TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in,
     ts.kt = 2 * n_in * n1;
     ts.kt_pad = ((ts.kt + 63) & ~63u) + 64;
     ts.x2_w = (size_t)n_in * n1 * 2 * ctw;
-    ts.acc_w = ts.tot_w = ts.rot_w = (size_t)ts.Jt * ctw;
-    ts.q_w = (size_t)ts.Pb * 2 * ts.Jt * L * 2 * D;
+    ts.acc_w = ts.rot_w = (size_t)rows * ctw;
+    ts.tot_w = (size_t)ts.Jt * ctw;
+    ts.q_w = (size_t)ts.Pb * 2 * rows * L * 2 * D;
     ts.ks_w = std::max(ks_scratch_words(ctx, level, ks_rot_batch(2 * n1 - 1)),
-                       ks_scratch_words(ctx, level, ks_rot_batch(ts.Jt), ts.Jt));
+                       ks_scratch_words(ctx, level, ks_rot_batch(rows), rows));
     ts.wd_w = (size_t)d_in * d_out;
     ts.xd_w = ts.mfma ? ((size_t)kDig * L * 2 * N * ts.kt_pad + 7) / 8 : 0;
     ts.ua_w = ctx->lazy_moddown ? (size_t)ts.Jt * 2 * (L + ctx->n_p) * N : 0;
@@ -478,7 +492,7 @@ TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in,
 ckks_status launch_mac_tm_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, const double *Q, const TmArgs &a,
                                uint32_t kt_pad, uint32_t L, uint32_t logT, bool accumulate)
 {
-    return launch_mac_mfma(ctx, acc, Xd, Q, a.jc, 2 * a.P, 2 * a.pb0, kt_pad, 2 * a.D, L, logT, accumulate);
+    return launch_mac_mfma(ctx, acc, Xd, Q, a.rows, 2 * a.P, 2 * a.pb0, kt_pad, 2 * a.D, L, logT, accumulate);
 }
 
 ckks_status launch_mac_tm(ckks_ctx *ctx, uint64_t *acc, const double *x2, const double *Q, const TmArgs &a,
@@ -576,17 +590,24 @@ ckks_status launch_mac_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, cons
     prof_begin(ctx, K_MAC_TM, (double)kDig * K * 2 * L * ctx->n + 8.0 * (double)K * jc * L * D2 +
                                   8.0 * res * (accumulate ? 2 : 1),
                0.0);
-#define CK_MFMA(NWV, MTV)                                                                                          \
+    // outputs in tiles of 16 rows: one tile where the launch has no more
+#define CK_MFMA(NWV)                                                                                               \
+    if (jc <= 16)                                                                                                  \
+        CK_MFMA_T(NWV, 1);                                                                                         \
+    else                                                                                                           \
+        CK_MFMA_T(NWV, 2)
+#define CK_MFMA_T(NWV, MTV)                                                                                        \
     hipLaunchKernelGGL((k_mac_tm_mfma<NWV, MTV>), dim3(L * D2 * 2 * (tiles16 / NWV)), dim3(64 * NWV), 0,           \
                        ctx->stream, acc, Xd, Q, jc, K, kbase, kt_pad, D2, L, logT, ctx->log_n, (int)accumulate,     \
                        ctx->d_mod)
     switch (tiles16) {
-    case 1: CK_MFMA(1, 2); break;
-    case 2: CK_MFMA(2, 2); break;
-    case 4: CK_MFMA(4, 2); break;
-    default: CK_MFMA(8, 2); break;
+    case 1: CK_MFMA(1); break;
+    case 2: CK_MFMA(2); break;
+    case 4: CK_MFMA(4); break;
+    default: CK_MFMA(8); break;
     }
 #undef CK_MFMA
+#undef CK_MFMA_T
     prof_end(ctx, K_MAC_TM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
@@ -601,7 +622,7 @@ ckks_status launch_enc_vectors(ckks_ctx *ctx, const double *U, uint32_t D, uint3
     a.U = U;
     a.D = D;
     while ((1u << a.logD) < D) a.logD++;
-    a.jc = 1;
+    a.jc = a.rows = 1;
     a.bcount = 1;
     a.npt = count;
     return launch_enc_periodic(ctx, a, delta, L, Q);
@@ -700,7 +721,8 @@ extern "C" ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in,
     while ((1u << logD) < D) logD++;
     for (uint32_t j0 = 0; j0 < n_out; j0 += ts.Jt) {
         const uint32_t jc = std::min(ts.Jt, n_out - j0);
-        for (uint32_t g = 0; g < n2; g++) {
+        for (uint32_t g = 0; g < n2; g += ts.G) {
+            const uint32_t gc = std::min(ts.G, n2 - g);   // giant steps of this launch (one, unless D % n1 == 0)
             const uint32_t bcount = std::min(n1, D - n1 * g);
             const uint32_t pairs = n_in * bcount;
             const uint32_t nsub = (pairs + ts.Pb - 1) / ts.Pb;
@@ -715,9 +737,11 @@ extern "C" ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in,
                 a.bcount = bcount;
                 a.j0 = j0;
                 a.jc = jc;
+                a.n1 = n1;
+                a.rows = gc * jc;
                 a.pb0 = pb0;
                 a.P = std::min(ts.Pb, pairs - pb0);
-                a.npt = a.P * 2 * jc;
+                a.npt = a.P * 2 * a.rows;
                 CK_TRY(launch_enc_periodic(ctx, a, delta_w, L, Q));
                 if (ts.mfma)
                     CK_TRY(launch_mac_tm_mfma(ctx, acc, Xd, Q, a, ts.kt_pad, L, logT, pb0 > 0));
@@ -725,16 +749,7 @@ extern "C" ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in,
                     CK_TRY(launch_mac_tm(ctx, acc, (const double *)x2, Q, a, n1, L, logT, pb0 > 0));
                 pb0 += a.P;
             }
-            if (g == 0) {
-                HIP_TRY(hipMemcpyAsync(tot, acc, jc * ctw * 8, hipMemcpyDeviceToDevice, ctx->stream));
-            } else if (lazy) {
-                CK_TRY(rotate_many_lazy(ctx, acc, ctw, jc, level, (int32_t)(n1 * g), gkeys[g], uacc, g > 1, ksw));
-            } else {
-                std::vector<uint64_t *> outs(jc);
-                for (uint32_t jj = 0; jj < jc; jj++) outs[jj] = rot + (size_t)jj * ctw;
-                CK_TRY(rotate_many(ctx, acc, ctw, jc, level, (int32_t)(n1 * g), gkeys[g], outs.data(), ksw));
-                CK_TRY(launch_binary(ctx, tot, tot, rot, jc * 2 * L, limb_range(0, L), EW_ADD));
-            }
+            CK_TRY(giant_steps(ctx, acc, tot, rot, uacc, jc, g, gc, (int32_t)n1, gkeys.data(), level, lazy, ksw));
         }
         if (lazy && n2 > 1) {
             CK_TRY(ks_moddown(ctx, uacc, 2 * jc, level, nullptr, 1, nullptr, rot, ksw));
