@@ -86,7 +86,7 @@ struct ckks_ctx {
     bool int_only = false;               // force the integer Shoup butterflies
     uint32_t proj_max_pairs = 0;         // projection sub-batch limit (0 = by the staging budget)
     bool lazy_moddown = false;           // sums of rotations with one ModDown per output
-    std::vector<uint8_t> blk_level;      // levels whose key switching the whole-row kernels take (ring_block.hip)
+    std::vector<uint8_t> f64_level;      // levels whose key switching is fp64 throughout, N >= 2^12 (f64_level_ok)
     uint32_t sum128_terms = 0;           // products of two residues an exact 128-bit sum holds (with a residue)
     double2 *d_fft_w = nullptr;          // [N/4]  omega^-e, omega = exp(2 pi i/(N/2))
     double2 *d_fft_wc = nullptr;         // [2048] stage-by-stage copy for 2048-point blocks (N >= 2^12)
@@ -162,10 +162,6 @@ bool ntt_uses_f64(const ckks_ctx *ctx, uint32_t limbs);
 // column pass only of a forward transform (fp64 primes, two-pass sizes); the rows are left as raw doubles
 ckks_status launch_ntt_fwd_first_pass(ckks_ctx *ctx, uint64_t *data, uint32_t batch, uint32_t bstride,
                                       const LimbMap &map);
-// column pass only of an inverse transform whose row pass a fused kernel ran (rows as raw doubles below 2q; fp64
-// primes, two-pass sizes): canonical coefficients out
-ckks_status launch_ntt_inv_second_pass(ckks_ctx *ctx, uint64_t *data, uint32_t batch, uint32_t bstride,
-                                       const LimbMap &map);
 // column pass only of launch_ntt_from_i64 (two-pass sizes); the rows stay in the inter-pass form
 ckks_status launch_ntt_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32_t batch, uint32_t limbs);
 // nominal VALU instructions of one radix-2 butterfly: fp64 (product with FMA

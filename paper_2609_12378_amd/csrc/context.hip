@@ -323,8 +323,8 @@ static ckks_status build_all_conv(ckks_ctx *c)
         CK_TRY(ctx_conv(c, (int)level, -1, &cd));
         for (uint32_t j = 0; j < n_digits(c, level); j++) CK_TRY(ctx_conv(c, (int)level, (int)j, &cd));
     }
-    c->blk_level.resize(c->n_q);
-    for (uint32_t level = 0; level < c->n_q; level++) c->blk_level[level] = blk_level_ok(c, level);
+    c->f64_level.resize(c->n_q);
+    for (uint32_t level = 0; level < c->n_q; level++) c->f64_level[level] = f64_level_ok(c, level);
     return CKKS_OK;
 }
 

@@ -170,79 +170,6 @@ __global__ __launch_bounds__(kThreads) void k_conv_f64(const uint64_t *in, uint3
     }
 }
 
-// The fp64 conversion (at most 8 source limbs) fused with the first forward column pass, N = 2^16: block
-// (poly, 16 adjacent columns), 512 threads, 8 points of one 256-point column per thread.  The centred source
-// digits y_i of the block's 4096 coefficients stay in registers; for each target limb in turn the block forms
-// the converted residues with the sums of k_conv_f64 (reduced to |x| <= t/2 rather than made canonical), runs that limb's column sub-transforms on them (nttc::fwd8_256 with the column pass's
-// lazy-reduction mask) and writes the rows as raw doubles, the inter-pass form the fused row passes read.  The
-// converted rows thus cross HBM once instead of three times (written, read and written by a separate column
-// pass, read by the ModDown).  Target t + 1's twiddles (Psi[1..255]) are staged into the idle half of a
-// double-buffered table while target t is transformed.  EXACT: ns == 8 (no guards on the source loop, all
-// source loads issued first).
-template <bool EXACT>
-__global__ __launch_bounds__(512) void k_conv_col8(const uint64_t *__restrict__ in, uint32_t in_stride,
-                                                   uint64_t *out, uint32_t out_stride, uint32_t split, uint32_t skip,
-                                                   ConvArgs a, const double *__restrict__ qhat_inv,
-                                                   const double *__restrict__ qhat_mod,
-                                                   const ModQ *__restrict__ mods, const double *__restrict__ twf,
-                                                   uint32_t log_n, uint32_t blocks_per_row, uint32_t t_per)
-{
-    using nttc::Ar;
-    using nttc::kE8;
-    __shared__ double s_mod[8 * kMaxPrimes];
-    __shared__ double tws[2][256];
-    __shared__ double tr[16][nttc::kTr8], trb[16][nttc::kTr8];
-    const int ns = EXACT ? 8 : a.ns, nt = a.nt;
-    for (int k = threadIdx.x; k < ns * nt; k += 512) s_mod[k] = qhat_mod[k];
-    // blockIdx.y: this block's group of t_per targets
-    const int t0 = (int)(blockIdx.y * t_per), t1 = min(nt, t0 + (int)t_per);
-    if (threadIdx.x < 255) tws[t0 & 1][threadIdx.x + 1] = twf[((size_t)a.dst[t0] << log_n) + threadIdx.x + 1];
-    const uint32_t poly = blockIdx.x / blocks_per_row, blk = blockIdx.x % blocks_per_row;
-    const uint32_t n2 = 1u << (log_n - 8);
-    const uint32_t col = threadIdx.x & 15, t = threadIdx.x >> 4;
-    const size_t coff = (size_t)blk * 16 + col;
-    const uint64_t *src = in + ((size_t)poly * in_stride << log_n) + coff;
-    uint64_t raw[8][kE8];
-#pragma unroll
-    for (int i = 0; i < 8; i++)
-#pragma unroll
-        for (int k = 0; k < kE8; k++)
-            if (EXACT || i < ns) raw[i][k] = src[((size_t)i << log_n) + (size_t)nttc::u8<0>(t, k) * n2];
-    double y[kE8][8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-        if (EXACT || i < ns) {
-            const Ar<true> ar(mods[a.src[i]]);
-            const double h = 0.5 * ar.q, w = qhat_inv[i];
-#pragma unroll
-            for (int k = 0; k < kE8; k++) {
-                const double v = ar.mul(Ar<true>::from_u64(raw[i][k]), w);
-                y[k][i] = v > h ? v - ar.q : (v < -h ? v + ar.q : v);
-            }
-        }
-    }
-    __syncthreads();
-    for (int tt = t0; tt < t1; tt++) {
-        const Ar<true> ar(mods[a.dst[tt]]);
-        nttc::StageNext next{tws[(tt + 1) & 1], 0.0, tt + 1 < t1 && threadIdx.x < 255};
-        if (next.on) next.v = twf[((size_t)a.dst[tt + 1] << log_n) + threadIdx.x + 1];
-        double x[kE8];
-#pragma unroll
-        for (int k = 0; k < kE8; k++) {
-            nttc::GridSum acc;
-#pragma unroll
-            for (int i = 0; i < 8; i++)
-                if (EXACT || i < ns) acc.add(y[k][i], s_mod[i * nt + tt]);
-            x[k] = ar.red(acc.value(ar));
-        }
-        nttc::fwd8_256_loop<nttc::kColMask8>(x, tws[tt & 1], tr[col], trb[col], t, ar, next);
-        const uint32_t row = tt < (int)split ? tt : tt + skip;
-        uint64_t *dst = out + (((size_t)poly * out_stride + row) << log_n) + coff;
-#pragma unroll
-        for (int k = 0; k < kE8; k++) nttc::st_stream(dst + (size_t)nttc::u8<2>(t, k) * n2, Ar<true>::to_raw(x[k]));
-    }
-}
-
 // out[k][i][n] = (u[k][i][n] - c[k][i][n]) * P^-1 + add_k[i][sigma_k(n)], i <= level
 __global__ __launch_bounds__(kThreads) void k_moddown_finish(uint64_t *out, const uint64_t *u, const uint64_t *c,
                                                               const uint64_t *add0, uint32_t add0_g,
@@ -765,42 +692,6 @@ ckks_status launch_conv(ckks_ctx *ctx, const ConvDev *cd, const uint64_t *in, ui
     return CKKS_OK;
 }
 
-// The raw fp64 conversion of `polys` polynomials followed by the first forward column pass of its output rows
-// (N = 2^16, at most 8 source limbs), in one kernel: out rows as launch_conv writes them, in the inter-pass form.
-ckks_status launch_conv_col8(ckks_ctx *ctx, const ConvDev *cd, const uint64_t *in, uint32_t in_stride, uint64_t *out,
-                             uint32_t out_stride, uint32_t split, uint32_t skip, uint32_t polys)
-{
-    CK_REQUIRE(ctx->log_n == 16 && cd->f64 && !ctx->int_only && cd->ns >= 1 && cd->ns <= 8 && cd->nt >= 1,
-               CKKS_EINVAL, "fused conversion needs N = 2^16, the fp64 tables and 1..8 source limbs");
-    CK_REQUIRE(split <= (uint32_t)cd->nt && (uint32_t)cd->nt + skip <= out_stride && cd->ns <= (int)in_stride,
-               CKKS_EINVAL, "fused conversion: target rows outside the output");
-    ConvArgs a;
-    a.ns = cd->ns;
-    a.nt = cd->nt;
-    for (int i = 0; i < cd->ns; i++) a.src[i] = cd->src[i];
-    for (int t = 0; t < cd->nt; t++) a.dst[t] = cd->dst[t];
-    const uint32_t bpr = 1u << (ctx->log_n - 12);
-    const double res = (double)polys * ctx->n;
-    // fewer than 256 blocks (one a CU): the targets split over blockIdx.y until the grid has that many, each group
-    // forming the centred digits again (one relinearisation at 13 limbs, 32 blocks: 61 -> 16 us)
-    const uint32_t want = std::max(1u, 256u / (polys * bpr)), ntu = (uint32_t)a.nt;
-    const uint32_t t_per = (ntu + std::min(want, ntu) - 1) / std::min(want, ntu);
-    const dim3 grid(polys * bpr, (ntu + t_per - 1) / t_per);
-    // the sources once, the converted rows once; the conversion products and the column pass's butterflies
-    prof_begin(ctx, K_CONV, 8.0 * res * (a.ns + a.nt), res * a.nt * (a.ns * 5.0 + kOpsButterflyF64 * 4));
-    if (a.ns == 8)
-        hipLaunchKernelGGL(k_conv_col8<true>, grid, dim3(512), 0, ctx->stream, in, in_stride, out,
-                           out_stride, split, skip, a, cd->d_qhat_inv_f, cd->d_qhat_mod_f, ctx->d_mod, ctx->d_twf,
-                           ctx->log_n, bpr, t_per);
-    else
-        hipLaunchKernelGGL(k_conv_col8<false>, grid, dim3(512), 0, ctx->stream, in, in_stride, out,
-                           out_stride, split, skip, a, cd->d_qhat_inv_f, cd->d_qhat_mod_f, ctx->d_mod, ctx->d_twf,
-                           ctx->log_n, bpr, t_per);
-    prof_end(ctx, K_CONV);
-    HIP_TRY(hipGetLastError());
-    return CKKS_OK;
-}
-
 // The a half [dnum][R][N] of a seed-expanded key: thread (prime k, position n) draws the Philox blocks of every
 // group of four digits (philox.h).
 __global__ __launch_bounds__(256) void k_expand_key_a(uint64_t *a, uint64_t s0, uint64_t s1, uint32_t dnum,
@@ -890,10 +781,9 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
         // fused ModDown: only the P rows of u are formed in HBM
         uint64_t *up = work;                             // [count][2][K][N]
         uint64_t *cw = up + (size_t)count * 2 * K * N;   // [count][2][L][N]
-        bool p_f64 = !ctx->int_only;
-        for (uint32_t i = 0; i < K; i++) p_f64 = p_f64 && ctx->f64_ok[ctx->n_q + i];
-        if (s1 == 8 && p_f64) {
-            // the P rows' inner products with the first pass of their inverse transform, then its second pass
+        if (f64_switch(ctx, level)) {
+            // the P rows' inner products with the first pass of their inverse transform, then its second pass, the
+            // conversion and the first forward pass of the converted rows
             const uint32_t bpl = 1u << (ctx->log_n - 9);
             const double res = (double)count * 2 * K * N;
             prof_begin(ctx, K_KEYIP, 8.0 * res * (nd + 1.0) + 8.0 * (double)nd * K * N,
@@ -908,7 +798,7 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
 #undef CK_IPI
             prof_end(ctx, K_KEYIP);
             HIP_TRY(hipGetLastError());
-            CK_TRY(launch_ntt_inv_second_pass(ctx, up, 2 * count, K, limb_range(ctx->n_q, K)));
+            CK_TRY(up_moddown(ctx, up, 2 * count, level, cw));
         } else {
             const dim3 grid((ctx->n + kThreads - 1) / kThreads, K, count), block(kThreads);
             prof_begin(ctx, K_KEYIP, 8.0 * ctx->n * K * (count * (2.0 * nd + 2.0) + nd));
@@ -921,13 +811,8 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
             prof_end(ctx, K_KEYIP);
             HIP_TRY(hipGetLastError());
             CK_TRY(launch_ntt_strided(ctx, up, 2 * count, K, limb_range(ctx->n_q, K), true));
-        }
-        const ConvDev *cd;
-        CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
-        if (s1 == 8 && cd->f64 && !ctx->int_only && cd->ns <= 8) {
-            // the conversion and the first forward pass of the converted rows in one kernel
-            CK_TRY(launch_conv_col8(ctx, cd, up, K, cw, L, L, 0, 2 * count));
-        } else {
+            const ConvDev *cd;
+            CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
             CK_TRY(launch_conv(ctx, cd, up, K, cw, L, L, 0, 2 * count));
             CK_TRY(launch_ntt_fwd_first_pass(ctx, cw, 2 * count, L, limb_range(0, L)));
         }
@@ -1025,12 +910,13 @@ ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, 
                            uint64_t *digits, size_t stage_rows)
 {
     if (!count) return CKKS_OK;
-    if (blk_switch(ctx, level) && (size_t)count * (level + 1) <= stage_rows)
+    if (blk_modups(ctx, level, count) && (size_t)count * (level + 1) <= stage_rows)
         return blk_modup(ctx, c1, count == 1 ? 0 : in_stride, nullptr, count, level, digits,
                          digits + (size_t)count * n_digits(ctx, level) * (level + 1 + ctx->n_p) * ctx->n);
     const uint32_t K = ctx->n_p, ext = level + 1 + K, nd = n_digits(ctx, level), alpha = ctx->alpha;
     const size_t N = ctx->n, dig_ct = (size_t)nd * ext * N;
     const size_t cstride = count == 1 ? 0 : in_stride;
+    if (f64_switch(ctx, level)) return up_modup(ctx, c1, cstride, count, level, digits);
     // A few ciphertexts leave each digit's transforms of its converted rows too small to fill the chip: then one
     // forward transform runs over all ext rows of every digit (each digit's own rows are transformed along and
     // overwritten with their NTT-domain values afterwards): 2 launches in place of 2 nd.  With more ciphertexts

@@ -79,6 +79,20 @@ ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, cons
                              const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
                              uint64_t *const *accs, uint32_t n_accs, bool accumulate);
 
+// ModUp and ModDown conversions in fp64 (modup.hip): N >= 2^12, every prime of the level and of P below 2^50, at most
+// 16 source limbs a conversion (computed once per context: ckks_ctx::f64_level)
+bool f64_level_ok(const ckks_ctx *ctx, uint32_t level);
+inline bool f64_switch(const ckks_ctx *ctx, uint32_t level)
+{
+    return !ctx->int_only && level < ctx->f64_level.size() && ctx->f64_level[level];
+}
+// ModUp of `count` polynomials at c1 + r stride into digits [count][nd][level+1+n_p][N]; needs no other memory
+ckks_status up_modup(ckks_ctx *ctx, const uint64_t *c1, size_t stride, uint32_t count, uint32_t level,
+                     uint64_t *digits);
+// up: [polys][n_p][N] rows modulo P after the row pass of their inverse transform (raw doubles below 2q): finishes it,
+// converts to the level's q limbs and runs the first forward pass into cw ([polys][level+1][N] raw doubles)
+ckks_status up_moddown(ckks_ctx *ctx, uint64_t *up, uint32_t polys, uint32_t level, uint64_t *cw);
+
 // Whole rows per block (ring_block.hip): N = 2^12 .. 2^14, fp64 primes.
 // the ring has them and the fp64 arithmetic is not switched off
 bool blk_ring(const ckks_ctx *ctx);
@@ -86,14 +100,12 @@ bool blk_ring(const ckks_ctx *ctx);
 bool blk_rows(const ckks_ctx *ctx, size_t rows);
 // they are the faster encryption and decryption of `limbs` limbs
 bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs);
+// they are the faster ModUp of `count` ciphertexts at `level`
+bool blk_modups(const ckks_ctx *ctx, uint32_t level, uint32_t count);
 // they are the faster key switching for a batch of `count` rotations at `level`
 bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count);
-// they take every key-switching step at `level` (computed once per context: ckks_ctx::blk_level)
-bool blk_level_ok(const ckks_ctx *ctx, uint32_t level);
-inline bool blk_switch(const ckks_ctx *ctx, uint32_t level)
-{
-    return !ctx->int_only && level < ctx->blk_level.size() && ctx->blk_level[level];
-}
+// they take every key-switching step at `level`
+bool blk_switch(const ckks_ctx *ctx, uint32_t level);
 // transform of `batch` groups of map.n rows from src (group stride src_stride rows) to dst; dst may be src
 ckks_status blk_ntt(ckks_ctx *ctx, uint64_t *dst, uint32_t dst_stride, const uint64_t *src, uint32_t src_stride,
                     uint32_t batch, const LimbMap &map, bool inverse);

@@ -546,8 +546,6 @@ bool early_loads(const ckks_ctx *ctx, size_t blocks) { return ctx->log_n <= 13 &
             CK_BLK(CK_L, GRID, __VA_ARGS__);                                                                       \
     } while (0)
 
-constexpr int kMaxSrc = 16;  // source limbs of a conversion (the fp64 conversion kernels' limit too)
-
 ckks_status launch_moddown_p(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t L, uint32_t K, const ConvDev *cd)
 {
     prof_begin(ctx, K_NTT_INV_ROW, 16.0 * polys * K * ctx->n);
@@ -580,8 +578,6 @@ ckks_status blk_key_product(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, ui
     return CKKS_OK;
 }
 
-bool conv_ok(const ConvDev *cd) { return cd->f64 && cd->ns >= 1 && cd->ns <= kMaxSrc; }
-
 }  // namespace
 
 // N = 2^14: a block is 1024 threads and all of a CU's LDS, 15 us a row with nothing to hide its waits, so the two
@@ -596,6 +592,12 @@ bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs)
     return blk_ring(ctx) && ntt_uses_f64(ctx, limbs) && (ctx->log_n < 14 || limbs >= 12);
 }
 
+// the same for a ModUp (modup.hip: five launches)
+bool blk_modups(const ckks_ctx *ctx, uint32_t level, uint32_t count)
+{
+    return blk_switch(ctx, level) && (ctx->log_n < 14 || count > 1000000);
+}
+
 // the same for a batch of rotations: per rotation of 24 limbs 16 us here against 13 us in the fused two-pass kernels
 // (keyswitch.hip), but 70 us less for a single one
 bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count)
@@ -605,17 +607,7 @@ bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count)
 
 bool blk_ring(const ckks_ctx *ctx) { return ctx->log_n >= blk::kMinLog && ctx->log_n <= blk::kMaxLog && !ctx->int_only; }
 
-bool blk_level_ok(const ckks_ctx *ctx, uint32_t level)
-{
-    if (ctx->log_n < (uint32_t)blk::kMinLog || ctx->log_n > (uint32_t)blk::kMaxLog || !ctx->n_p) return false;
-    for (uint32_t i = 0; i < ctx->n_primes(); i++)
-        if ((i <= level || i >= ctx->n_q) && !ctx->f64_ok[i]) return false;
-    for (int j = -1; j < (int)n_digits(ctx, level); j++) {
-        const auto it = ctx->conv.find({(int)level, j});
-        if (it == ctx->conv.end() || !conv_ok(&it->second)) return false;
-    }
-    return true;
-}
+bool blk_switch(const ckks_ctx *ctx, uint32_t level) { return blk_ring(ctx) && f64_switch(ctx, level); }
 
 ckks_status blk_ntt(ckks_ctx *ctx, uint64_t *dst, uint32_t dst_stride, const uint64_t *src, uint32_t src_stride,
                     uint32_t batch, const LimbMap &map, bool inverse)
