@@ -190,7 +190,8 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
     if (!count) return CKKS_OK;
     const size_t N = ctx->n;
     const uint32_t polys = 2 * count;
-    if (blk_ring(ctx) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, polys, l, out, work);
+    if (blk_rows(ctx, (size_t)polys * l) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, polys, l, out, work);
+    if (fused_rows_ok(ctx)) return fused_rescale(ctx, c, polys, l, out, nullptr, work);
     uint64_t *top = work, *r = top + (size_t)polys * N;
     // the top limb of every polynomial, then the same steps as one rescale over all of them
     CK_TRY(launch_copy_rows(ctx, top, N, nullptr, 0, c + (size_t)l * N, (size_t)(l + 1) * N, N, polys));
@@ -201,19 +202,20 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
     return launch_rescale_finish(ctx, out, c, r, polys, l);
 }
 
+ckks_status rescale_each(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint32_t l, uint64_t *const *outs,
+                         uint64_t *work)
+{
+    if (fused_rows_ok(ctx) && !(blk_rows(ctx, 2 * l) && ntt_uses_f64(ctx, l + 1)))
+        return fused_rescale(ctx, c, 2 * count, l, nullptr, outs, work);
+    for (uint32_t r = 0; r < count; r++)
+        CK_TRY(rescale_many(ctx, c + (size_t)r * 2 * (l + 1) * ctx->n, 1, l, outs[r], work));
+    return CKKS_OK;
+}
+
 // c ([2][l+1][N]) -> out ([2][l][N]) = round(c / q_l); work: (2 + 2l) N words
 ckks_status rescale_core(ckks_ctx *ctx, const uint64_t *c, uint32_t l, uint64_t *out, uint64_t *work)
 {
-    const size_t N = ctx->n;
-    if (blk_ring(ctx) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, 2, l, out, work);
-    uint64_t *top = work, *r = top + 2 * N;
-    for (int k = 0; k < 2; k++)
-        HIP_TRY(hipMemcpyAsync(top + k * N, c + ((size_t)k * (l + 1) + l) * N, N * 8, hipMemcpyDeviceToDevice,
-                               ctx->stream));
-    CK_TRY(launch_ntt(ctx, top, 2, limb_range(l, 1), true));
-    CK_TRY(launch_rescale_centre(ctx, top, 2, l));
-    CK_TRY(launch_ntt_from_i64(ctx, (const int64_t *)top, r, 2, l));
-    return launch_rescale_finish(ctx, out, c, r, 2, l);
+    return rescale_many(ctx, c, 1, l, out, work);
 }
 
 extern "C" {
@@ -276,6 +278,11 @@ ckks_status ckks_encrypt_sk(ckks_ctx *ctx, const int8_t *s, const ckks_buf *pt, 
         ct->scale = pt->scale;
         return CKKS_OK;
     }
+    if (fused_rows_ok(ctx)) {
+        CK_TRY(fused_encrypt(ctx, ct->data, ct->data + words(ctx, L), a, s, e, pt->data, L, (uint64_t *)w));
+        ct->scale = pt->scale;
+        return CKKS_OK;
+    }
     uint64_t *sn = (uint64_t *)w, *en = sn + words(ctx, L);
     const LimbMap map = limb_range(0, L);
     CK_TRY(launch_expand_i8(ctx, sn, s, map));
@@ -298,6 +305,11 @@ ckks_status ckks_decrypt(ckks_ctx *ctx, const int8_t *s, const ckks_buf *ct, ckk
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_DECRYPT, &L), &w));
     if (blk_crypt(ctx, L)) {
         CK_TRY(blk_decrypt(ctx, pt->data, ct->data, ct->data + words(ctx, L), s, L));
+        pt->scale = ct->scale;
+        return CKKS_OK;
+    }
+    if (fused_rows_ok(ctx)) {
+        CK_TRY(fused_decrypt(ctx, pt->data, ct->data, ct->data + words(ctx, L), s, L, (uint64_t *)w));
         pt->scale = ct->scale;
         return CKKS_OK;
     }

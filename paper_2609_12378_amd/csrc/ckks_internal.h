@@ -159,7 +159,13 @@ ckks_status launch_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, 
 void ntt_split(uint32_t log_n, int *s1, int *s2);
 // the transforms over primes 0..limbs-1 use the fp64 butterflies
 bool ntt_uses_f64(const ckks_ctx *ctx, uint32_t limbs);
-// column pass only of a forward transform (fp64 primes, two-pass sizes); the rows are left as raw doubles
+// the transforms over the primes of `map` use the fp64 butterflies
+bool ntt_map_f64(const ckks_ctx *ctx, const LimbMap &map);
+// column pass only of the forward transforms of a secret s and (unless null) an error polynomial e over primes
+// 0..limbs-1 into out [1 or 2][limbs][N]
+ckks_status launch_ntt_col_small(ckks_ctx *ctx, const int8_t *s, const int32_t *e, uint64_t *out, uint32_t limbs);
+// column pass only of a forward transform (two-pass sizes); the rows are left in the inter-pass form of the
+// arithmetic ntt_map_f64 selects
 ckks_status launch_ntt_fwd_first_pass(ckks_ctx *ctx, uint64_t *data, uint32_t batch, uint32_t bstride,
                                       const LimbMap &map);
 // column pass only of launch_ntt_from_i64 (two-pass sizes); the rows stay in the inter-pass form

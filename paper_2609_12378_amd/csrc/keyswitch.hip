@@ -852,6 +852,10 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
     const ConvDev *cd;
     CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
     CK_TRY(launch_conv(ctx, cd, u + (size_t)L * N, ext, cw, L, L, 0, 2 * count));
+    if (s2 == 8 && !ntt_uses_f64(ctx, L)) {
+        CK_TRY(launch_ntt_fwd_first_pass(ctx, cw, 2 * count, L, limb_range(0, L)));
+        return fused_moddown_int(ctx, level, ra, u, cw);
+    }
     CK_TRY(launch_ntt(ctx, cw, 2 * count * L, limb_range(0, L), false));
     {
         const dim3 grid((ctx->n + kThreads - 1) / kThreads, L, 2 * count), block(kThreads);

@@ -139,8 +139,20 @@ __global__ __launch_bounds__(256) void ntt_col(uint64_t *data, LimbMap map, uint
 // transform.
 // Integer arithmetic: below every limb's prime in magnitude (weights at the usual scales), a wave's coefficients
 // are their own residues (or q plus them), so the general reduction is skipped; `small` is the smallest q - 1.
-template <int LOGS, bool F>
-__global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restrict__ m, uint64_t *out, uint32_t limbs,
+// The coefficients come from a source: CoefI64, or CoefSmall, a secret (entry 0) and an error polynomial (entry 1).
+struct CoefI64 {
+    static constexpr bool kWide = true;   // may exceed 2^52
+    const int64_t *m;
+    __device__ int64_t at(uint32_t b, uint32_t log_n, size_t i) const { return m[((size_t)b << log_n) + i]; }
+};
+struct CoefSmall {
+    static constexpr bool kWide = false;
+    const int8_t *s;
+    const int32_t *e;
+    __device__ int64_t at(uint32_t b, uint32_t, size_t i) const { return b ? (int64_t)e[i] : (int64_t)s[i]; }
+};
+template <int LOGS, bool F, typename Src>
+__global__ __launch_bounds__(256) void ntt_col_from_i64(Src m, uint64_t *out, uint32_t limbs,
                                                         const ModQ *mods, const void *tw_all, uint32_t log_n,
                                                         uint32_t cols_per_block, uint32_t blocks_per_row,
                                                         int64_t small, uint32_t l_per)
@@ -153,10 +165,9 @@ __global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restric
     const uint32_t n2 = 1u << (log_n - LOGS);
     const uint32_t col = threadIdx.x % cols_per_block, r = threadIdx.x / cols_per_block;
     const size_t coff = (size_t)blk * cols_per_block + col;
-    const int64_t *src = m + ((size_t)b << log_n) + coff;
     int64_t v[kE];
 #pragma unroll
-    for (int k = 0; k < kE; k++) v[k] = src[(size_t)(r + TS * k) * n2];
+    for (int k = 0; k < kE; k++) v[k] = m.at(b, log_n, coff + (size_t)(r + TS * k) * n2);
     // fp64: coefficients within 2^52 are converted once for all limbs; a thread holding a larger one takes the
     // exact integer reduction for every limb, re-reading its coefficients
     double vd[kE];
@@ -185,9 +196,9 @@ __global__ __launch_bounds__(256) void ntt_col_from_i64(const int64_t *__restric
             if (!big) {
 #pragma unroll
                 for (int k = 0; k < kE; k++) x[k] = ar.red(vd[k]);
-            } else {
+            } else if constexpr (Src::kWide) {
                 // an opaque copy of the pointer: the 16 addresses are formed here, not kept live across the loop
-                auto sg = (const __attribute__((address_space(1))) int64_t *)src;
+                auto sg = (const __attribute__((address_space(1))) int64_t *)(m.m + ((size_t)b << log_n) + coff);
                 asm volatile("" : "+v"(sg));
 #pragma unroll
                 for (int k = 0; k < kE; k++) x[k] = ar.from_i64(sg[(size_t)(r + TS * k) * n2], md);
@@ -408,8 +419,8 @@ uint32_t limbs_per_block(uint32_t blocks, uint32_t limbs, uint32_t fill)
     return (limbs + groups - 1) / groups;
 }
 
-template <int LOGS, bool F>
-hipError_t launch_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32_t batch, uint32_t limbs)
+template <int LOGS, bool F, typename Src>
+hipError_t launch_col_i64(ckks_ctx *ctx, const Src &m, uint64_t *out, uint32_t batch, uint32_t limbs)
 {
     const uint32_t n2 = 1u << (ctx->log_n - LOGS);
     const uint32_t TS = (1u << LOGS) / 16;
@@ -421,7 +432,7 @@ hipError_t launch_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32
     const dim3 grid(batch * bpr, (limbs + l_per - 1) / l_per), block(cols * TS);
     uint64_t qmin = ~0ull;
     for (uint32_t l = 0; l < limbs; l++) qmin = ctx->primes[l] < qmin ? ctx->primes[l] : qmin;
-    hipLaunchKernelGGL((ntt_col_from_i64<LOGS, F>), grid, block, lds_bytes<LOGS>(cols), ctx->stream, m, out, limbs,
+    hipLaunchKernelGGL((ntt_col_from_i64<LOGS, F, Src>), grid, block, lds_bytes<LOGS>(cols), ctx->stream, m, out, limbs,
                        ctx->d_mod, fwd_table<F>(ctx), ctx->log_n, cols, bpr, (int64_t)(qmin - 1), l_per);
     return hipGetLastError();
 }
@@ -452,8 +463,8 @@ hipError_t dispatch_row(int s2, ckks_ctx *ctx, uint64_t *d, uint32_t b, uint32_t
                (launch_row<7, INV, FIRST, LAST, F>(ctx, d, b, bs, m)),
                (launch_row<8, INV, FIRST, LAST, F>(ctx, d, b, bs, m)))
 }
-template <bool F>
-hipError_t dispatch_col_i64(int s1, ckks_ctx *ctx, const int64_t *m, uint64_t *out, uint32_t b, uint32_t limbs)
+template <bool F, typename Src>
+hipError_t dispatch_col_i64(int s1, ckks_ctx *ctx, const Src &m, uint64_t *out, uint32_t b, uint32_t limbs)
 {
     NTT_SWITCH(s1, (launch_col_i64<4, F>(ctx, m, out, b, limbs)), (launch_col_i64<5, F>(ctx, m, out, b, limbs)),
                (launch_col_i64<6, F>(ctx, m, out, b, limbs)), (launch_col_i64<7, F>(ctx, m, out, b, limbs)),
@@ -547,18 +558,20 @@ ckks_status launch_ntt_strided(ckks_ctx *ctx, uint64_t *data, uint32_t batch, ui
 
 void ntt_split(uint32_t log_n, int *s1, int *s2) { split_log((int)log_n, s1, s2); }
 
-// First (column) pass only of the forward transform of `batch` groups of map.n rows, fp64 butterflies; the rows
-// are left as raw doubles for a fused second pass.  Needs a two-pass size and primes below 2^50.
+// First (column) pass only of the forward transform of `batch` groups of map.n rows; the rows are left in the
+// inter-pass form of the primes' arithmetic for a fused second pass.  Needs a two-pass size.
 ckks_status launch_ntt_fwd_first_pass(ckks_ctx *ctx, uint64_t *data, uint32_t batch, uint32_t bstride,
                                       const LimbMap &map)
 {
     if (!batch || !map.n) return CKKS_OK;
     int s1, s2;
     split_log((int)ctx->log_n, &s1, &s2);
-    CK_REQUIRE(s1 > 0 && use_f64(ctx, map), CKKS_EINVAL, "ntt: first pass alone needs two passes and fp64 primes");
+    CK_REQUIRE(s1 > 0, CKKS_EINVAL, "ntt: first pass alone needs two passes");
+    const bool f = use_f64(ctx, map);
     const double res = (double)batch * map.n * ctx->n;
-    prof_begin(ctx, K_NTT_FWD_COL, 16.0 * res, res * kOpsButterflyF64 * s1 / 2);
-    const hipError_t e = dispatch_col<false, true>(s1, ctx, data, batch, bstride, map);
+    prof_begin(ctx, K_NTT_FWD_COL, 16.0 * res, res * (f ? kOpsButterflyF64 : kOpsButterflyInt) * s1 / 2);
+    const hipError_t e = f ? dispatch_col<false, true>(s1, ctx, data, batch, bstride, map)
+                           : dispatch_col<false, false>(s1, ctx, data, batch, bstride, map);
     prof_end(ctx, K_NTT_FWD_COL);
     if (e != hipSuccess) return set_error(CKKS_EHIP, "ntt launch failed: %s", hipGetErrorString(e));
     return CKKS_OK;
@@ -599,13 +612,34 @@ ckks_status launch_ntt_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, u
                            identity_reduction_bound(ctx, limbs), l_per);
         e = hipGetLastError();
     } else {
-        e = f ? dispatch_col_i64<true>(s1, ctx, m, out, batch, limbs)
-              : dispatch_col_i64<false>(s1, ctx, m, out, batch, limbs);
+        const CoefI64 src{m};
+        e = f ? dispatch_col_i64<true>(s1, ctx, src, out, batch, limbs)
+              : dispatch_col_i64<false>(s1, ctx, src, out, batch, limbs);
     }
     prof_end(ctx, K_NTT_FWD_COL);
     if (e != hipSuccess) return set_error(CKKS_EHIP, "ntt launch failed: %s", hipGetErrorString(e));
     return CKKS_OK;
 }
+
+// Column pass only of the forward NTT of a secret s and, unless e is null, an error polynomial e over primes
+// 0..limbs-1: out [1 or 2][limbs][N] in the inter-pass form of the arithmetic ntt_uses_f64 selects.  Two-pass sizes.
+ckks_status launch_ntt_col_small(ckks_ctx *ctx, const int8_t *s, const int32_t *e, uint64_t *out, uint32_t limbs)
+{
+    int s1, s2;
+    split_log((int)ctx->log_n, &s1, &s2);
+    CK_REQUIRE(s1 > 0 && limbs, CKKS_EINVAL, "ntt: a single-pass size has no column pass");
+    const CoefSmall src{s, e};
+    const uint32_t batch = e ? 2 : 1;
+    prof_begin(ctx, K_NTT_FWD_COL, (double)ctx->n * (e ? 5 : 1) + 8.0 * batch * limbs * ctx->n);
+    const hipError_t err = use_f64(ctx, limb_range(0, limbs))
+                               ? dispatch_col_i64<true>(s1, ctx, src, out, batch, limbs)
+                               : dispatch_col_i64<false>(s1, ctx, src, out, batch, limbs);
+    prof_end(ctx, K_NTT_FWD_COL);
+    if (err != hipSuccess) return set_error(CKKS_EHIP, "ntt launch failed: %s", hipGetErrorString(err));
+    return CKKS_OK;
+}
+
+bool ntt_map_f64(const ckks_ctx *ctx, const LimbMap &map) { return use_f64(ctx, map); }
 
 // Forward NTT of signed coefficient rows m[batch][N] into out[batch][limbs][N]
 // over primes 0..limbs-1 (reduction fused into the first pass).

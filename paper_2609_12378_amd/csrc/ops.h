@@ -79,6 +79,22 @@ ckks_status ks_ip_accumulate(ckks_ctx *ctx, uint32_t level, uint32_t count, cons
                              const uint64_t *const *digs, const uint32_t *g, const uint64_t *const *keys,
                              uint64_t *const *accs, uint32_t n_accs, bool accumulate);
 
+// Row passes with the element-wise work that follows the transform (fused_row.hip): N >= 2^12, either arithmetic.
+bool fused_rows_ok(const ckks_ctx *ctx);
+// rescale of `polys` polynomials c ([polys][l+1][N]) into out ([polys][l][N]) or, out null, of polys / 2 <= 32
+// ciphertexts into outs[r] ([2][l][N]); work: polys (1 + l) N words
+ckks_status fused_rescale(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint32_t l, uint64_t *out,
+                          uint64_t *const *outs, uint64_t *work);
+// the last step of a rotation batch in the integer arithmetic: u [count][2][level+1+n_p][N], cw [count][2][level+1][N]
+// after the column pass
+struct RotArgs;
+ckks_status fused_moddown_int(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, const uint64_t *u, const uint64_t *cw);
+// work: limbs N words, 2 limbs N words
+ckks_status fused_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const uint64_t *c1, const int8_t *s,
+                          uint32_t limbs, uint64_t *work);
+ckks_status fused_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_t *a, const int8_t *s,
+                          const int32_t *e, const uint64_t *m, uint32_t limbs, uint64_t *work);
+
 // ModUp and ModDown conversions in fp64 (modup.hip): N >= 2^12, every prime of the level and of P below 2^50, at most
 // 16 source limbs a conversion (computed once per context: ckks_ctx::f64_level)
 bool f64_level_ok(const ckks_ctx *ctx, uint32_t level);
@@ -203,6 +219,9 @@ ckks_status rotate_each(ckks_ctx *ctx, const uint64_t *cs, size_t stride, uint32
 // rescale of `count` contiguous ciphertexts c ([count][2][l+1][N]) into out ([count][2][l][N]);
 // work: 2 count (1 + l) N words
 ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint32_t l, uint64_t *out,
+                         uint64_t *work);
+// the same into separate outputs outs[r] ([2][l][N]); count <= 32
+ckks_status rescale_each(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint32_t l, uint64_t *const *outs,
                          uint64_t *work);
 
 // matrix-core multiply-accumulate over residues (project_tm.hip): acc[jj] (+)= sum_kappa Q[kappa][jj] x_kappa for

@@ -568,10 +568,10 @@ extern "C" ckks_status ckks_linear_project(ckks_ctx *ctx, const ckks_buf *in, co
             CK_TRY(ks_moddown(ctx, uacc, 2 * jc, level, nullptr, 1, nullptr, rot, ksw));
             CK_TRY(launch_binary(ctx, tot, tot, rot, jc * 2 * L, limb_range(0, L), EW_ADD));
         }
-        for (uint32_t jj = 0; jj < jc; jj++) {
-            CK_TRY(rescale_core(ctx, tot + (size_t)jj * ctw, level, out[j0 + jj].data, rot));
-            out[j0 + jj].scale = in[0].scale;
-        }
+        std::vector<uint64_t *> outs(jc);
+        for (uint32_t jj = 0; jj < jc; jj++) outs[jj] = out[j0 + jj].data;
+        CK_TRY(rescale_each(ctx, tot, jc, level, outs.data(), rot));
+        for (uint32_t jj = 0; jj < jc; jj++) out[j0 + jj].scale = in[0].scale;
     }
     return CKKS_OK;
 }

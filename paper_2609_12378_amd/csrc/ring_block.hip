@@ -585,11 +585,10 @@ ckks_status blk_key_product(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, ui
 // way 30 against 20 us, 96 rows 34 against 31, 768 rows 113 against 154
 bool blk_rows(const ckks_ctx *ctx, size_t rows) { return blk_ring(ctx) && (ctx->log_n < 14 || rows >= 192); }
 
-// the same for one encryption and decryption (two transforms in a row of blocks, one a limb): 3 limbs 121 against 102 us
-// with the encoding and decoding around them, 22 limbs 135 against 164
+// the same for one encryption and decryption (fused_row.hip: two launches)
 bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs)
 {
-    return blk_ring(ctx) && ntt_uses_f64(ctx, limbs) && (ctx->log_n < 14 || limbs >= 12);
+    return blk_ring(ctx) && ntt_uses_f64(ctx, limbs) && ctx->log_n < 14;
 }
 
 // the same for a ModUp (modup.hip: five launches)
