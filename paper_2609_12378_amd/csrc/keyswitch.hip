@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kThreads) void k_conv(const uint64_t *in, uint32_t 
                                                     const ulonglong2 *__restrict__ qhat_inv,
                                                     const ulonglong2 *__restrict__ qhat_mod,
                                                     const ulonglong2 *__restrict__ neg_q,
-                                                    const ModQ *__restrict__ mods, uint32_t log_n)
+                                                    const ModQ *__restrict__ mods, uint32_t log_n, uint32_t t_per)
 {
     __shared__ uint64_t s_mod[NS_MAX * kMaxPrimes];
     __shared__ uint64_t s_neg[kMaxPrimes];
@@ -79,7 +79,9 @@ __global__ __launch_bounds__(kThreads) void k_conv(const uint64_t *in, uint32_t 
         }
     }
     uint64_t *dst = out + ((size_t)poly * out_stride << log_n) + col;
-    for (int t = 0; t < nt; t++) {
+    // blockIdx.z: this block's group of t_per targets (each group forms the digits again)
+    const int t0 = (int)(blockIdx.z * t_per), t1 = min(nt, t0 + (int)t_per);
+    for (int t = t0; t < t1; t++) {
         const ModQ mt = s_tm[t];
         acc128 acc{0, 0};
         mac(acc, neg, s_neg[t]);
@@ -545,12 +547,15 @@ __global__ __launch_bounds__(64) void k_ks_finish8(RotArgs ra, const uint64_t *_
     }
 }
 
-// k_ks_finish8 for seed-expanded keys: the inner products (with their Philox blocks) first, every position's
-// loads issued before the transforms, and c0's gathers at the start.  (With stored keys the same order, 160 VGPRs
-// and 3 waves per SIMD, measured 5% slower than k_ks_finish8's one position at a time after the transforms, 88
-// VGPRs and 5 waves: that kernel streams ~5 TB/s of keys, converted rows and outputs.)
-template <int ND>
-__global__ __launch_bounds__(64) void k_ks_finish8_seeded(RotArgs ra, const uint64_t *__restrict__ cw, uint32_t nd,
+// k_ks_finish8 with the inner products first, every position's loads issued before the transforms, and the addends'
+// gathers at the start: for seed-expanded keys (whose Philox blocks the loads then overlap), and with stored keys for
+// batches of at most kWideWaves waves, which cannot hide one position's loads behind another wave's work (one
+// rotation at 13 limbs of N = 2^16, 1664 waves: 26 -> 15 us).  Larger batches with stored keys take k_ks_finish8: this
+// order needs 160 VGPRs, 3 waves per SIMD, and measured 5% slower there than one position at a time after the
+// transforms, 88 VGPRs and 5 waves, which streams ~5 TB/s of keys, converted rows and outputs.
+constexpr size_t kWideWaves = 3072;
+template <bool SEEDED, int ND>
+__global__ __launch_bounds__(64) void k_ks_finish8_wide(RotArgs ra, const uint64_t *__restrict__ cw, uint32_t nd,
                                                           uint32_t ext, uint32_t L, uint32_t key_rows,
                                                           const ModQ *__restrict__ mods,
                                                           const double *__restrict__ twf,
@@ -568,17 +573,18 @@ __global__ __launch_bounds__(64) void k_ks_finish8_seeded(RotArgs ra, const uint
     const uint32_t h = blk * 2 + sub;
     nttc::stage_twiddles8(tws[sub], twf + ((size_t)i << log_n), (1u << (log_n - 8)) + h, t, 32);
     const uint32_t g = ra.g[r];
-    const uint64_t *c0 = ra.c0[r] + ((size_t)i << log_n);
+    const uint64_t *c0 = ra.c0[r] + ((size_t)i << log_n), *add1 = ra.add1[r];
     uint32_t pos[kE8], sc[kE8];
-    uint64_t c0v[kE8];
+    uint64_t c0v[kE8], c1v[SEEDED ? 1 : kE8];  // no second addend with seeded keys
 #pragma unroll
     for (int e = 0; e < kE8; e++) {
         pos[e] = h * 256 + nttc::u8<0>(t, e);
         sc[e] = auto_index(pos[e], g, log_n);
         c0v[e] = c0[sc[e]];
+        if constexpr (!SEEDED) c1v[e] = add1 ? add1[((size_t)i << log_n) + pos[e]] : 0;
     }
     double u0[kE8], u1[kE8];
-    key_ip8<true, ND>(ra, r, nd, ext, i, i, key_rows, log_n, mods[i].q, ar, pos, sc, u0, u1);
+    key_ip8<SEEDED, ND>(ra, r, nd, ext, i, i, key_rows, log_n, mods[i].q, ar, pos, sc, u0, u1);
     __syncthreads();
     const size_t row = ((size_t)i << log_n) + (size_t)h * 256;
     double v[2][kE8];
@@ -598,7 +604,8 @@ __global__ __launch_bounds__(64) void k_ks_finish8_seeded(RotArgs ra, const uint
 #pragma unroll
     for (int e = 0; e < kE8; e++) {
         const double r0 = ar.mul(u0[e] - v[0][e], pi) + nttc::Ar<true>::from_u64(c0v[e]);
-        const double r1 = ar.mul(u1[e] - v[1][e], pi);
+        double r1 = ar.mul(u1[e] - v[1][e], pi);
+        if constexpr (!SEEDED) r1 += nttc::Ar<true>::from_u64(c1v[e]);
         nttc::st_stream(out + ((size_t)i << log_n) + pos[e], ar.to_canon(r0));
         nttc::st_stream(out + (((size_t)L + i) << log_n) + pos[e], ar.to_canon(r1));
     }
@@ -638,7 +645,8 @@ ckks_status launch_conv(ckks_ctx *ctx, const ConvDev *cd, const uint64_t *in, ui
     // 4096 waves (4 per SIMD); with fewer polynomials one coefficient per thread, and the target limbs split over
     // blockIdx.z until the grid has that many waves
     const size_t waves1 = (size_t)((ctx->n + 63) / 64) * polys;
-    const bool two = ctx->n % (2 * kThreads) == 0 && waves1 / 2 >= 4096;
+    const bool f64 = cd->f64 && !ctx->int_only && a.ns <= 16;
+    const bool two = f64 && ctx->n % (2 * kThreads) == 0 && waves1 / 2 >= 4096;
     uint32_t groups = 1;
     const uint32_t ntg = a.nt > 0 ? (uint32_t)a.nt : 1u;
     if (!two && waves1 < 4096) groups = (uint32_t)std::min<size_t>(ntg, (4096 + waves1 - 1) / waves1);
@@ -665,23 +673,23 @@ ckks_status launch_conv(ckks_ctx *ctx, const ConvDev *cd, const uint64_t *in, ui
             hipLaunchKernelGGL((k_conv_f64<NSM, 1>), grid1, block, 0, ctx->stream, in, in_stride, out, out_stride,  \
                                split, skip, a, cd->d_qhat_inv_f, cd->d_qhat_mod_f, ctx->d_mod, ctx->log_n, t_per); \
     } while (0)
-    if (cd->f64 && !ctx->int_only && a.ns <= 16) {
+    if (f64) {
         if (a.ns <= 8)
             CK_CONVF(8);
         else
             CK_CONVF(16);
     } else if (a.ns <= 4)
-        hipLaunchKernelGGL(k_conv<4>, grid, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
-                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n);
+        hipLaunchKernelGGL(k_conv<4>, grid1, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
+                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n, t_per);
     else if (a.ns <= 8)
-        hipLaunchKernelGGL(k_conv<8>, grid, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
-                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n);
+        hipLaunchKernelGGL(k_conv<8>, grid1, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
+                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n, t_per);
     else if (a.ns <= 16)
-        hipLaunchKernelGGL(k_conv<16>, grid, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
-                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n);
+        hipLaunchKernelGGL(k_conv<16>, grid1, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
+                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n, t_per);
     else if (a.ns <= 32)
-        hipLaunchKernelGGL(k_conv<32>, grid, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
-                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n);
+        hipLaunchKernelGGL(k_conv<32>, grid1, block, 0, ctx->stream, in, in_stride, out, out_stride, split, skip, a,
+                           cd->d_qhat_inv, cd->d_qhat_mod, cd->d_neg_q, ctx->d_mod, ctx->log_n, t_per);
     else {
         prof_end(ctx, K_CONV);
         return set_error(CKKS_EUNSUPPORTED, "basis conversion from %d limbs (at most 32)", a.ns);
@@ -822,10 +830,12 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
         prof_begin(ctx, K_MODDOWN, 8.0 * res * (2.0 + 2.0 * nd + 2.0),
                    res * (2 * (4 * kOpsButterflyF64 + 4 * (kOpsButterflyF64 - 3)) / 2 + nd * 2 * 10.0 + 40.0));
 #define CK_FIN(SD, ND)                                                                                             \
-    hipLaunchKernelGGL((k_ks_finish8_seeded<ND>), dim3(count * L * bpl), dim3(64), 0, ctx->stream, ra, cw, nd, ext, \
+    hipLaunchKernelGGL((k_ks_finish8_wide<SD, ND>), dim3(count * L * bpl), dim3(64), 0, ctx->stream, ra, cw, nd, ext, \
                        L, kp, ctx->d_mod, ctx->d_twf, ctx->d_pinv, ctx->log_n, bpl)
         if (seeded)
             CK_ND_DISPATCH(nd, CK_FIN, true);
+        else if ((size_t)count * L * bpl <= kWideWaves)
+            CK_ND_DISPATCH(nd, CK_FIN, false);
         else
             hipLaunchKernelGGL(k_ks_finish8, dim3(count * L * bpl), dim3(64), 0, ctx->stream, ra, cw, nd, ext, L, kp,
                                ctx->d_mod, ctx->d_twf, ctx->d_pinv, ctx->log_n, bpl);
