@@ -67,13 +67,69 @@ __device__ __forceinline__ void round_out(int64_t *m, size_t base, uint32_t k, u
     m[base + k + M] = (int64_t)round(c * v.y);
 }
 
+// Where a transform's results go: kept complex (mode 0), rounded to coefficients (mode 1), or, decoding, as slots
+// (mode 2: slot j = conj(Y[s(j)]), j the slot whose FFT position is the bit reversal of the result's index).
+struct FftOut {
+    int mode;
+    const double2 *twist;
+    double c;
+    int64_t *m;
+    double *re, *im;
+    const uint32_t *slot_of_pos;
+};
+__device__ __forceinline__ void fft_out(const FftOut &o, uint32_t p, uint32_t k, uint32_t logm, double2 y)
+{
+    const uint32_t M = 1u << logm;
+    if (o.mode == 1) {
+        round_out(o.m, (size_t)p * 2 * M, k, M, y, o.twist[k], o.c);
+    } else {
+        const uint32_t j = o.slot_of_pos[__brev(k) >> (32 - logm)];
+        o.re[j] = y.x;
+        o.im[j] = -y.y;
+    }
+}
+
+// Decoding: the FFT's input at natural index i is the centred CRT lift of limbs 0 (and 1) of the coefficient form,
+// scaled by 1/Delta, twisted by zeta^-i and conjugated: the inverse-direction FFT of conj((m_i + i m_{i+M}) zeta^i)
+// is the conjugate of the decoding sum.
+struct DecodeIn {
+    const uint64_t *coef;   // [limbs][N]
+    uint32_t limbs;         // 1 or 2
+    uint64_t q0, q1, q0inv, q0inv_s;
+    double inv_scale;
+    const double2 *twist;
+};
+__device__ __forceinline__ double2 decode_value(const DecodeIn &d, uint32_t i, uint32_t logm)
+{
+    const uint32_t M = 1u << logm, n = 2 * M;
+    double v[2];
+    for (int h = 0; h < 2; h++) {
+        const uint32_t idx = i + h * M;
+        const uint64_t x0 = d.coef[idx];
+        double val;
+        if (d.limbs == 1) {
+            val = x0 > d.q0 / 2 ? -(double)(d.q0 - x0) : (double)x0;
+        } else {
+            const uint64_t x1 = d.coef[n + idx];
+            const uint64_t y = shoup(submod(x1, csub(x0, d.q1), d.q1), d.q0inv, d.q0inv_s, d.q1);
+            const unsigned __int128 Q = (unsigned __int128)d.q0 * d.q1;
+            const unsigned __int128 x = (unsigned __int128)d.q0 * y + x0;  // in [0, q0 q1)
+            const bool neg = x > Q / 2;
+            const unsigned __int128 mag = neg ? Q - x : x;
+            const double dv = (double)(uint64_t)(mag >> 64) * 18446744073709551616.0 + (double)(uint64_t)mag;
+            val = neg ? -dv : dv;
+        }
+        v[h] = val * d.inv_scale;
+    }
+    return cmul(d.twist[i], make_double2(v[0], -v[1]));
+}
+
 // Pass A: stages len = 2 .. 2^logb on contiguous blocks of 2^logb points.
 // Input: from `a` (bit-reversed order), or, when `gather` is set, straight from
 // the slot source through slot_of_pos (FFT position -> slot index).
 // mode 0: write complex back; mode 1: final pass, twist/round into m.
 __global__ __launch_bounds__(kThreads) void k_fft_a(double2 *a, const double2 *__restrict__ w, uint32_t logm,
-                                                     uint32_t logb, int mode, const double2 *__restrict__ twist,
-                                                     double c, int64_t *m, int gather, SlotSource ss,
+                                                     uint32_t logb, FftOut o, int gather, SlotSource ss,
                                                      const uint32_t *__restrict__ slot_of_pos)
 {
     extern __shared__ double2 sh[];
@@ -101,10 +157,10 @@ __global__ __launch_bounds__(kThreads) void k_fft_a(double2 *a, const double2 *_
         }
         __syncthreads();
     }
-    if (mode == 0) {
+    if (o.mode == 0) {
         for (uint32_t x = threadIdx.x; x < B; x += kThreads) src[x] = sh[x];
     } else {
-        for (uint32_t x = threadIdx.x; x < B; x += kThreads) round_out(m, (size_t)p * 2 * M, x, M, sh[x], twist[x], c);
+        for (uint32_t x = threadIdx.x; x < B; x += kThreads) fft_out(o, p, x, logm, sh[x]);
     }
 }
 
@@ -164,8 +220,7 @@ __device__ __forceinline__ void fft8_transpose(double2 (&v)[8], double2 *sh, uin
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_fft_a8(double2 *a, const double2 *__restrict__ wc, uint32_t logm, int mode,
-                                                const double2 *__restrict__ twist, double c, int64_t *m,
+__global__ __launch_bounds__(256) void k_fft_a8(double2 *a, const double2 *__restrict__ wc, uint32_t logm, FftOut o,
                                                 SlotSource ss)
 {
     __shared__ double2 sh[2048];
@@ -199,16 +254,123 @@ __global__ __launch_bounds__(256) void k_fft_a8(double2 *a, const double2 *__res
     fft8_transpose<3, 4, true>(v, sh, t);
     fft8_stage<4, 10>(v, wc, t);
     fft8_stage<4, 11>(v, wc, t);
-    if (mode == 0) {
+    if (o.mode == 0) {
         double2 *dst = a + (size_t)p * M + ((size_t)blk << 11);
 #pragma unroll
         for (int r = 0; r < 8; r++) dst[posA<4>(t, r)] = v[r];
     } else {
 #pragma unroll
-        for (int r = 0; r < 8; r++) {
-            const uint32_t x = posA<4>(t, r);
-            round_out(m, (size_t)p * 2 * M, x, M, v[r], twist[x], c);
+        for (int r = 0; r < 8; r++) fft_out(o, p, posA<4>(t, r), logm, v[r]);
+    }
+}
+
+// One slot vector (a client's encode and decode, N >= 2^12): the stages split at 2^8 instead of 2^11.  One vector is at
+// most 512 KB, so its passes are bounded by how few CUs they reach and by the serial chain on each: 2048-point blocks
+// use 16 CUs at N = 2^16 and one at 2^12.  Here 256-point blocks are one wave each (N/512 of them), four points a thread
+// and two stages per LDS exchange; then columns of 2^LC points at stride 256.  Every butterfly and twiddle is the one
+// of k_fft_a and k_fft_b, so the results are the same bits.  The first pass reads explicit slots by FFT position, or
+// (DEC) forms a decode's lifted coefficients; the second rounds, or writes the slots.
+// Measured: @FIG@
+__device__ __forceinline__ uint32_t pos4(int g, uint32_t t, int r)
+{
+    return ((t >> (2 * g)) << (2 * g + 2)) | ((uint32_t)r << (2 * g)) | (t & ((1u << (2 * g)) - 1u));
+}
+// LDS position: both two-bit groups that the exchanges walk spread over the 16 lanes' banks
+__device__ __forceinline__ uint32_t swz4(uint32_t x) { return x ^ (((x >> 4) & 3u) * 5u); }
+
+__device__ __forceinline__ void bfly(double2 &u, double2 &v, double2 w)
+{
+    const double2 t = cmul(w, v), u0 = u;
+    u = make_double2(u0.x + t.x, u0.y + t.y);
+    v = make_double2(u0.x - t.x, u0.y - t.y);
+}
+
+template <bool DEC>
+__global__ __launch_bounds__(64) void k_fft_one_a(double2 *a, const double2 *__restrict__ wc, uint32_t logm,
+                                                  SlotSource ss, DecodeIn dec,
+                                                  const uint32_t *__restrict__ slot_of_pos)
+{
+    __shared__ double2 sh[256];
+    const uint32_t M = 1u << logm, base = blockIdx.x << 8, t = threadIdx.x;
+    double2 w[4][3];  // per exchange: the first stage's twiddle, the second's two
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        const uint32_t k = t & ((1u << (2 * g)) - 1u), h1 = 1u << (2 * g), h2 = 2u << (2 * g);
+        w[g][0] = wc[h1 + k];
+        w[g][1] = wc[h2 + k];
+        w[g][2] = wc[h2 + h1 + k];
+    }
+    double2 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const uint32_t x = base + pos4(0, t, r);
+        v[r] = DEC ? decode_value(dec, __brev(x) >> (32 - logm), logm) : slot_value(ss, 0, slot_of_pos[x], M);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        if (g) {
+#pragma unroll
+            for (int r = 0; r < 4; r++) sh[swz4(pos4(g - 1, t, r))] = v[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] = sh[swz4(pos4(g, t, r))];
+            __syncthreads();
         }
+        bfly(v[0], v[1], w[g][0]);
+        bfly(v[2], v[3], w[g][0]);
+        bfly(v[0], v[2], w[g][1]);
+        bfly(v[1], v[3], w[g][2]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++) a[base + pos4(3, t, r)] = v[r];
+}
+
+// columns per block: 64 B to 512 B of each row, at least one wave
+constexpr uint32_t one_cols(int lc) { return lc >= 6 ? 4u : 256u >> lc; }
+template <int LC>
+__global__ __launch_bounds__(128) void k_fft_one_b(const double2 *a, const double2 *__restrict__ fw, uint32_t logm,
+                                                   FftOut o)
+{
+    constexpr uint32_t kCols = one_cols(LC), C = 1u << LC;
+    __shared__ double2 sh[C * kCols];
+    const uint32_t c = threadIdx.x % kCols, t = threadIdx.x / kCols, col = blockIdx.x * kCols + c;
+    double2 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = a[(pos4(0, t, r) << 8) + col];
+    // twiddle of the stage with half-length h (in rows) at row x: exponent ((x mod h) 256 + col) M / (512 h)
+    auto tw = [&](uint32_t x, int lh) { return fw[((((x & ((1u << lh) - 1u)) << 8) + col) << (logm - 9 - lh))]; };
+    constexpr int G = LC / 2;
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        if (g) {
+#pragma unroll
+            for (int r = 0; r < 4; r++) sh[pos4(g - 1, t, r) * kCols + c] = v[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] = sh[pos4(g, t, r) * kCols + c];
+            __syncthreads();
+        }
+        const double2 w0 = tw(pos4(g, t, 0), 2 * g);
+        bfly(v[0], v[1], w0);
+        bfly(v[2], v[3], w0);
+        bfly(v[0], v[2], tw(pos4(g, t, 0), 2 * g + 1));
+        bfly(v[1], v[3], tw(pos4(g, t, 1), 2 * g + 1));
+    }
+    if constexpr (LC % 2 == 1) {
+        // the last stage alone: rows 2 t + (r & 1) and those half a column on
+#pragma unroll
+        for (int r = 0; r < 4; r++) sh[pos4(G - 1, t, r) * kCols + c] = v[r];
+        __syncthreads();
+        auto row = [&](int r) { return ((uint32_t)(r >> 1) << (LC - 1)) | (t << 1) | (uint32_t)(r & 1); };
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = sh[row(r) * kCols + c];
+        bfly(v[0], v[2], tw(row(0), LC - 1));
+        bfly(v[1], v[3], tw(row(1), LC - 1));
+#pragma unroll
+        for (int r = 0; r < 4; r++) fft_out(o, 0, (row(r) << 8) + col, logm, v[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++) fft_out(o, 0, (pos4(G - 1, t, r) << 8) + col, logm, v[r]);
     }
 }
 
@@ -340,8 +502,7 @@ __global__ __launch_bounds__(kThreads) void k_feat_of_pos(uint32_t *out, const u
 // Pass B: stages len = 2^(logb+1) .. M; thread owns column c (points h*B + c, h < 2^HB).
 template <int HB>
 __global__ __launch_bounds__(kThreads) void k_fft_b(double2 *a, const double2 *__restrict__ w, uint32_t logm,
-                                                     uint32_t logb, int mode, const double2 *__restrict__ twist,
-                                                     double c, int64_t *m)
+                                                     uint32_t logb, FftOut o)
 {
     const uint32_t M = 1u << logm, B = 1u << logb;
     const uint32_t cols_blocks = B / kThreads;
@@ -365,15 +526,12 @@ __global__ __launch_bounds__(kThreads) void k_fft_b(double2 *a, const double2 *_
             x[h + half] = make_double2(u.x - t.x, u.y - t.y);
         }
     }
-    if (mode == 0) {
+    if (o.mode == 0) {
 #pragma unroll
         for (int h = 0; h < (1 << HB); h++) src[(size_t)h * B + col] = x[h];
     } else {
 #pragma unroll
-        for (int h = 0; h < (1 << HB); h++) {
-            const uint32_t k = (uint32_t)h * B + col;
-            round_out(m, (size_t)p * 2 * M, k, M, x[h], twist[k], c);
-        }
+        for (int h = 0; h < (1 << HB); h++) fft_out(o, p, (uint32_t)h * B + col, logm, x[h]);
     }
 }
 
@@ -396,45 +554,16 @@ __global__ __launch_bounds__(kThreads) void k_to_rns(uint64_t *out, const int64_
     }
 }
 
-// Decode, step 1: centred CRT lift of limbs 0 (and 1) of the coefficient form,
-// scaled by 1/Delta, twisted by zeta^-i and conjugated, into bit-reversed FFT
-// order: the inverse-direction FFT of conj((m_i + i m_{i+M}) zeta^i) is the
-// conjugate of the decoding sum.
-__global__ __launch_bounds__(kThreads) void k_decode_in(double2 *a, const uint64_t *coef, uint32_t limbs,
-                                                         uint32_t log_n, const ModQ *__restrict__ mods,
-                                                         const double2 *__restrict__ twist, double inv_scale,
-                                                         uint64_t q0inv, uint64_t q0inv_s)
+// Decode, step 1 (rings below 2^12): the FFT's input in bit-reversed order
+__global__ __launch_bounds__(kThreads) void k_decode_in(double2 *a, DecodeIn d, uint32_t logm)
 {
-    const uint32_t n = 1u << log_n, M = n / 2, logm = log_n - 1;
     const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-    if (i >= M) return;
-    const uint64_t q0 = mods[0].q;
-    double v[2];
-    for (int h = 0; h < 2; h++) {
-        const uint32_t idx = i + h * M;
-        const uint64_t x0 = coef[idx];
-        double val;
-        if (limbs == 1) {
-            val = x0 > q0 / 2 ? -(double)(q0 - x0) : (double)x0;
-        } else {
-            const uint64_t q1 = mods[1].q;
-            const uint64_t x1 = coef[n + idx];
-            const uint64_t d = shoup(submod(x1, csub(x0, q1), q1), q0inv, q0inv_s, q1);
-            const unsigned __int128 Q = (unsigned __int128)q0 * q1;
-            const unsigned __int128 x = (unsigned __int128)q0 * d + x0;  // in [0, q0 q1)
-            const bool neg = x > Q / 2;
-            const unsigned __int128 mag = neg ? Q - x : x;
-            const double dv = (double)(uint64_t)(mag >> 64) * 18446744073709551616.0 + (double)(uint64_t)mag;
-            val = neg ? -dv : dv;
-        }
-        v[h] = val * inv_scale;
-    }
-    a[__brev(i) >> (32 - logm)] = cmul(twist[i], make_double2(v[0], -v[1]));
+    if (i < (1u << logm)) a[__brev(i) >> (32 - logm)] = decode_value(d, i, logm);
 }
 
-// Decode, step 3: slot j = conj(Y[s(j)]), s(j) the natural index whose bit reversal is pos[j]
+// Decode, step 3 (rings below 2^12): slot j = conj(Y[s(j)]), s(j) the natural index whose bit reversal is pos[j]
 __global__ __launch_bounds__(kThreads) void k_decode_out(const double2 *y, const uint32_t *__restrict__ pos,
-                                                          uint32_t logm, double *re, double *im)
+                                                         uint32_t logm, double *re, double *im)
 {
     const uint32_t M = 1u << logm;
     const uint32_t j = blockIdx.x * kThreads + threadIdx.x;
@@ -448,8 +577,40 @@ __global__ __launch_bounds__(kThreads) void k_decode_out(const double2 *y, const
 
 size_t enc_work_bytes(const ckks_ctx *ctx, uint32_t batch) { return (size_t)batch * (ctx->n / 2) * sizeof(double2); }
 
-ckks_status fft_passes(ckks_ctx *ctx, double2 *work, uint32_t batch, int mode, double c, int64_t *m,
-                       const SlotSource *gather, bool pass_a_only = false)
+// one vector of explicit slots (src) or a decode's coefficients (dec), N >= 2^12
+ckks_status fft_one(ckks_ctx *ctx, double2 *work, const FftOut &o, const SlotSource *src, const DecodeIn *dec)
+{
+    const uint32_t logm = ctx->log_n - 1, M = 1u << logm;
+    prof_begin(ctx, K_FFT_A, 32.0 * M);
+    if (dec)
+        hipLaunchKernelGGL(k_fft_one_a<true>, dim3(M >> 8), dim3(64), 0, ctx->stream, work, ctx->d_fft_wc, logm,
+                           SlotSource{}, *dec, ctx->d_pos_slot);
+    else
+        hipLaunchKernelGGL(k_fft_one_a<false>, dim3(M >> 8), dim3(64), 0, ctx->stream, work, ctx->d_fft_wc, logm, *src,
+                           DecodeIn{}, ctx->d_pos_slot);
+    prof_end(ctx, K_FFT_A);
+    prof_begin(ctx, K_FFT_B, 32.0 * M);
+#define CK_ONE(LC)                                                                                                  \
+    hipLaunchKernelGGL(k_fft_one_b<LC>, dim3(256 / one_cols(LC)), dim3((one_cols(LC) << LC) / 4), 0, ctx->stream,    \
+                       work, ctx->d_fft_w, logm, o)
+    switch (logm - 8) {
+    case 3: CK_ONE(3); break;
+    case 4: CK_ONE(4); break;
+    case 5: CK_ONE(5); break;
+    case 6: CK_ONE(6); break;
+    case 7: CK_ONE(7); break;
+    default: prof_end(ctx, K_FFT_B); return set_error(CKKS_EUNSUPPORTED, "fft: unsupported size");
+    }
+#undef CK_ONE
+    prof_end(ctx, K_FFT_B);
+    HIP_TRY(hipGetLastError());
+    return CKKS_OK;
+}
+
+// the transforms of `batch` vectors: pass A from the slot source `gather` or the work array itself, pass B (or pass A,
+// if it is the only one) to `o`
+ckks_status fft_passes(ckks_ctx *ctx, double2 *work, uint32_t batch, const FftOut &o, const SlotSource *gather,
+                       bool pass_a_only = false)
 {
     const uint32_t logm = ctx->log_n - 1, M = 1u << logm;
     const uint32_t logb = logm < (uint32_t)kLogBA ? logm : (uint32_t)kLogBA;
@@ -460,30 +621,26 @@ ckks_status fft_passes(ckks_ctx *ctx, double2 *work, uint32_t batch, int mode, d
     const double bytes_a = gather ? batch * (16.0 * M + (gather->W ? 8.0 * gather->feats
                                                                     : (gather->im ? 16.0 : 8.0) * M))
                                   : bytes;
-    SlotSource none;
+    const SlotSource src = gather ? *gather : SlotSource{};
+    FftOut oa = o;
+    if (!single) oa.mode = 0;
+    const dim3 grid_a(batch * (M >> logb));
     prof_begin(ctx, K_FFT_A, bytes_a);
-    if (gather && gather->Wd && logb == (uint32_t)kLogBA) {
-        hipLaunchKernelGGL(k_fft_a8, dim3(batch * (M >> logb)), dim3(256), 0, ctx->stream, work, ctx->d_fft_wc, logm,
-                           single ? mode : 0, ctx->d_fft_twist, c, m, *gather);
-    } else {
-        hipLaunchKernelGGL(k_fft_a, dim3(batch * (M >> logb)), dim3(kThreads), B * sizeof(double2), ctx->stream,
-                           work, ctx->d_fft_w, logm, logb, single ? mode : 0, ctx->d_fft_twist, c, m, gather ? 1 : 0,
-                           gather ? *gather : none, ctx->d_pos_slot);
-    }
+    if (gather && gather->Wd && logb == (uint32_t)kLogBA)
+        hipLaunchKernelGGL(k_fft_a8, grid_a, dim3(256), 0, ctx->stream, work, ctx->d_fft_wc, logm, oa, src);
+    else
+        hipLaunchKernelGGL(k_fft_a, grid_a, dim3(kThreads), B * sizeof(double2), ctx->stream, work, ctx->d_fft_w, logm,
+                           logb, oa, gather ? 1 : 0, src, ctx->d_pos_slot);
     prof_end(ctx, K_FFT_A);
     if (!single && !pass_a_only) {
         const uint32_t hb = logm - logb;
         const dim3 grid(batch * (B / kThreads));
         prof_begin(ctx, K_FFT_B, bytes);
         switch (hb) {
-        case 1: hipLaunchKernelGGL(k_fft_b<1>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb,
-                                   mode, ctx->d_fft_twist, c, m); break;
-        case 2: hipLaunchKernelGGL(k_fft_b<2>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb,
-                                   mode, ctx->d_fft_twist, c, m); break;
-        case 3: hipLaunchKernelGGL(k_fft_b<3>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb,
-                                   mode, ctx->d_fft_twist, c, m); break;
-        case 4: hipLaunchKernelGGL(k_fft_b<4>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb,
-                                   mode, ctx->d_fft_twist, c, m); break;
+        case 1: hipLaunchKernelGGL(k_fft_b<1>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
+        case 2: hipLaunchKernelGGL(k_fft_b<2>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
+        case 3: hipLaunchKernelGGL(k_fft_b<3>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
+        case 4: hipLaunchKernelGGL(k_fft_b<4>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
         default: prof_end(ctx, K_FFT_B); return set_error(CKKS_EUNSUPPORTED, "fft: unsupported size");
         }
         prof_end(ctx, K_FFT_B);
@@ -496,7 +653,13 @@ ckks_status enc_coeffs(ckks_ctx *ctx, const SlotSource &src, uint32_t batch, dou
                        int64_t *m_out)
 {
     if (!batch) return CKKS_OK;
-    return fft_passes(ctx, work, batch, 1, scale * (2.0 / (double)ctx->n), m_out, &src);
+    FftOut o{};
+    o.mode = 1;
+    o.twist = ctx->d_fft_twist;
+    o.c = scale * (2.0 / (double)ctx->n);
+    o.m = m_out;
+    if (batch == 1 && !src.W && ctx->log_n >= 12) return fft_one(ctx, work, o, &src, nullptr);
+    return fft_passes(ctx, work, batch, o, &src);
 }
 
 bool enc_fused_ok(const ckks_ctx *ctx, uint32_t limbs) { return ctx->log_n == 16 && ntt_uses_f64(ctx, limbs); }
@@ -507,7 +670,7 @@ ckks_status enc_ntt_first_pass(ckks_ctx *ctx, const SlotSource &src, uint32_t ba
     if (!batch) return CKKS_OK;
     CK_REQUIRE(enc_fused_ok(ctx, limbs), CKKS_EINVAL, "encode: the fused first pass needs N = 2^16 and fp64 primes");
     const double c = scale * (2.0 / (double)ctx->n);
-    CK_TRY(fft_passes(ctx, work, batch, 0, c, nullptr, &src, true));
+    CK_TRY(fft_passes(ctx, work, batch, FftOut{}, &src, true));
     // pass B's work array once, the limbs' first-pass rows
     const double res = (double)batch * limbs * ctx->n;
     prof_begin(ctx, K_NTT_FWD_COL, batch * 8.0 * ctx->n * (1 + limbs),
@@ -556,13 +719,30 @@ ckks_status dec_slots(ckks_ctx *ctx, const uint64_t *coef, uint32_t limbs, doubl
         q0inv = r;
         q0inv_s = (uint64_t)(((unsigned __int128)r << 64) / q1);
     }
+    DecodeIn d{};
+    d.coef = coef;
+    d.limbs = limbs > 1 ? 2u : 1u;
+    d.q0 = ctx->primes[0];
+    d.q1 = limbs > 1 ? ctx->primes[1] : 0;
+    d.q0inv = q0inv;
+    d.q0inv_s = q0inv_s;
+    d.inv_scale = 1.0 / scale;
+    d.twist = ctx->d_fft_twist;
+    const uint32_t logm = ctx->log_n - 1;
+    if (ctx->log_n >= 12) {
+        // the lift in the first pass, the slots from the last
+        FftOut o{};
+        o.mode = 2;
+        o.re = re;
+        o.im = im;
+        o.slot_of_pos = ctx->d_pos_slot;
+        return fft_one(ctx, work, o, nullptr, &d);
+    }
     const dim3 grid((M + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(k_decode_in, grid, dim3(kThreads), 0, ctx->stream, work, coef, limbs > 1 ? 2u : 1u,
-                       ctx->log_n, ctx->d_mod, ctx->d_fft_twist, 1.0 / scale, q0inv, q0inv_s);
+    hipLaunchKernelGGL(k_decode_in, grid, dim3(kThreads), 0, ctx->stream, work, d, logm);
     HIP_TRY(hipGetLastError());
-    CK_TRY(fft_passes(ctx, work, 1, 0, 0.0, nullptr, nullptr));
-    hipLaunchKernelGGL(k_decode_out, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_slot_pos, ctx->log_n - 1, re,
-                       im);
+    CK_TRY(fft_passes(ctx, work, 1, FftOut{}, nullptr));
+    hipLaunchKernelGGL(k_decode_out, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_slot_pos, logm, re, im);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
