@@ -226,11 +226,13 @@ __global__ __launch_bounds__(256) void ntt_col_from_i64(Src m, uint64_t *out, ui
 // adjacent columns (consecutive lanes take consecutive columns, so every load
 // and store moves 128-byte segments).  The twiddles of limb l+1 (Psi[1..255],
 // shared by all columns) are staged into the idle half of a double-buffered LDS
-// table while limb l is transformed.
-__global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restrict__ m, uint64_t *out,
-                                                         uint32_t limbs, const ModQ *mods, const double *twf,
-                                                         uint32_t log_n, uint32_t blocks_per_row, int64_t small,
-                                                         uint32_t l_per)
+// table while limb l is transformed.  The secret and error polynomials of one
+// encryption (two of 13 limbs) take this kernel too: 13 us in
+// ntt_col_from_i64, 11 us here.
+template <typename Src>
+__global__ __launch_bounds__(512) void ntt_col8_from_i64(Src m, uint64_t *out, uint32_t limbs, const ModQ *mods,
+                                                         const double *twf, uint32_t log_n, uint32_t blocks_per_row,
+                                                         int64_t small, uint32_t l_per)
 {
     using nttc::kE8;
     __shared__ double tws[2][256];
@@ -239,10 +241,9 @@ __global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restri
     const uint32_t n2 = 1u << (log_n - 8);
     const uint32_t col = threadIdx.x & 15, t = threadIdx.x >> 4;
     const size_t coff = (size_t)blk * 16 + col;
-    const int64_t *src = m + ((size_t)b << log_n) + coff;
     int64_t v[kE8];
 #pragma unroll
-    for (int k = 0; k < kE8; k++) v[k] = src[(size_t)nttc::u8<0>(t, k) * n2];
+    for (int k = 0; k < kE8; k++) v[k] = m.at(b, log_n, coff + (size_t)nttc::u8<0>(t, k) * n2);
     double vd[kE8];
     bool big = false, wide = false;
 #pragma unroll
@@ -268,11 +269,11 @@ __global__ __launch_bounds__(512) void ntt_col8_from_i64(const int64_t *__restri
         if (!reduce) {
 #pragma unroll
             for (int k = 0; k < kE8; k++) x[k] = vd[k];
-        } else if (!big) {
+        } else if (!Src::kWide || !big) {
 #pragma unroll
             for (int k = 0; k < kE8; k++) x[k] = ar.red(vd[k]);
-        } else {
-            auto sg = (const __attribute__((address_space(1))) int64_t *)src;
+        } else if constexpr (Src::kWide) {
+            auto sg = (const __attribute__((address_space(1))) int64_t *)(m.m + ((size_t)b << log_n) + coff);
             asm volatile("" : "+v"(sg));
 #pragma unroll
             for (int k = 0; k < kE8; k++) x[k] = ar.from_i64(sg[(size_t)nttc::u8<0>(t, k) * n2], md);
@@ -437,6 +438,17 @@ hipError_t launch_col_i64(ckks_ctx *ctx, const Src &m, uint64_t *out, uint32_t b
     return hipGetLastError();
 }
 
+template <typename Src>
+hipError_t launch_col8_i64(ckks_ctx *ctx, const Src &m, uint64_t *out, uint32_t batch, uint32_t limbs)
+{
+    const uint32_t bpr = (ctx->n >> 8) / 16;
+    const uint32_t l_per = limbs_per_block(batch * bpr, limbs, 256);
+    hipLaunchKernelGGL(ntt_col8_from_i64<Src>, dim3(batch * bpr, (limbs + l_per - 1) / l_per), dim3(512), 0, ctx->stream,
+                       m, out, limbs, ctx->d_mod, ctx->d_twf, ctx->log_n, bpr, identity_reduction_bound(ctx, limbs),
+                       l_per);
+    return hipGetLastError();
+}
+
 #define NTT_SWITCH(s, CALL4, CALL5, CALL6, CALL7, CALL8)                                                            \
     switch (s) {                                                                                                   \
     case 4: return CALL4;                                                                                          \
@@ -466,9 +478,15 @@ hipError_t dispatch_row(int s2, ckks_ctx *ctx, uint64_t *d, uint32_t b, uint32_t
 template <bool F, typename Src>
 hipError_t dispatch_col_i64(int s1, ckks_ctx *ctx, const Src &m, uint64_t *out, uint32_t b, uint32_t limbs)
 {
-    NTT_SWITCH(s1, (launch_col_i64<4, F>(ctx, m, out, b, limbs)), (launch_col_i64<5, F>(ctx, m, out, b, limbs)),
-               (launch_col_i64<6, F>(ctx, m, out, b, limbs)), (launch_col_i64<7, F>(ctx, m, out, b, limbs)),
-               (launch_col_i64<8, F>(ctx, m, out, b, limbs)))
+    if constexpr (F) {
+        NTT_SWITCH(s1, (launch_col_i64<4, F>(ctx, m, out, b, limbs)), (launch_col_i64<5, F>(ctx, m, out, b, limbs)),
+                   (launch_col_i64<6, F>(ctx, m, out, b, limbs)), (launch_col_i64<7, F>(ctx, m, out, b, limbs)),
+                   (launch_col8_i64(ctx, m, out, b, limbs)))
+    } else {
+        NTT_SWITCH(s1, (launch_col_i64<4, F>(ctx, m, out, b, limbs)), (launch_col_i64<5, F>(ctx, m, out, b, limbs)),
+                   (launch_col_i64<6, F>(ctx, m, out, b, limbs)), (launch_col_i64<7, F>(ctx, m, out, b, limbs)),
+                   (launch_col_i64<8, F>(ctx, m, out, b, limbs)))
+    }
 }
 
 void split_log(int log_n, int *s1, int *s2)
@@ -603,19 +621,9 @@ ckks_status launch_ntt_col_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, u
     const double bf_ops = f && s1 == 8 ? (2 * kOpsButterflyF64 + 6 * (kOpsButterflyF64 - 3)) / 2
                                        : (f ? kOpsButterflyF64 : kOpsButterflyInt) * s1 / 2;
     prof_begin(ctx, K_NTT_FWD_COL, 8.0 * batch * ctx->n * (1 + limbs), res * (bf_ops + (f ? 3.0 : 8.0)));
-    hipError_t e;
-    if (f && s1 == 8) {
-        const uint32_t bpr = (ctx->n >> 8) / 16;
-        const uint32_t l_per = limbs_per_block(batch * bpr, limbs, 256);
-        hipLaunchKernelGGL(ntt_col8_from_i64, dim3(batch * bpr, (limbs + l_per - 1) / l_per), dim3(512), 0, ctx->stream,
-                           m, out, limbs, ctx->d_mod, ctx->d_twf, ctx->log_n, bpr,
-                           identity_reduction_bound(ctx, limbs), l_per);
-        e = hipGetLastError();
-    } else {
-        const CoefI64 src{m};
-        e = f ? dispatch_col_i64<true>(s1, ctx, src, out, batch, limbs)
-              : dispatch_col_i64<false>(s1, ctx, src, out, batch, limbs);
-    }
+    const CoefI64 src{m};
+    const hipError_t e = f ? dispatch_col_i64<true>(s1, ctx, src, out, batch, limbs)
+                           : dispatch_col_i64<false>(s1, ctx, src, out, batch, limbs);
     prof_end(ctx, K_NTT_FWD_COL);
     if (e != hipSuccess) return set_error(CKKS_EHIP, "ntt launch failed: %s", hipGetErrorString(e));
     return CKKS_OK;
