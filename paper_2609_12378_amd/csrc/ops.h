@@ -202,7 +202,7 @@ ckks_status launch_to_f64(ckks_ctx *ctx, uint64_t *v, size_t words);
 // The gc giant steps g, g + 1, ... of a projection's tile of jc outputs, their partial sums at acc ([gc][jc]
 // ciphertexts): that of step 0 to tot ([jc]), the others rotated by step * (g + gg) with gkeys[g + gg] and added to
 // tot, or (lazy) their key-switching sums to uacc ([jc][2][level+1+n_p][N]).  rot: gc jc ciphertexts; work:
-// ks_scratch_words(ctx, level, ks_rot_batch(gc jc), gc jc) words; gc jc <= 32
+// ks_scratch_words(ctx, level, ks_rot_batch(gc jc), gc jc) words; jc <= 32
 ckks_status giant_steps(ckks_ctx *ctx, const uint64_t *acc, uint64_t *tot, uint64_t *rot, uint64_t *uacc, uint32_t jc,
                         uint32_t g, uint32_t gc, int32_t step, const uint64_t *const *gkeys, uint32_t level, bool lazy,
                         uint64_t *work);

@@ -35,6 +35,7 @@ constexpr int kPE = 8;        // plaintexts per encode block: 8 consecutive doub
 constexpr int kMaxD = 256;    // features per ciphertext handled by the encode kernel
 constexpr int kJT = 32;       // output ciphertexts per vector-ALU multiply-accumulate tile
 constexpr int kMaxJtMfma = 32; // and per matrix-core one (64 outputs need 452 VGPRs, one wave per SIMD: slower)
+constexpr int kMaxRowsMfma = 64;  // rows (outputs times giant steps) of a matrix-core launch, in groups of kMaxJtMfma
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
@@ -249,17 +250,30 @@ __global__ __launch_bounds__(kThreads) void k_mac_tm(uint64_t *acc, const double
 typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int kDig = 7, kGroups = 2 * kDig - 1, kKB = 64, kRowW = 20;
 
-__device__ __forceinline__ void digits7(uint64_t v, int8_t *d, size_t stride)
+// all seven at once, digit a in byte a: digit = byte of (v + 128 sum 256^a) less 128, an exclusive or of its top bit
+__device__ __forceinline__ uint64_t digits7(uint64_t v)
+{
+    constexpr uint64_t k80 = 0x0080808080808080ull;
+    return (v + k80) ^ k80;
+}
+
+// digit a of four values, packed low byte first: the byte transpose of their low and high words
+__device__ __forceinline__ void pack_digits(const uint64_t (&v)[4], uint32_t (&packed)[8])
 {
 #pragma unroll
-    for (int a = 0; a < kDig; a++) {
-        int t = (int)(v & 255u);
-        v >>= 8;
-        if (t >= 128) {
-            t -= 256;
-            v += 1;
-        }
-        d[(size_t)a * stride] = (int8_t)t;
+    for (int h = 0; h < 2; h++) {
+        uint32_t w[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) w[t] = (uint32_t)(v[t] >> (32 * h));
+        // bytes 0, 1 and bytes 2, 3 of two words, then of the two pairs
+        const uint32_t a01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);  // v0.0 v1.0 v0.1 v1.1
+        const uint32_t a23 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+        const uint32_t b01 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+        const uint32_t b23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+        packed[4 * h + 0] = __builtin_amdgcn_perm(b01, a01, 0x05040100u);
+        packed[4 * h + 1] = __builtin_amdgcn_perm(b01, a01, 0x07060302u);
+        packed[4 * h + 2] = __builtin_amdgcn_perm(b23, a23, 0x05040100u);
+        packed[4 * h + 3] = __builtin_amdgcn_perm(b23, a23, 0x07060302u);
     }
 }
 
@@ -292,20 +306,16 @@ __global__ __launch_bounds__(kThreads) void k_xdigits(const uint64_t *__restrict
     const size_t plane = (size_t)L * cols * kt_pad;
     static_assert(kThreads == 256, "64 columns x 4 groups of 16 kappa");
     const uint32_t cc = threadIdx.x >> 2, kq = (threadIdx.x & 3u) << 4;
-    uint32_t w[kDig][4] = {};
+    uint32_t w[8][4];
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-        uint64_t v = tile[kq + i][cc];
+    for (int i = 0; i < 4; i++) {
+        uint64_t v[4];
+        uint32_t packed[8];
 #pragma unroll
-        for (int a = 0; a < kDig; a++) {
-            int t = (int)(v & 255u);
-            v >>= 8;
-            if (t >= 128) {
-                t -= 256;
-                v += 1;
-            }
-            w[a][i >> 2] |= (uint32_t)(uint8_t)t << (8 * (i & 3));
-        }
+        for (int t = 0; t < 4; t++) v[t] = digits7(tile[kq + 4 * i + t][cc]);
+        pack_digits(v, packed);
+#pragma unroll
+        for (int a = 0; a < kDig; a++) w[a][i] = packed[a];
     }
     int8_t *dst = Xd + (((size_t)l * kblocks + kb) * cols + c0 + cc) * 64 + kq;
 #pragma unroll
@@ -313,131 +323,146 @@ __global__ __launch_bounds__(kThreads) void k_xdigits(const uint64_t *__restrict
         *(uint4 *)(dst + (size_t)a * plane) = make_uint4(w[a][0], w[a][1], w[a][2], w[a][3]);
 }
 
-// Block (limb l, run x, polynomial, part): NW waves, wave w holds 16 positions of the run (x T + 16 (part NW + w)
-// + 0..15) of the polynomial and the tile's jc <= 16 MT outputs (MT 16-row MFMA tiles).  Q ([L][2D][npt],
-// npt = K jc, kappa-major) gives the plaintext digits of each 64-kappa block (rows jj >= jc and kappa >= K are
-// zero); Xd the ciphertext digits from kappa_base on (16-byte aligned, rows padded so a block never reads past
-// them).
+// Block (limb l, run x, part[, polynomial]): NW waves, wave w holds 16 positions of the run (x T + 16 (part NW + w)
+// + 0..15) and the tile's jc <= 16 MT outputs (MT 16-row MFMA tiles).  Q ([L][2D][npt], npt = K jc, kappa-major) gives
+// the plaintext values (rows jj >= jc and kappa >= K are zero); Xd the ciphertext digits from kappa_base on (16-byte
+// aligned, rows padded so a block never reads past them).  The digits of up to 64 kKBC kappa of the run's plaintexts
+// (kKBC = NW keeps eight waves on a CU) are laid out in LDS at once, for both polynomials (`polys` of them per block), so the loop over kappa has no barrier:
+// each wave streams its ciphertext digits (1 KB per digit and 64 kappa, loaded one step ahead) against them.
+// At N = 2^16, 13 limbs, 512 kappa and 16 times 16 rows: 14.1 ms with the digits formed per polynomial and 64 kappa and
+// 32 rows a launch; 12.8 ms so, 1.7 P int8 op/s (14.4 ms with 32 rows a launch, the ciphertext digits then crossing HBM
+// twice as often: bound by the matrix cores now).
 template <int NW, int MT>
 __global__ __launch_bounds__(64 * NW) void k_mac_tm_mfma(uint64_t *acc, const int8_t *__restrict__ Xd,
                                                            const double *__restrict__ Q, uint32_t jc, uint32_t K,
                                                            uint32_t kappa_base, uint32_t kt_pad, uint32_t D2,
-                                                           uint32_t L, uint32_t logT, uint32_t log_n,
-                                                           int accumulate, const ModQ *__restrict__ mods)
+                                                           uint32_t L, uint32_t logT, uint32_t log_n, uint32_t polys,
+                                                           uint32_t ng, int accumulate, const ModQ *__restrict__ mods)
 {
-    constexpr int R = 16 * MT;
-    // plaintext digits of the 64-kappa block: row jj of digit a holds 64 bytes, padded to 80 so that both the
+    constexpr int R = 16 * MT, kKBC = NW;
+    // plaintext digits of a 64-kappa block: row jj of digit a holds 64 bytes, padded to 80 so that both the
     // packed 4-byte writes (lanes along jj) and the 16-byte MFMA reads spread over the banks
-    __shared__ __attribute__((aligned(16))) uint32_t A[kDig][R][kRowW];
+    __shared__ __attribute__((aligned(16))) uint32_t A[kKBC][kDig][R][kRowW];
     const uint32_t parts = (1u << (logT - 4)) / NW;
-    uint32_t bid = blockIdx.x;
+    // consecutive blocks go to the eight XCDs in turn: the ng row groups of one (limb, run, part) follow each other on
+    // one XCD, where the ciphertext digits that the first one reads are still in the L2
+    uint32_t bid = blockIdx.x, group = 0;
+    if (gridDim.x % (8 * ng) == 0) {
+        group = (bid >> 3) % ng;
+        bid = (bid >> 3) / ng * 8 + (bid & 7u);
+    } else {
+        group = bid % ng;
+        bid /= ng;
+    }
+    const uint32_t jj0 = group * R, rows = min(jc - jj0, (uint32_t)R);
     const uint32_t part = bid % parts;
     bid /= parts;
-    const uint32_t poly = bid & 1, x = (bid >> 1) % D2, l = (bid >> 1) / D2;
+    const uint32_t groups = 2 / polys, poly0 = (bid % groups) * polys;
+    bid /= groups;
+    const uint32_t x = bid % D2, l = bid / D2;
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t pos = (x << logT) + 16 * (part * NW + w) + (lane & 15);
     const size_t n = (size_t)1 << log_n, cols = 2 * n;
     const size_t plane = (size_t)L * cols * kt_pad;
-    // this lane's 16 kappa of block k0 (kappa_base is a multiple of 16, so they lie in one 64-kappa block)
-    const int8_t *xb = Xd + ((size_t)l * cols * (kt_pad / 64) + (size_t)poly * n + pos) * 64;
-    auto xoff = [&](uint32_t k0) {
-        const uint32_t kap = kappa_base + k0 + 16 * (lane >> 4);
-        return (size_t)(kap >> 6) * cols * 64 + (kap & 63u);
+    // this lane's 16 kappa of a 64-kappa step lie in one 64-kappa block of Xd (kappa_base is a multiple of 16): a
+    // 32-bit lane offset from a uniform base per step and digit
+    const uint32_t kl = (kappa_base & 63u) + 16 * (lane >> 4);
+    const uint32_t loff = ((kl >> 6) * (uint32_t)cols + pos) * 64 + (kl & 63u);
+    const uint32_t kblocks = (K + kKB - 1) / kKB, steps = polys * kblocks;
+    auto step_base = [&](uint32_t s) {
+        const uint32_t poly = poly0 + s / kblocks, kb = (kappa_base >> 6) + s % kblocks;
+        return Xd + (((size_t)l * (kt_pad / 64) + kb) * cols + poly * n) * 64;
     };
-    const double *qx = Q + ((size_t)l * D2 + x) * (size_t)K * jc;
-    v4i c[MT][kGroups];
-#pragma unroll
-    for (int m = 0; m < MT; m++)
-#pragma unroll
-        for (int g = 0; g < kGroups; g++) c[m][g] = v4i{0, 0, 0, 0};
-    // software pipeline: the next block's ciphertext digits and plaintext values are loaded into registers
-    // while the current block's products run
-    constexpr int QPT = (R * (kKB / 4) + 64 * NW - 1) / (64 * NW);  // packed table entries per thread
-    auto load_q = [&](uint32_t k0, double (&qv)[QPT][4]) {
-#pragma unroll
-        for (int i = 0; i < QPT; i++) {
-            const uint32_t e = threadIdx.x + i * 64 * NW, jj = e % R, k4 = e / R;
+    const double *qx = Q + ((size_t)l * D2 + x) * (size_t)K * jc + jj0;
+    // the digits of kappa c0 .. c0 + 64 nkb - 1
+    auto build = [&](uint32_t c0, uint32_t nkb) {
+#pragma unroll 2
+        for (uint32_t e = threadIdx.x; e < nkb * R * (kKB / 4); e += 64 * NW) {
+            const uint32_t jj = e % R, k4 = e / R;
+            uint64_t v[4];
 #pragma unroll
             for (int t = 0; t < 4; t++) {
-                const uint32_t kappa = k0 + 4 * k4 + t;
-                qv[i][t] = (e < R * (kKB / 4) && jj < jc && kappa < K) ? qx[(size_t)kappa * jc + jj] : 0.0;
+                const uint32_t kappa = c0 + 4 * k4 + t;
+                v[t] = digits7(jj < rows && kappa < K ? (uint64_t)qx[(size_t)kappa * jc + jj] : 0);
             }
+            uint32_t packed[8];
+            pack_digits(v, packed);
+#pragma unroll
+            for (int a = 0; a < kDig; a++) A[k4 / (kKB / 4)][a][jj][k4 % (kKB / 4)] = packed[a];
         }
     };
-    v4i bn[kDig];
-    double qn[QPT][4];
+    v4i c[MT][kGroups];
+    // a polynomial's end: sum_s 256^s C_s mod q_l, canonical, added to the stored sums when accumulating
+    auto finish = [&](uint32_t poly) {
+        const ModQ md = mods[l];
+        const nttc::Ar<true> ar(md);
+        double w256[kGroups];
+        w256[0] = 1.0;
+        asm volatile("" : "+v"(w256[0]));  // formed here, not kept in registers across the loop over kappa
 #pragma unroll
-    for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane + xoff(0));
-    load_q(0, qn);
-    for (uint32_t k0 = 0; k0 < K; k0 += kKB) {
-        v4i b[kDig];
-        double qc[QPT][4];
-#pragma unroll
-        for (int d = 0; d < kDig; d++) b[d] = bn[d];
-#pragma unroll
-        for (int i = 0; i < QPT; i++)
-#pragma unroll
-            for (int t = 0; t < 4; t++) qc[i][t] = qn[i][t];
-        if (k0 + kKB < K) {
-#pragma unroll
-            for (int d = 0; d < kDig; d++) bn[d] = *(const v4i *)(xb + (size_t)d * plane + xoff(k0 + kKB));
-            load_q(k0 + kKB, qn);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < QPT; i++) {
-            const uint32_t e = threadIdx.x + i * 64 * NW, jj = e % R, k4 = e / R;
-            if (e < R * (kKB / 4)) {
-                uint32_t packed[kDig] = {0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    int8_t d[kDig];
-                    digits7((uint64_t)qc[i][t], d, 1);
-#pragma unroll
-                    for (int a = 0; a < kDig; a++) packed[a] |= (uint32_t)(uint8_t)d[a] << (8 * t);
-                }
-#pragma unroll
-                for (int a = 0; a < kDig; a++) A[a][jj][k4] = packed[a];
-            }
-        }
-        __syncthreads();
+        for (int g = 1; g < kGroups; g++) w256[g] = (double)ar.to_canon(ar.mul(w256[g - 1], 256.0));
+        const size_t ctw = 2 * (size_t)L * n;
 #pragma unroll
         for (int m = 0; m < MT; m++) {
 #pragma unroll
-            for (int a = 0; a < kDig; a++) {
-                const v4i av = *(const v4i *)&A[a][16 * m + (lane & 15)][4 * (lane >> 4)];
+            for (int r = 0; r < 4; r++) {
+                const uint32_t jj = 16 * m + 4 * (lane >> 4) + r;
+                double sum = 0.0;
 #pragma unroll
-                for (int d = 0; d < kDig; d++)
-                    c[m][a + d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, b[d], c[m][a + d], 0, 0, 0);
+                for (int g = 0; g < kGroups; g++) {
+                    sum += ar.mul((double)c[m][g][r], w256[g]);
+                    if ((g & 3) == 3) sum = ar.red(sum);
+                }
+                if (jj < rows) {
+                    uint64_t *dst = acc + (size_t)(jj0 + jj) * ctw + ((size_t)poly * L + l) * n + pos;
+                    uint64_t v = ar.to_canon(sum);
+                    if (accumulate) v = addmod(v, *dst, md.q);
+                    *dst = v;
+                }
             }
         }
+    };
+    // one step: b holds its ciphertext digits; once a digit's last product is issued, its registers take the digit of
+    // the step after the next
+    auto step = [&](uint32_t s, v4i (&b)[kDig]) {
+        const uint32_t kb = s % kblocks, slot = kb % kKBC;
+        if (kb == 0) {
+#pragma unroll
+            for (int m = 0; m < MT; m++)
+#pragma unroll
+                for (int g = 0; g < kGroups; g++) c[m][g] = v4i{0, 0, 0, 0};
+        }
+        if (slot == 0 && (s < kblocks || kblocks > (uint32_t)kKBC)) {
+            __syncthreads();
+            build(kb * kKB, min((uint32_t)kKBC, kblocks - kb));
+            __syncthreads();
+        }
+        const int8_t *nb = s + 2 < steps ? step_base(s + 2) : step_base(s);
+#pragma unroll
+        for (int m = 0; m < MT; m++) {
+            v4i av[kDig];
+#pragma unroll
+            for (int a = 0; a < kDig; a++) av[a] = *(const v4i *)&A[slot][a][16 * m + (lane & 15)][4 * (lane >> 4)];
+#pragma unroll
+            for (int d = 0; d < kDig; d++) {
+#pragma unroll
+                for (int a = 0; a < kDig; a++)
+                    c[m][a + d] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[a], b[d], c[m][a + d], 0, 0, 0);
+                if (m == MT - 1) b[d] = *(const v4i *)(nb + (size_t)d * plane + loff);
+            }
+        }
+        if (kb + 1 == kblocks) finish(poly0 + s / kblocks);
+    };
+    v4i b0[kDig], b1[kDig];
+#pragma unroll
+    for (int d = 0; d < kDig; d++) {
+        b0[d] = *(const v4i *)(step_base(0) + (size_t)d * plane + loff);
+        b1[d] = *(const v4i *)(step_base(steps > 1 ? 1 : 0) + (size_t)d * plane + loff);
     }
-    // epilogue: sum_s 256^s C_s mod q_l, canonical, added to the stored sums when accumulating
-    const ModQ md = mods[l];
-    const nttc::Ar<true> ar(md);
-    double w256[kGroups];
-    w256[0] = 1.0;
-#pragma unroll
-    for (int g = 1; g < kGroups; g++) w256[g] = (double)ar.to_canon(ar.mul(w256[g - 1], 256.0));
-    const size_t ctw = 2 * (size_t)L * n;
-#pragma unroll
-    for (int m = 0; m < MT; m++) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const uint32_t jj = 16 * m + 4 * (lane >> 4) + r;
-            double sum = 0.0;
-#pragma unroll
-            for (int g = 0; g < kGroups; g++) {
-                sum += ar.mul((double)c[m][g][r], w256[g]);
-                if ((g & 3) == 3) sum = ar.red(sum);
-            }
-            if (jj < jc) {
-                uint64_t *dst = acc + (size_t)jj * ctw + ((size_t)poly * L + l) * n + pos;
-                uint64_t v = ar.to_canon(sum);
-                if (accumulate) v = addmod(v, *dst, md.q);
-                *dst = v;
-            }
-        }
+#pragma unroll 1
+    for (uint32_t s = 0; s < steps; s += 2) {
+        step(s, b0);
+        if (s + 1 < steps) step(s + 1, b1);
     }
 }
 
@@ -464,7 +489,7 @@ TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in,
     ts.Jt = (n_out + tiles - 1) / tiles;
     // with few outputs several giant steps share a launch (their plaintexts are rows of the same product): the digit
     // planes are read once for all of them, and their sums' key switching is one batch
-    ts.G = ts.mfma ? std::max(1u, std::min((D + n1 - 1) / n1, (uint32_t)kMaxJtMfma / ts.Jt)) : 1;
+    ts.G = ts.mfma ? std::max(1u, std::min((D + n1 - 1) / n1, (uint32_t)kMaxRowsMfma / ts.Jt)) : 1;
     const uint32_t rows = ts.G * ts.Jt;
     // pairs per sub-batch: the tile's weight tables within 2 GiB, a multiple of 8 (16-byte aligned digit rows),
     // at most 2048 (int32 digit sums stay exact)
@@ -581,7 +606,7 @@ ckks_status launch_mac_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, cons
                             uint32_t kbase, uint32_t kt_pad, uint32_t D2, uint32_t L, uint32_t logT, bool accumulate)
 {
     const uint32_t tiles16 = 1u << (logT - 4);
-    CK_REQUIRE(jc >= 1 && jc <= (uint32_t)kMaxJtMfma && kbase % 16 == 0 && K >= 1 && K <= 4096 && logT >= 4 &&
+    CK_REQUIRE(jc >= 1 && jc <= (uint32_t)kMaxRowsMfma && kbase % 16 == 0 && K >= 1 && K <= 4096 && logT >= 4 &&
                    logT <= 7 && kbase + ((K + 63) & ~63u) <= kt_pad,
                CKKS_EINVAL, "matrix-core multiply-accumulate: unsupported tile (jc %u, kappa base %u, K %u, T %u)",
                jc, kbase, K, 1u << logT);
@@ -590,6 +615,9 @@ ckks_status launch_mac_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, cons
     prof_begin(ctx, K_MAC_TM, (double)kDig * K * 2 * L * ctx->n + 8.0 * (double)K * jc * L * D2 +
                                   8.0 * res * (accumulate ? 2 : 1),
                0.0);
+    // both polynomials in one block (their plaintext digits laid out once) while the blocks still fill the chip
+    const uint32_t nw = std::min(tiles16, 8u), ng = (jc + kMaxJtMfma - 1) / kMaxJtMfma;
+    const uint32_t polys = ng * L * D2 * (tiles16 / nw) >= 512 ? 2u : 1u;
     // outputs in tiles of 16 rows: one tile where the launch has no more
 #define CK_MFMA(NWV)                                                                                               \
     if (jc <= 16)                                                                                                  \
@@ -597,9 +625,9 @@ ckks_status launch_mac_mfma(ckks_ctx *ctx, uint64_t *acc, const int8_t *Xd, cons
     else                                                                                                           \
         CK_MFMA_T(NWV, 2)
 #define CK_MFMA_T(NWV, MTV)                                                                                        \
-    hipLaunchKernelGGL((k_mac_tm_mfma<NWV, MTV>), dim3(L * D2 * 2 * (tiles16 / NWV)), dim3(64 * NWV), 0,           \
-                       ctx->stream, acc, Xd, Q, jc, K, kbase, kt_pad, D2, L, logT, ctx->log_n, (int)accumulate,     \
-                       ctx->d_mod)
+    hipLaunchKernelGGL((k_mac_tm_mfma<NWV, MTV>), dim3(ng * L * D2 * (2 / polys) * (tiles16 / NWV)), dim3(64 * NWV), 0, \
+                       ctx->stream, acc, Xd, Q, jc, K, kbase, kt_pad, D2, L, logT, ctx->log_n, polys, ng,            \
+                       (int)accumulate, ctx->d_mod)
     switch (tiles16) {
     case 1: CK_MFMA(1); break;
     case 2: CK_MFMA(2); break;
