@@ -65,10 +65,13 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
                                                       const double *__restrict__ twf, uint32_t log_n, double *Q)
 {
     constexpr uint32_t kBT = 512;
-    __shared__ double2 buf[kPE * kMaxD];        // FFT, then the transform's outputs (kPE x 2D doubles)
-    __shared__ int64_t mq[kPE * 2 * kMaxD];     // rounded coefficients m'
+    // FFT, then the transform's exchange rows, then its outputs (kPE x 2D doubles): 74 KB in all, two blocks a CU
+    __shared__ __attribute__((aligned(16))) double buf_raw[2 * kPE * nttc::kTr8];
+    static_assert(nttc::kTr8 >= 256 && kMaxD == 256, "the FFT and the outputs fit the exchange rows");
+    __shared__ int64_t mq[kPE * 2 * kMaxD];     // rounded coefficients m'; doubles unless one exceeds 2^52
     __shared__ double tws[2][256];
-    __shared__ double tr[2 * kPE][nttc::kTr8];
+    double2 *buf = (double2 *)buf_raw;
+    auto tr = [&](uint32_t sub) { return buf_raw + sub * nttc::kTr8; };
     const uint32_t D = a.D, logD = a.logD, D2 = 2 * D;
     const uint32_t pt0 = blockIdx.x * kPE;
     // 1. one period of each plaintext's slot vector, at its bit-reversed FFT position
@@ -114,13 +117,23 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
         __syncthreads();
     }
     // 3. twist, scale and round: m'[k] = round(c Re v_k), m'[k + D] = round(c Im v_k)
+    bool wide = false;
     for (uint32_t e = threadIdx.x; e < kPE * D; e += kBT) {
         const uint32_t p = e / D, k = e % D;
         const double2 v = cmul(twist[(size_t)k * T], buf[p * D + k]);
-        mq[p * D2 + k] = (int64_t)round(c * v.x);
-        mq[p * D2 + k + D] = (int64_t)round(c * v.y);
+        const double m0 = round(c * v.x), m1 = round(c * v.y);
+        wide |= !(fabs(m0) <= 0x1p52 && fabs(m1) <= 0x1p52);
+        mq[p * D2 + k] = (int64_t)m0;
+        mq[p * D2 + k + D] = (int64_t)m1;
     }
-    double *xs = (double *)buf;  // kPE rows of 2D doubles
+    // within 2^52 a coefficient's residue is one range reduction of its double: converted once for all limbs (32768
+    // plaintexts of 512 points at 13 limbs, with the exchange rows' own LDS, one block a CU, and an integer reduction
+    // per limb: 1392 us; 927 us so)
+    const bool big = __syncthreads_or(wide);
+    if (!big) {
+        for (uint32_t e = threadIdx.x; e < kPE * D2; e += kBT) mq[e] = __double_as_longlong((double)mq[e]);
+    }
+    double *xs = buf_raw;  // kPE rows of 2D doubles
     const bool regs = D2 == 512 || D2 == 256;
     const uint32_t nsub = D2 / 256;
     // 4. per limb: the 2D-point negacyclic NTT (Cooley-Tukey, group i of stage m takes Psi[m + i])
@@ -128,6 +141,7 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
         const ModQ md = mods[l];
         const nttc::Ar<true> ar(md);
         const double *tw = twf + ((size_t)l << log_n);
+        auto residue = [&](uint32_t e) { return big ? ar.from_i64(mq[e], md) : ar.red(__longlong_as_double(mq[e])); };
         __syncthreads();
         if (regs) {
             for (uint32_t e = threadIdx.x; e < nsub * 255; e += kBT) {
@@ -146,7 +160,7 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
                     const uint32_t u = nttc::u8<0>(t, k);
                     double xo = 0.0;
                     if (live) {
-                        const double X = ar.from_i64(mq[p * D2 + u], md), Y = ar.from_i64(mq[p * D2 + u + 256], md);
+                        const double X = residue(p * D2 + u), Y = residue(p * D2 + u + 256);
                         const double r = ar.mul(Y, w0);
                         xo = si == 0 ? X + r : X - r;
                     }
@@ -155,16 +169,16 @@ __global__ __launch_bounds__(512) void k_enc_periodic(TmArgs a, const double2 *_
             } else {
 #pragma unroll
                 for (int k = 0; k < nttc::kE8; k++)
-                    x[k] = live ? ar.from_i64(mq[p * D2 + nttc::u8<0>(t, k)], md) : 0.0;
+                    x[k] = live ? residue(p * D2 + nttc::u8<0>(t, k)) : 0.0;
             }
-            nttc::fwd8_256<0xFFu>(x, tws[si], tr[sub], t, ar);
+            nttc::fwd8_256<0xFFu>(x, tws[si], tr(sub), t, ar);
             if (live) {
 #pragma unroll
                 for (int k = 0; k < nttc::kE8; k++) xs[p * D2 + 256 * si + nttc::u8<2>(t, k)] = x[k];
             }
             __syncthreads();
         } else {
-            for (uint32_t e = threadIdx.x; e < kPE * D2; e += kBT) xs[e] = ar.from_i64(mq[e], md);
+            for (uint32_t e = threadIdx.x; e < kPE * D2; e += kBT) xs[e] = residue(e);
             __syncthreads();
             for (uint32_t m = 1, t = D; m < D2; m <<= 1, t >>= 1) {
                 for (uint32_t e = threadIdx.x; e < kPE * D; e += kBT) {
