@@ -549,9 +549,9 @@ __global__ __launch_bounds__(64) void k_ks_finish8(RotArgs ra, const uint64_t *_
 
 // k_ks_finish8 with the inner products first, every position's loads issued before the transforms, and the addends'
 // gathers at the start: for seed-expanded keys (whose Philox blocks the loads then overlap), and with stored keys for
-// batches of at most kWideWaves waves, which cannot hide one position's loads behind another wave's work (one
-// rotation at 13 limbs of N = 2^16, 1664 waves: 26 -> 15 us).  Larger batches with stored keys take k_ks_finish8: this
-// order needs 160 VGPRs, 3 waves per SIMD, and measured 5% slower there than one position at a time after the
+// batches of at most kWideWaves waves, which cannot hide one position's loads behind another wave's work (an
+// evaluation step with two key switches of 1664 waves each at N = 2^16: 287 -> 277 us, this kernel 20 us of each).
+// Larger batches with stored keys take k_ks_finish8: this order needs 160 VGPRs, 3 waves per SIMD, and measured 5% slower there than one position at a time after the
 // transforms, 88 VGPRs and 5 waves, which streams ~5 TB/s of keys, converted rows and outputs.
 constexpr size_t kWideWaves = 3072;
 template <bool SEEDED, int ND>
@@ -924,7 +924,7 @@ ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, 
                            uint64_t *digits, size_t stage_rows)
 {
     if (!count) return CKKS_OK;
-    if (blk_modups(ctx, level, count) && (size_t)count * (level + 1) <= stage_rows)
+    if (blk_modups(ctx, level) && (size_t)count * (level + 1) <= stage_rows)
         return blk_modup(ctx, c1, count == 1 ? 0 : in_stride, nullptr, count, level, digits,
                          digits + (size_t)count * n_digits(ctx, level) * (level + 1 + ctx->n_p) * ctx->n);
     const uint32_t K = ctx->n_p, ext = level + 1 + K, nd = n_digits(ctx, level), alpha = ctx->alpha;

@@ -8,8 +8,9 @@
 //   2. column pass, leaving the digits y there;
 //   3. conversion of every digit, fused with the forward column pass where columns have 256 points;
 //   4. forward row pass, which in the digits' own rows (no longer needed for y) puts the polynomial itself.
-// One launch per digit and step and copies of the limbs in and out, as before, were 6 nd + 2 launches; at 13 limbs
-// (two digits) of N = 2^16 a ModUp took 75 us, now 36 us, and at 24 limbs (three) 150 us, now 62 us.
+// One launch per digit and step and copies of the limbs in and out were 6 nd + 2 launches: an evaluation step with two
+// key switches at N = 2^16 (13 limbs, two digits) took 378 us with those and 316 us so, 32 rotations sharing a ModUp
+// (24 limbs, three digits) 1640 and 1536 us.
 #include <algorithm>
 
 #include "ckks_internal.h"
@@ -141,8 +142,9 @@ __global__ __launch_bounds__(256) void k_up_conv(uint64_t *out, const uint64_t *
 // doubles, the inter-pass form the row passes read.  The converted rows thus cross HBM once instead of three times.
 // Target t + 1's twiddles (Psi[1..255]) are staged into the idle half of a double-buffered table while target t is
 // transformed.  EXACT: every block has 8 sources.  32 rotations at 24 limbs: 600 us with a reduced product per term and
-// the digits formed here, 550 us with the one quotient, 520 us from ready digits; with 212 registers it runs two
-// waves a SIMD and is bounded by arithmetic latency more than by either roof.
+// the digits formed here, 550 us with the one quotient, 505 us from ready digits; with 212 registers it runs two
+// waves a SIMD.  Blocks of 8 columns (256 threads, two independent blocks a CU) measured the same within 1% on every
+// call, so the two barriers per target are not what bounds it: the fp64 pipes at their sustained clock are.
 template <bool EXACT>
 __global__ __launch_bounds__(512) void k_conv_col8(uint64_t *out, const uint64_t *in, Blocks bl, uint32_t t_per,
                                                    const ModQ *__restrict__ mods, const double *__restrict__ twf)

@@ -117,7 +117,7 @@ bool blk_rows(const ckks_ctx *ctx, size_t rows);
 // they are the faster encryption and decryption of `limbs` limbs
 bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs);
 // they are the faster ModUp of `count` ciphertexts at `level`
-bool blk_modups(const ckks_ctx *ctx, uint32_t level, uint32_t count);
+bool blk_modups(const ckks_ctx *ctx, uint32_t level);
 // they are the faster key switching for a batch of `count` rotations at `level`
 bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count);
 // they take every key-switching step at `level`

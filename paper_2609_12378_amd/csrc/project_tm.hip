@@ -488,7 +488,8 @@ struct TmScratch {
     size_t x2_w, acc_w, tot_w, rot_w, q_w, ks_w, wd_w, xd_w, ua_w, total;
 };
 
-TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in, uint32_t d_out, uint32_t n1)
+TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in, uint32_t d_out, uint32_t n1,
+                     uint32_t max_g = ~0u)
 {
     TmScratch ts{};
     const uint32_t level = L - 1, n_in = d_in / D, n_out = d_out / D;
@@ -504,6 +505,7 @@ TmScratch tm_scratch(const ckks_ctx *ctx, uint32_t L, uint32_t D, uint32_t d_in,
     // with few outputs several giant steps share a launch (their plaintexts are rows of the same product): the digit
     // planes are read once for all of them, and their sums' key switching is one batch
     ts.G = ts.mfma ? std::max(1u, std::min((D + n1 - 1) / n1, (uint32_t)kMaxRowsMfma / ts.Jt)) : 1;
+    ts.G = std::min(ts.G, max_g);
     const uint32_t rows = ts.G * ts.Jt;
     // pairs per sub-batch: the tile's weight tables within 2 GiB, a multiple of 8 (16-byte aligned digit rows),
     // at most 2048 (int32 digit sums stay exact)
@@ -725,9 +727,17 @@ extern "C" ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in,
     }
 
     const size_t N = ctx->n, ctw = 2 * (size_t)L * N;
-    const TmScratch ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1);
+    TmScratch ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1);
     void *w;
-    CK_TRY(ctx_scratch(ctx, ts.total * 8, &w));
+    ckks_status st = ctx_scratch(ctx, ts.total * 8, &w);
+    // a workspace or a card without the room for several giant steps per launch: fewer of them, down to one
+    while (st == CKKS_ENOMEM && ts.G > 1) {
+        (void)hipGetLastError();
+        clear_error();
+        ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1, ts.G / 2);
+        st = ctx_scratch(ctx, ts.total * 8, &w);
+    }
+    CK_TRY(st);
     uint64_t *x2 = (uint64_t *)w;  // [n_in][n1][xr, xw][2][L][N]
     uint64_t *acc = x2 + ts.x2_w;
     uint64_t *tot = acc + ts.acc_w;

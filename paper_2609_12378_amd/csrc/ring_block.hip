@@ -592,9 +592,9 @@ bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs)
 }
 
 // the same for a ModUp (modup.hip: five launches)
-bool blk_modups(const ckks_ctx *ctx, uint32_t level, uint32_t count)
+bool blk_modups(const ckks_ctx *ctx, uint32_t level)
 {
-    return blk_switch(ctx, level) && (ctx->log_n < 14 || count > 1000000);
+    return blk_switch(ctx, level) && ctx->log_n < 14;
 }
 
 // the same for a batch of rotations: per rotation of 24 limbs 16 us here against 13 us in the fused two-pass kernels
