@@ -785,7 +785,9 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
     const uint32_t kp = ctx->n_primes();
     int s1, s2;
     ntt_split(ctx->log_n, &s1, &s2);
-    if (s2 == 8 && ntt_uses_f64(ctx, L)) {
+    // the fused kernels take rows of 256 points after a column pass; N = 2^8 is one such row without columns
+    const bool rows256 = s1 > 0 && s2 == 8;
+    if (rows256 && ntt_uses_f64(ctx, L)) {
         // fused ModDown: only the P rows of u are formed in HBM
         uint64_t *up = work;                             // [count][2][K][N]
         uint64_t *cw = up + (size_t)count * 2 * K * N;   // [count][2][L][N]
@@ -862,7 +864,7 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
     const ConvDev *cd;
     CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
     CK_TRY(launch_conv(ctx, cd, u + (size_t)L * N, ext, cw, L, L, 0, 2 * count));
-    if (s2 == 8 && !ntt_uses_f64(ctx, L)) {
+    if (rows256) {
         CK_TRY(launch_ntt_fwd_first_pass(ctx, cw, 2 * count, L, limb_range(0, L)));
         return fused_moddown_int(ctx, level, ra, u, cw);
     }
