@@ -791,9 +791,16 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
         // fused ModDown: only the P rows of u are formed in HBM
         uint64_t *up = work;                             // [count][2][K][N]
         uint64_t *cw = up + (size_t)count * 2 * K * N;   // [count][2][L][N]
-        if (f64_switch(ctx, level)) {
-            // the P rows' inner products with the first pass of their inverse transform, then its second pass, the
-            // conversion and the first forward pass of the converted rows
+        // Each step by its own primes, not by the level: a chain of a 50-bit base or special primes over 40-bit primes
+        // has fp64 special primes whose conversion is not exact in fp64, or a ModUp digit that is not while the
+        // ModDown is (24 limbs of 40 bits under 8 of 49, 32 rotations at 13 and 4 limbs of N = 2^16: 1230 and 584 us
+        // with every step held to the level's worst conversion, 1132 and 496 us so).
+        const ConvDev *cd;
+        CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
+        const LimbMap pm = limb_range(ctx->n_q, K);
+        const bool p_f64 = ntt_map_f64(ctx, pm), conv_f64 = p_f64 && up_conv_ok(ctx, cd);
+        if (p_f64) {
+            // the P rows' inner products with the first pass of their inverse transform
             const uint32_t bpl = 1u << (ctx->log_n - 9);
             const double res = (double)count * 2 * K * N;
             prof_begin(ctx, K_KEYIP, 8.0 * res * (nd + 1.0) + 8.0 * (double)nd * K * N,
@@ -808,7 +815,6 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
 #undef CK_IPI
             prof_end(ctx, K_KEYIP);
             HIP_TRY(hipGetLastError());
-            CK_TRY(up_moddown(ctx, up, 2 * count, level, cw));
         } else {
             const dim3 grid((ctx->n + kThreads - 1) / kThreads, K, count), block(kThreads);
             prof_begin(ctx, K_KEYIP, 8.0 * ctx->n * K * (count * (2.0 * nd + 2.0) + nd));
@@ -820,9 +826,13 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
                                            ctx->d_mod, ctx->log_n);
             prof_end(ctx, K_KEYIP);
             HIP_TRY(hipGetLastError());
-            CK_TRY(launch_ntt_strided(ctx, up, 2 * count, K, limb_range(ctx->n_q, K), true));
-            const ConvDev *cd;
-            CK_TRY(ctx_conv(ctx, (int)level, -1, &cd));
+            CK_TRY(launch_ntt_strided(ctx, up, 2 * count, K, pm, true));
+        }
+        // the inverse's second pass, the conversion and the first forward pass of the converted rows
+        if (conv_f64) {
+            CK_TRY(up_moddown(ctx, up, 2 * count, level, cw));
+        } else {
+            if (p_f64) CK_TRY(launch_ntt_inv_second_pass(ctx, up, 2 * count, K, pm));
             CK_TRY(launch_conv(ctx, cd, up, K, cw, L, L, 0, 2 * count));
             CK_TRY(launch_ntt_fwd_first_pass(ctx, cw, 2 * count, L, limb_range(0, L)));
         }

@@ -325,14 +325,19 @@ ckks_status launch_blocks_conv(ckks_ctx *ctx, uint64_t *out, const uint64_t *in,
 
 }  // namespace
 
+bool up_conv_ok(const ckks_ctx *ctx, const ConvDev *cd)
+{
+    return ctx->log_n >= 12 && cd->f64 && cd->ns >= 1 && cd->ns <= 16;
+}
+
 bool f64_level_ok(const ckks_ctx *ctx, uint32_t level)
 {
-    if (ctx->log_n < 12 || !ctx->n_p) return false;
+    if (!ctx->n_p) return false;
     for (uint32_t i = 0; i < ctx->n_primes(); i++)
         if ((i <= level || i >= ctx->n_q) && !ctx->f64_ok[i]) return false;
     for (int j = -1; j < (int)n_digits(ctx, level); j++) {
         const auto it = ctx->conv.find({(int)level, j});
-        if (it == ctx->conv.end() || !it->second.f64 || it->second.ns < 1 || it->second.ns > 16) return false;
+        if (it == ctx->conv.end() || !up_conv_ok(ctx, &it->second)) return false;
     }
     return true;
 }

@@ -95,8 +95,11 @@ ckks_status fused_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const
 ckks_status fused_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_t *a, const int8_t *s,
                           const int32_t *e, const uint64_t *m, uint32_t limbs, uint64_t *work);
 
-// ModUp and ModDown conversions in fp64 (modup.hip): N >= 2^12, every prime of the level and of P below 2^50, at most
-// 16 source limbs a conversion (computed once per context: ckks_ctx::f64_level)
+// ModUp and ModDown conversions in fp64 (modup.hip): N >= 2^12, at most 16 source limbs a conversion whose constants
+// are exact in fp64
+bool up_conv_ok(const ckks_ctx *ctx, const ConvDev *cd);
+// every prime of the level and of P below 2^50 and every conversion of the level such (computed once per context:
+// ckks_ctx::f64_level)
 bool f64_level_ok(const ckks_ctx *ctx, uint32_t level);
 inline bool f64_switch(const ckks_ctx *ctx, uint32_t level)
 {
