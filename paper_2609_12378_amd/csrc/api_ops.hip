@@ -498,8 +498,7 @@ ckks_status ckks_mul_relin(ckks_ctx *ctx, const ckks_buf *a, const ckks_buf *b, 
     uint64_t *digits = d2 + L * N;
     uint64_t *rw = digits + ((size_t)nd * ext + ctx->alpha) * N;
     // the whole-row kernels form the tensor product where they read it, unless the output overwrites an input
-    if (blk_modups(ctx, level) && blk_rotations(ctx, level, 1) &&
-        !overlap(out->data, 2 * L * N, a->data, 2 * L * N) &&
+    if (blk_switch(ctx, level) && !overlap(out->data, 2 * L * N, a->data, 2 * L * N) &&
         !overlap(out->data, 2 * L * N, b->data, 2 * L * N)) {
         CK_TRY(ks_mul_relin_blk(ctx, a->data, b->data, rlk, level, out->data, digits));
     } else {
@@ -527,7 +526,7 @@ ckks_status ckks_modup(ckks_ctx *ctx, const uint64_t *c, uint32_t level, uint64_
     CK_TRY(ctx_scratch(ctx, op_workspace_bytes(ctx, CKKS_OP_MODUP, &level), &w));
     const size_t dig_w = (size_t)nd * ext * N, c_w = (size_t)(level + 1) * N;
     if (f64_switch(ctx, level) && !overlap(digits, dig_w, c, c_w)) {
-        if (blk_modups(ctx, level)) return blk_modup(ctx, c, 0, nullptr, 1, level, digits, (uint64_t *)w);
+        if (blk_switch(ctx, level)) return blk_modup(ctx, c, 0, nullptr, 1, level, digits, (uint64_t *)w);
         return up_modup(ctx, c, 0, 1, level, digits);
     }
     CK_TRY(ks_modup(ctx, c, level, (uint64_t *)w, ctx->alpha));

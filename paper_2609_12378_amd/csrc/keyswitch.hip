@@ -780,7 +780,7 @@ ckks_status ks_rotate_batch(ckks_ctx *ctx, uint32_t level, uint32_t count, const
             ra.seed[r][1] = seeds[2 * r + 1];
         }
     }
-    if (!seeded && blk_rotations(ctx, level, count)) return blk_rotate_batch(ctx, level, ra, work);
+    if (!seeded && blk_switch(ctx, level)) return blk_rotate_batch(ctx, level, ra, work);
     // a seeded key holds its b half only: key_rows rows per digit instead of 2 key_rows
     const uint32_t kp = ctx->n_primes();
     int s1, s2;
@@ -936,7 +936,7 @@ ckks_status ks_modup_batch(ckks_ctx *ctx, const uint64_t *c1, size_t in_stride, 
                            uint64_t *digits, size_t stage_rows)
 {
     if (!count) return CKKS_OK;
-    if (blk_modups(ctx, level) && (size_t)count * (level + 1) <= stage_rows)
+    if (blk_switch(ctx, level) && (size_t)count * (level + 1) <= stage_rows)
         return blk_modup(ctx, c1, count == 1 ? 0 : in_stride, nullptr, count, level, digits,
                          digits + (size_t)count * n_digits(ctx, level) * (level + 1 + ctx->n_p) * ctx->n);
     const uint32_t K = ctx->n_p, ext = level + 1 + K, nd = n_digits(ctx, level), alpha = ctx->alpha;
@@ -1008,7 +1008,7 @@ ckks_status ks_moddown(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t leve
 {
     const uint32_t K = ctx->n_p, ext = level + 1 + K, L = level + 1;
     const size_t N = ctx->n;
-    if (blk_switch(ctx, level)) return blk_moddown(ctx, u, polys, level, add0, add0_g, add1, out);
+    if (blk_moddowns(ctx, level, polys)) return blk_moddown(ctx, u, polys, level, add0, add0_g, add1, out);
     // INTT of the P rows of every polynomial, in place
     LimbMap pm = limb_range(ctx->n_q, K);
     CK_TRY(launch_ntt_strided(ctx, u + (size_t)L * N, polys, ext, pm, true));

@@ -119,12 +119,10 @@ bool blk_ring(const ckks_ctx *ctx);
 bool blk_rows(const ckks_ctx *ctx, size_t rows);
 // they are the faster encryption and decryption of `limbs` limbs
 bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs);
-// they are the faster ModUp of `count` ciphertexts at `level`
-bool blk_modups(const ckks_ctx *ctx, uint32_t level);
-// they are the faster key switching for a batch of `count` rotations at `level`
-bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count);
-// they take every key-switching step at `level`
+// they are the faster ModUp and key switching at `level`
 bool blk_switch(const ckks_ctx *ctx, uint32_t level);
+// they are the faster ModDown of `polys` polynomials at `level`
+bool blk_moddowns(const ckks_ctx *ctx, uint32_t level, uint32_t polys);
 // transform of `batch` groups of map.n rows from src (group stride src_stride rows) to dst; dst may be src
 ckks_status blk_ntt(ckks_ctx *ctx, uint64_t *dst, uint32_t dst_stride, const uint64_t *src, uint32_t src_stride,
                     uint32_t batch, const LimbMap &map, bool inverse);

@@ -591,22 +591,24 @@ bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs)
     return blk_ring(ctx) && ntt_uses_f64(ctx, limbs) && ctx->log_n < 14;
 }
 
-// the same for a ModUp (modup.hip: five launches)
-bool blk_modups(const ckks_ctx *ctx, uint32_t level)
+// the same for a ModDown of `polys` polynomials, by the rows it transforms back: 24 + 8 limbs, 1, 4 and 8 polynomials
+// 48, 53 and 54 us here against 30, 49 and 61 in two passes; 12 + 4 limbs, 4, 8 and 16 polynomials 44, 48 and 51
+// against 40, 48 and 60
+bool blk_moddowns(const ckks_ctx *ctx, uint32_t level, uint32_t polys)
 {
-    return blk_switch(ctx, level) && ctx->log_n < 14;
-}
-
-// the same for a batch of rotations: per rotation of 24 limbs 16 us here against 13 us in the fused two-pass kernels
-// (keyswitch.hip), but 70 us less for a single one
-bool blk_rotations(const ckks_ctx *ctx, uint32_t level, uint32_t count)
-{
-    return blk_switch(ctx, level) && (ctx->log_n < 14 || (size_t)count * (level + 1) <= 320);
+    return blk_ring(ctx) && f64_switch(ctx, level) && (ctx->log_n < 14 || (size_t)polys * (level + 1) >= 96);
 }
 
 bool blk_ring(const ckks_ctx *ctx) { return ctx->log_n >= blk::kMinLog && ctx->log_n <= blk::kMaxLog && !ctx->int_only; }
 
-bool blk_switch(const ckks_ctx *ctx, uint32_t level) { return blk_ring(ctx) && f64_switch(ctx, level); }
+// A ModUp and a batch of rotations: not at N = 2^14, where the two-pass kernels (modup.hip, keyswitch.hip) keep the q
+// rows of the key products on chip and their grids are not bound to whole rows.  24 + 8 limbs, 1, 9 and 32 rotations of
+// 24 limbs 100, 201 and 585 us with the whole-row ModDown against 76, 192 and 465 in two passes, of 8 limbs 85, 117 and
+// 266 against 52, 86 and 184; 12 + 4 limbs, 9 rotations of 8 limbs 96 against 85
+bool blk_switch(const ckks_ctx *ctx, uint32_t level)
+{
+    return blk_ring(ctx) && ctx->log_n < 14 && f64_switch(ctx, level);
+}
 
 ckks_status blk_ntt(ckks_ctx *ctx, uint64_t *dst, uint32_t dst_stride, const uint64_t *src, uint32_t src_stride,
                     uint32_t batch, const LimbMap &map, bool inverse)
