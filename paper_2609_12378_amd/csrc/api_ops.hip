@@ -190,7 +190,7 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
     if (!count) return CKKS_OK;
     const size_t N = ctx->n;
     const uint32_t polys = 2 * count;
-    if (blk_rows(ctx, (size_t)polys * l) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, polys, l, out, work);
+    if (blk_rescales(ctx, (size_t)polys * l) && ntt_uses_f64(ctx, l + 1)) return blk_rescale(ctx, c, polys, l, out, work);
     if (fused_rows_ok(ctx)) return fused_rescale(ctx, c, polys, l, out, nullptr, work);
     uint64_t *top = work, *r = top + (size_t)polys * N;
     // the top limb of every polynomial, then the same steps as one rescale over all of them
@@ -205,7 +205,7 @@ ckks_status rescale_many(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint3
 ckks_status rescale_each(ckks_ctx *ctx, const uint64_t *c, uint32_t count, uint32_t l, uint64_t *const *outs,
                          uint64_t *work)
 {
-    if (fused_rows_ok(ctx) && !(blk_rows(ctx, 2 * l) && ntt_uses_f64(ctx, l + 1)))
+    if (fused_rows_ok(ctx) && !(blk_rescales(ctx, 2 * l) && ntt_uses_f64(ctx, l + 1)))
         return fused_rescale(ctx, c, 2 * count, l, nullptr, outs, work);
     for (uint32_t r = 0; r < count; r++)
         CK_TRY(rescale_many(ctx, c + (size_t)r * 2 * (l + 1) * ctx->n, 1, l, outs[r], work));

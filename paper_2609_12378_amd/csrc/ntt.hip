@@ -680,7 +680,7 @@ ckks_status launch_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, 
     }
     const LimbMap map = limb_range(0, limbs);
     const bool f = use_f64(ctx, map);
-    if (f && blk_rows(ctx, (size_t)batch * limbs)) return blk_ntt_from_i64(ctx, m, out, batch, limbs);
+    if (f && blk_from_i64(ctx)) return blk_ntt_from_i64(ctx, m, out, batch, limbs);
     CK_TRY(launch_ntt_col_i64(ctx, m, out, batch, limbs));
     const double res = (double)batch * limbs * ctx->n, bf = f ? kOpsButterflyF64 : kOpsButterflyInt;
     prof_begin(ctx, K_NTT_FWD_ROW, 16.0 * batch * limbs * ctx->n, res * bf * s2 / 2);

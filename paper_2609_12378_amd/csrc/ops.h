@@ -115,8 +115,11 @@ ckks_status up_moddown(ckks_ctx *ctx, uint64_t *up, uint32_t polys, uint32_t lev
 // Whole rows per block (ring_block.hip): N = 2^12 .. 2^14, fp64 primes.
 // the ring has them and the fp64 arithmetic is not switched off
 bool blk_ring(const ckks_ctx *ctx);
-// they are the faster transform for a launch of `rows` rows
+// they are the faster transform for a launch of `rows` rows, the faster rescale to `rows` rows in all, the faster
+// transform of signed coefficients
 bool blk_rows(const ckks_ctx *ctx, size_t rows);
+bool blk_rescales(const ckks_ctx *ctx, size_t rows);
+bool blk_from_i64(const ckks_ctx *ctx);
 // they are the faster encryption and decryption of `limbs` limbs
 bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs);
 // they are the faster ModUp and key switching at `level`

@@ -2,9 +2,12 @@
 oracle on both sides of its rule, with the side it took read from the event profiler (a whole-row step has no column
 passes of its own).  Ciphertexts and keys are uniform residues.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
+import test_gpu_attention as attention
 from gpu_common import to_dev, to_host
 from test_gpu_ring_block import Env
 from workloads import rng, uniform_residues
@@ -67,3 +70,22 @@ def test_moddown_of_one_polynomial(env):
     dx = to_dev(x)
     assert np.array_equal(to_host(env.ctx.moddown(dx, 11)), env.ck.moddown(x, 11))
     assert launches(env.ctx, lambda: env.ctx.moddown(dx, 11))["ntt_inv_col"] == 1
+
+
+@pytest.mark.parametrize("polys,limbs", [(9, 7), (8, 8)])   # 63 rows in two passes, 64 whole
+def test_transforms(env, polys, limbs):
+    x = uniform_residues(env.g, env.ctx.q[:limbs], env.n, lead=(polys,))
+    t = env.ctx.ntt(to_dev(x))
+    for b in (0, polys - 1):
+        assert np.array_equal(to_host(t)[b], env.ck.ntt(x[b], list(range(limbs)))), b
+    seen = launches(env.ctx, lambda: env.ctx.intt(t))
+    assert np.array_equal(to_host(t), x)
+    assert ("ntt_inv_col" in seen) == (polys * limbs < 64), seen
+
+
+def test_rescales_of_many_ciphertexts():
+    # the weighted sums rescale 32 and 31 ciphertexts of six limbs at once (320 and 310 rows: whole rows); a single
+    # rescale never has 128.  The noise in the slots grows at most with N: twice the bounds of N = 2^13.
+    cfg = dataclasses.replace(attention.ATTN_TOY, name="attn14", log_n=14, tokens=32, head_dim=32)
+    es, eo = attention.run_parity(cfg, 1, 1, [0])
+    assert es <= 2.0 ** -28 and eo <= 2.0 ** -25

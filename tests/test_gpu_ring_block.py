@@ -1,7 +1,7 @@
 """The whole-row kernels of the rings N = 2^12 .. 2^14 bit for bit against the oracle, at the sizes where they can go
 wrong: each ring, short last digits, more source limbs than one sum of eight terms takes (9 special primes, a digit
-of 10), both sides of the rules that choose between them and the two-pass kernels at N = 2^14 (rows of a transform,
-rotations of a batch, limbs of an encryption), more blocks than the CUs, and an output that is an input's buffer.
+of 10), the same calls at N = 2^14, where transforms of many rows take them and the other steps the two-pass kernels,
+more blocks than the CUs, and an output that is an input's buffer.
 Ciphertexts and keys are uniform residues, which is all these steps see of them.
 """
 import ctypes
@@ -48,7 +48,7 @@ def env(request):
 
 @pytest.mark.parametrize("rows", [1, 3, 64])
 def test_transforms(env, rows):
-    limbs = min(env.n_q, 5)                      # 64 x 5 rows: past the 192 of N = 2^14
+    limbs = min(env.n_q, 5)                      # 64 x 5 rows: past the 64 of N = 2^14
     idx = list(range(limbs))
     x = uniform_residues(env.g, env.ctx.q[:limbs], env.n, lead=(rows,))
     t = env.ctx.ntt(to_dev(x))
