@@ -549,11 +549,12 @@ __global__ __launch_bounds__(64) void k_ks_finish8(RotArgs ra, const uint64_t *_
 
 // k_ks_finish8 with the inner products first, every position's loads issued before the transforms, and the addends'
 // gathers at the start: for seed-expanded keys (whose Philox blocks the loads then overlap), and with stored keys for
-// batches of at most kWideWaves waves, which cannot hide one position's loads behind another wave's work (an
-// evaluation step with two key switches of 1664 waves each at N = 2^16: 287 -> 277 us, this kernel 20 us of each).
-// Larger batches with stored keys take k_ks_finish8: this order needs 160 VGPRs, 3 waves per SIMD, and measured 5% slower there than one position at a time after the
-// transforms, 88 VGPRs and 5 waves, which streams ~5 TB/s of keys, converted rows and outputs.
-constexpr size_t kWideWaves = 3072;
+// batches of at most kWideWaves waves.  It needs 160 VGPRs (88 there), 3 waves per SIMD for 5: few waves cannot hide
+// one position's loads behind another wave's work, while 32 rotations of 24 limbs stream ~5 TB/s of keys, converted
+// rows and outputs with either and lose by the occupancy.  Whole batches, N = 2^16: 1536 waves 97.1 -> 91.3 us, 6144
+// waves (12 limbs) 181 -> 163, 24576 waves (24 and 12 limbs) 473 -> 467 and 464 -> 452, 36864 waves 685 -> 690 and
+// 648 -> 641, 49152 waves 834 -> 847 and 839 -> 835, 98304 waves 1560 -> 1596; N = 2^14 and 2^15 alike, six digits too.
+constexpr size_t kWideWaves = 24576;
 template <bool SEEDED, int ND>
 __global__ __launch_bounds__(64) void k_ks_finish8_wide(RotArgs ra, const uint64_t *__restrict__ cw, uint32_t nd,
                                                           uint32_t ext, uint32_t L, uint32_t key_rows,

@@ -1,7 +1,7 @@
 """The two-pass rings N = 2^15 and 2^16 bit for bit against the oracle where the fused passes can go wrong: digits of
 more than eight limbs, short last digits, 59-bit (integer) moduli, a chain whose top prime needs the integer arithmetic
-and the others do not, and both sides of the rule that splits small batches of rotations off (4 and 5 rotations of five
-limbs at N = 2^16).  Then the one-vector FFT of every ring size, and the projections that run several giant steps a
+and the others do not, and both sides of the rule that splits the largest batches of rotations off (27 and 28 rotations
+of seven limbs at N = 2^16).  Then the one-vector FFT of every ring size, and the projections that run several giant steps a
 launch.  Ciphertexts and keys are uniform residues.
 """
 import dataclasses
@@ -53,6 +53,18 @@ def test_rotations(env):
             outs = env.ctx.rotate_hoisted(env.buf(c), steps, [dev[r % 2] for r in range(count)])
             for r in sorted({0, count - 1}):
                 assert np.array_equal(to_host(outs[r].data), env.ck.rotate(c, steps[r], keys[r % 2])), (limbs, count, r)
+
+
+def test_finishing_kernels_of_large_batches():
+    # waves: 896 a rotation, the line at 24576
+    env = Env((16, 7, 3, 3, 50))
+    c, key = env.ct(7), env.key()
+    dev = to_dev(key)
+    for count in (27, 28):
+        steps = [1 + 3 * r for r in range(count)]
+        outs = env.ctx.rotate_hoisted(env.buf(c), steps, [dev] * count)
+        for r in (0, count - 1):
+            assert np.array_equal(to_host(outs[r].data), env.ck.rotate(c, steps[r], key)), (count, r)
 
 
 def test_mul_relin_rescale_modup_moddown(env):
