@@ -393,7 +393,8 @@ ckks_status ckks_attention_apply(ckks_ctx *ctx, const ckks_buf *p, uint32_t n_p,
 /* ---- measurement helpers ------------------------------------------------- */
 
 /* Per-kernel timing with HIP events on the context stream.  While enabled,
- * every kernel launch is bracketed by two events and tagged with its
+ * every kernel launch but the calibration probes' below is bracketed by two
+ * events and tagged with its
  * algorithmic HBM bytes (each input and output word once; cache-resident
  * tables excluded) and its nominal VALU lane instructions (the kernel's
  * arithmetic model: 11 per fp64 butterfly, 37 per integer one, plus the

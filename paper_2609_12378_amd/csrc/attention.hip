@@ -267,7 +267,9 @@ inline dim3 grid_of(size_t total) { return dim3((unsigned)((total + kThreads - 1
 
 ckks_status launch_masks(ckks_ctx *ctx, double *U, double *MQ, uint32_t D, uint32_t hd, double delta, uint32_t L)
 {
+    prof_begin(ctx, K_ELEM, 8.0 * D * hd);
     hipLaunchKernelGGL(k_attn_masks, grid_of((size_t)D * hd), dim3(kThreads), 0, ctx->stream, U, D, hd);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return launch_enc_vectors(ctx, U, D, hd, delta, L, MQ);
 }
@@ -280,21 +282,24 @@ ckks_status launch_corr_tables(ckks_ctx *ctx, uint32_t logn, uint32_t L, uint32_
                                double *Om, double *Omi, double *Mh)
 {
     const uint32_t n = 1u << logn;
+    prof_begin(ctx, K_ELEM, 16.0 * L * n);
     hipLaunchKernelGGL(k_attn_tw, grid_of((size_t)L * n), dim3(kThreads), 0, ctx->stream, Om, Omi, n, L,
                        (const double *)ctx->d_twf, (const double *)ctx->d_itwf, ctx->log_n);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
-    if (logn == 7)
-        hipLaunchKernelGGL(k_attn_mhat<7>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod);
-    else if (logn == 8)
-        hipLaunchKernelGGL(k_attn_mhat<8>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod);
-    else if (logn == 6)
-        hipLaunchKernelGGL(k_attn_mhat<6>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod);
-    else if (logn == 5)
-        hipLaunchKernelGGL(k_attn_mhat<5>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod);
-    else if (logn == 4)
-        hipLaunchKernelGGL(k_attn_mhat<4>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod);
-    else
-        return set_error(CKKS_EUNSUPPORTED, "attention: correlation length 2^%u outside [16, 256]", logn);
+    CK_REQUIRE(logn >= 4 && logn <= 8, CKKS_EUNSUPPORTED, "attention: correlation length 2^%u outside [16, 256]", logn);
+    prof_begin(ctx, K_ATTN_CORR, 8.0 * (double)L * D2 * (hd + n));
+#define CK_MHAT(LG)                                                                                                \
+    hipLaunchKernelGGL(k_attn_mhat<LG>, dim3(L * D2), dim3(kThreads), 0, ctx->stream, Mh, MQ, hd, D2, Om, ctx->d_mod)
+    switch (logn) {
+    case 4: CK_MHAT(4); break;
+    case 5: CK_MHAT(5); break;
+    case 6: CK_MHAT(6); break;
+    case 7: CK_MHAT(7); break;
+    default: CK_MHAT(8); break;
+    }
+#undef CK_MHAT
+    prof_end(ctx, K_ATTN_CORR);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }

@@ -686,8 +686,10 @@ ckks_status enc_ntt_first_pass(ckks_ctx *ctx, const SlotSource &src, uint32_t ba
 ckks_status enc_feat_of_pos(ckks_ctx *ctx, uint32_t tokens, uint32_t *out)
 {
     const uint32_t M = ctx->n / 2;
+    prof_begin(ctx, K_ELEM, 8.0 * M);
     hipLaunchKernelGGL(k_feat_of_pos, dim3((M + kThreads - 1) / kThreads), dim3(kThreads), 0, ctx->stream, out,
                        ctx->d_pos_slot, M, tokens);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -740,10 +742,14 @@ ckks_status dec_slots(ckks_ctx *ctx, const uint64_t *coef, uint32_t limbs, doubl
         return fft_one(ctx, work, o, nullptr, &d);
     }
     const dim3 grid((M + kThreads - 1) / kThreads);
+    prof_begin(ctx, K_ELEM, 16.0 * M * (d.limbs + 1.0));
     hipLaunchKernelGGL(k_decode_in, grid, dim3(kThreads), 0, ctx->stream, work, d, logm);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     CK_TRY(fft_passes(ctx, work, 1, FftOut{}, nullptr));
+    prof_begin(ctx, K_ELEM, 32.0 * M);
     hipLaunchKernelGGL(k_decode_out, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_slot_pos, logm, re, im);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }

@@ -262,9 +262,13 @@ template <bool F>
 ckks_status top_coeffs(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint32_t l, uint64_t *top)
 {
     const uint32_t per = 1u << (ctx->log_n - 11);
+    const double res = (double)polys * ctx->n, bf = F ? kOpsButterflyF64 : kOpsButterflyInt;
+    prof_begin(ctx, K_NTT_INV_ROW, 16.0 * res, res * bf * 4);
     hipLaunchKernelGGL(k_top_row<F>, dim3(polys * per), dim3(128), 0, ctx->stream, top, c, l + 1, l, ctx->log_n,
                        ctx->d_mod, inv<F>(ctx));
+    prof_end(ctx, K_NTT_INV_ROW);
     HIP_TRY(hipGetLastError());
+    prof_begin(ctx, K_NTT_INV_COL, 16.0 * res, res * bf * (ctx->log_n - 8) / 2);
 #define CK_COL(S)                                                                                                  \
     hipLaunchKernelGGL((k_top_col<S, F>), dim3(polys * (256 / (4096u >> S))), dim3(256), 0, ctx->stream, top, l,     \
                        ctx->log_n, ctx->d_mod, inv<F>(ctx))
@@ -276,8 +280,16 @@ ckks_status top_coeffs(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint32_
     default: CK_COL(8); break;
     }
 #undef CK_COL
+    prof_end(ctx, K_NTT_INV_COL);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
+}
+
+// brackets a row pass over `rows` rows with its fused element-wise work, `words` words moved a position
+void row_begin(ckks_ctx *ctx, bool f, double rows, double words)
+{
+    prof_begin(ctx, K_NTT_FWD_ROW, 8.0 * ctx->n * rows * words,
+               rows * ctx->n * (f ? kOpsButterflyF64 : kOpsButterflyInt) * 4);
 }
 
 }  // namespace
@@ -308,10 +320,13 @@ ckks_status fused_rescale(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint
     a.polys = polys;
     a.log_n = ctx->log_n;
     a.w = ctx->d_qlinv + (size_t)l * ctx->n_q;
-    if (ntt_uses_f64(ctx, l))
+    const bool f = ntt_uses_f64(ctx, l);
+    row_begin(ctx, f, (double)polys * l, 3.0);
+    if (f)
         launch_fin<true, FIN_RESCALE>(ctx, a, ra);
     else
         launch_fin<false, FIN_RESCALE>(ctx, a, ra);
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -338,12 +353,15 @@ ckks_status fused_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const
 {
     CK_TRY(launch_ntt_col_small(ctx, s, nullptr, work, limbs));
     const dim3 grid(limbs << (ctx->log_n - 11)), block(128);
-    if (ntt_uses_f64(ctx, limbs))
+    const bool f = ntt_uses_f64(ctx, limbs);
+    row_begin(ctx, f, limbs, 4.0);
+    if (f)
         hipLaunchKernelGGL((k_row_crypt<true, false>), grid, block, 0, ctx->stream, work, pt, (uint64_t *)nullptr, c0, c1,
                            limbs, ctx->log_n, ctx->d_mod, fwd<true>(ctx));
     else
         hipLaunchKernelGGL((k_row_crypt<false, false>), grid, block, 0, ctx->stream, work, pt, (uint64_t *)nullptr, c0,
                            c1, limbs, ctx->log_n, ctx->d_mod, fwd<false>(ctx));
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -353,12 +371,15 @@ ckks_status fused_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint6
 {
     CK_TRY(launch_ntt_col_small(ctx, s, e, work, limbs));
     const dim3 grid(limbs << (ctx->log_n - 11)), block(128);
-    if (ntt_uses_f64(ctx, limbs))
+    const bool f = ntt_uses_f64(ctx, limbs);
+    row_begin(ctx, f, 2.0 * limbs, 3.0);
+    if (f)
         hipLaunchKernelGGL((k_row_crypt<true, true>), grid, block, 0, ctx->stream, work, c0, c1, a, m, limbs, ctx->log_n,
                            ctx->d_mod, fwd<true>(ctx));
     else
         hipLaunchKernelGGL((k_row_crypt<false, true>), grid, block, 0, ctx->stream, work, c0, c1, a, m, limbs, ctx->log_n,
                            ctx->d_mod, fwd<false>(ctx));
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }

@@ -219,8 +219,10 @@ ckks_status launch_mul_plain(ckks_ctx *ctx, uint64_t *out, const uint64_t *ct, c
 {
     const size_t total = ((size_t)polys * limbs) << ctx->log_n;
     if (!total) return CKKS_OK;
+    prof_begin(ctx, K_ELEM, 8.0 * total * (2.0 + 1.0 / polys));
     hipLaunchKernelGGL(k_mul_plain, grid_for(total), dim3(kThreads), 0, ctx->stream, out, ct, pt, total, ctx->log_n,
                        limbs, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -240,8 +242,10 @@ ckks_status launch_tensor_batch(ckks_ctx *ctx, uint64_t *d0, uint64_t *d1, uint6
     CK_REQUIRE(count <= 65535u, CKKS_EINVAL, "tensor-product batch of %u entries exceeds 65535", count);
     dim3 grid = grid_for(total);
     grid.y = count;
+    prof_begin(ctx, K_ELEM, 8.0 * total * count * 7.0);
     hipLaunchKernelGGL(k_tensor, grid, dim3(kThreads), 0, ctx->stream, d0, d1, d2, a, b, total, ctx->log_n,
                        ctx->d_mod, d_stride, a_stride, b_stride);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -250,7 +254,9 @@ ckks_status launch_automorph(ckks_ctx *ctx, const uint64_t *in, uint64_t *out, u
 {
     const size_t total = (size_t)rows << ctx->log_n;
     if (!total) return CKKS_OK;
+    prof_begin(ctx, K_ELEM, 16.0 * total);
     hipLaunchKernelGGL(k_automorph, grid_for(total), dim3(kThreads), 0, ctx->stream, out, in, total, ctx->log_n, g);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -258,8 +264,10 @@ ckks_status launch_automorph(ckks_ctx *ctx, const uint64_t *in, uint64_t *out, u
 ckks_status launch_expand_i8(ckks_ctx *ctx, uint64_t *out, const int8_t *v, const LimbMap &map)
 {
     const size_t total = (size_t)map.n << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 8.0 * total + ctx->n);
     hipLaunchKernelGGL(k_expand<int8_t>, grid_for(total), dim3(kThreads), 0, ctx->stream, out, v, total, ctx->log_n,
                        map, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -267,8 +275,10 @@ ckks_status launch_expand_i8(ckks_ctx *ctx, uint64_t *out, const int8_t *v, cons
 ckks_status launch_expand_i32(ckks_ctx *ctx, uint64_t *out, const int32_t *v, const LimbMap &map)
 {
     const size_t total = (size_t)map.n << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 8.0 * total + 4.0 * ctx->n);
     hipLaunchKernelGGL(k_expand<int32_t>, grid_for(total), dim3(kThreads), 0, ctx->stream, out, v, total,
                        ctx->log_n, map, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -277,8 +287,10 @@ ckks_status launch_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint
                            const uint64_t *e, const uint64_t *m, const LimbMap &map)
 {
     const size_t total = (size_t)map.n << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 8.0 * total * (m ? 6.0 : 5.0));
     hipLaunchKernelGGL(k_encrypt, grid_for(total), dim3(kThreads), 0, ctx->stream, c0, c1, a, s, e, m, total,
                        ctx->log_n, map, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -288,8 +300,10 @@ ckks_status launch_keygen_digit(ckks_ctx *ctx, uint64_t *b_out, uint64_t *a_out,
                                 uint32_t dig_hi)
 {
     const size_t total = (size_t)ctx->n_primes() << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 8.0 * total * (a_out ? 6.0 : 5.0));
     hipLaunchKernelGGL(k_keygen, grid_for(total), dim3(kThreads), 0, ctx->stream, b_out, a_out, a, s, e, t,
                        ctx->d_pmodq, dig_lo, dig_hi, total, ctx->log_n, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -297,8 +311,10 @@ ckks_status launch_keygen_digit(ckks_ctx *ctx, uint64_t *b_out, uint64_t *a_out,
 ckks_status launch_rescale_centre(ckks_ctx *ctx, uint64_t *top, uint32_t polys, uint32_t l)
 {
     const size_t total = (size_t)polys << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 16.0 * total);
     hipLaunchKernelGGL(k_rescale_centre, grid_for(total), dim3(kThreads), 0, ctx->stream, top, total,
                        ctx->primes[l]);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -307,8 +323,10 @@ ckks_status launch_rescale_finish(ckks_ctx *ctx, uint64_t *out, const uint64_t *
                                   uint32_t polys, uint32_t l)
 {
     const size_t total = ((size_t)polys * l) << ctx->log_n;
+    prof_begin(ctx, K_ELEM, 24.0 * total);
     hipLaunchKernelGGL(k_rescale_finish, grid_for(total), dim3(kThreads), 0, ctx->stream, out, c, r, total,
                        ctx->log_n, l, ctx->d_qlinv + (size_t)l * ctx->n_q, ctx->d_mod);
+    prof_end(ctx, K_ELEM);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }

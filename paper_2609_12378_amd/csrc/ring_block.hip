@@ -652,9 +652,12 @@ ckks_status blk_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uin
 ckks_status blk_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_t *a, const int8_t *s,
                         const int32_t *e, const uint64_t *m, uint32_t limbs)
 {
+    const double res = (double)limbs * ctx->n;
+    prof_begin(ctx, K_NTT_FWD_ROW, 32.0 * res + 5.0 * ctx->n, res * kOpsButterflyF64 * ctx->log_n);
 #define CK_K(LG) k_blk_encrypt<LG>
     CK_BLK(CK_K, dim3(limbs), c0, c1, a, s, e, m, tab_of(ctx));
 #undef CK_K
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -662,9 +665,12 @@ ckks_status blk_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_
 ckks_status blk_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const uint64_t *c1, const int8_t *s,
                         uint32_t limbs)
 {
+    const double res = (double)limbs * ctx->n;
+    prof_begin(ctx, K_NTT_FWD_ROW, 24.0 * res + ctx->n, res * kOpsButterflyF64 * ctx->log_n / 2);
 #define CK_K(LG) k_blk_decrypt<LG>
     CK_BLK(CK_K, dim3(limbs), pt, c0, c1, s, tab_of(ctx));
 #undef CK_K
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
@@ -674,15 +680,20 @@ ckks_status blk_rescale(ckks_ctx *ctx, const uint64_t *c, uint32_t polys, uint32
     const Tab tb = tab_of(ctx);
     double *top = (double *)work;
     const ulonglong2 *qlinv = ctx->d_qlinv + (size_t)l * ctx->n_q;
+    const double res = (double)polys * ctx->n, bf = kOpsButterflyF64 * ctx->log_n / 2;
+    prof_begin(ctx, K_NTT_INV_ROW, 16.0 * res, res * bf);
 #define CK_K(LG) k_blk_rescale_top<LG>
     CK_BLK(CK_K, dim3(polys), top, c, l, tb);
 #undef CK_K
+    prof_end(ctx, K_NTT_INV_ROW);
     HIP_TRY(hipGetLastError());
+    prof_begin(ctx, K_NTT_FWD_ROW, 8.0 * res * (1 + 2.0 * l), res * l * bf);
 #define CK_E(LG) k_blk_rescale<LG, (LG <= 13)>
 #define CK_L(LG) k_blk_rescale<LG, false>
     CK_BLK_E((size_t)polys * l, dim3(polys * l), out, c, top, l, qlinv, tb);
 #undef CK_E
 #undef CK_L
+    prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
     return CKKS_OK;
 }
