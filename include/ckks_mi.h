@@ -329,8 +329,11 @@ ckks_status ckks_linear_project(ckks_ctx *ctx, const ckks_buf *in, const double 
  * Keys: steps b (0 < b < n1), b - D (0 <= b < n1) and n1 g (0 < g < n2).
  * Needs every prime below 2^50.  Arguments, scales and errors as for
  * ckks_linear_project; scratch: ckks_workspace_bytes with
- * CKKS_OP_LINEAR_PROJECT_TM; a workspace with less room is used with fewer giant steps per launch (down to one,
- * below which the call is refused). */
+ * CKKS_OP_LINEAR_PROJECT_TM; a workspace with less room is used with fewer
+ * giant steps per launch (down to one, below which the call is refused), and
+ * so is a device without the room for the library's own arena: a size that it
+ * has refused is not asked for again until a call that cannot do with less
+ * gets as much, or ckks_set_workspace gives the arena back. */
 ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in, const double *dev_W,
                                    const ckks_proj_shape *shape, const int32_t *key_steps,
                                    const uint64_t *const *dev_keys, uint32_t n_keys, ckks_buf *out);

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "ckks_mi.h"
+#include "arena.h"
 #include "modarith.h"
 
 // ---------------------------------------------------------------- errors ----
@@ -98,10 +99,7 @@ struct ckks_ctx {
     ulonglong2 *d_pmodq = nullptr;       // [n_q] ([P]_{q_i}, Shoup)
     ulonglong2 *d_qlinv = nullptr;       // [n_q][n_q] (q_l^-1 mod q_i, Shoup) row l
 
-    // grow-only scratch arena
-    void *scratch = nullptr;
-    size_t scratch_bytes = 0;
-    bool scratch_external = false;  // the arena is a caller's workspace (ckks_set_workspace): never reallocated
+    Arena arena;                    // scratch of the calls
 
     // optional per-kernel event profiling
     bool profiling = false;

@@ -331,25 +331,30 @@ static ckks_status build_all_conv(ckks_ctx *c)
 ckks_status ctx_scratch(ckks_ctx *c, size_t bytes, void **out)
 {
     if (bytes == SIZE_MAX) return set_error(CKKS_EINVAL, "workspace size of an invalid shape");
-    if (bytes > c->scratch_bytes && c->scratch_external)
-        return set_error(CKKS_ENOMEM, "workspace of %zu bytes is too small: this call needs %zu", c->scratch_bytes,
-                         bytes);
-    if (bytes > c->scratch_bytes) {
-        if (c->scratch) {
-            HIP_TRY(hipStreamSynchronize(c->stream));
-            HIP_TRY(hipFree(c->scratch));
-            c->scratch = nullptr;
-            c->scratch_bytes = 0;
+    struct Runtime {
+        hipStream_t stream;
+        hipError_t e = hipSuccess;
+        bool release(void *p)
+        {
+            e = hipStreamSynchronize(stream);
+            if (e == hipSuccess) e = hipFree(p);
+            return e == hipSuccess;
         }
-        const size_t sz = (bytes + 255) & ~(size_t)255;
-        hipError_t e = hipMalloc(&c->scratch, sz);
-        if (e != hipSuccess) {
-            c->scratch = nullptr;
-            return set_error(CKKS_ENOMEM, "scratch arena of %zu bytes: %s", sz, hipGetErrorString(e));
+        void *allocate(size_t n)
+        {
+            void *p = nullptr;
+            e = hipMalloc(&p, n);
+            return e == hipSuccess ? p : nullptr;
         }
-        c->scratch_bytes = sz;
+    } rt{c->stream};
+    switch (c->arena.take(bytes, rt)) {
+    case Arena::TOO_SMALL:
+        return set_error(CKKS_ENOMEM, "workspace of %zu bytes is too small: this call needs %zu", c->arena.bytes, bytes);
+    case Arena::NO_ROOM: return set_error(CKKS_ENOMEM, "scratch arena of %zu bytes: %s", bytes, hipGetErrorString(rt.e));
+    case Arena::RELEASE_FAILED: HIP_TRY(rt.e); break;
+    default: break;
     }
-    *out = c->scratch;
+    *out = c->arena.base;
     return CKKS_OK;
 }
 
@@ -473,10 +478,10 @@ void ckks_ctx_destroy(ckks_ctx *c)
     if (!c) return;
     (void)hipDeviceSynchronize();
     (void)prof_collect(c);
-    if (c->scratch_external) c->scratch = nullptr;  // the caller's workspace
+    if (c->arena.external) c->arena.base = nullptr;  // the caller's workspace
     void *ptrs[] = {c->d_mod, c->d_tw, c->d_itw, c->d_twf, c->d_itwf, c->d_fft_w, c->d_fft_wc, c->d_fft_twist, c->d_slot_pos,
                     c->d_pos_slot,
-                    c->d_pinv, c->d_pmodq, c->d_qlinv, c->scratch};
+                    c->d_pinv, c->d_pmodq, c->d_qlinv, c->arena.base};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &kv : c->conv) {
@@ -552,10 +557,8 @@ ckks_status ckks_set_workspace(ckks_ctx *c, void *dev, size_t bytes)
                "set_workspace: dev and bytes must be both set or both zero");
     CK_REQUIRE(((uintptr_t)dev & 255) == 0, CKKS_EINVAL, "set_workspace: dev must be 256-byte aligned");
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (c->scratch && !c->scratch_external) HIP_TRY(hipFree(c->scratch));
-    c->scratch = dev;
-    c->scratch_bytes = bytes;
-    c->scratch_external = dev != nullptr;
+    if (c->arena.base && !c->arena.external) HIP_TRY(hipFree(c->arena.base));
+    c->arena.set(dev, bytes);
     return CKKS_OK;
 }
 

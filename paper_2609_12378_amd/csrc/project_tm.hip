@@ -731,15 +731,21 @@ extern "C" ckks_status ckks_linear_project_tm(ckks_ctx *ctx, const ckks_buf *in,
     const size_t N = ctx->n, ctw = 2 * (size_t)L * N;
     TmScratch ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1);
     void *w;
-    ckks_status st = ctx_scratch(ctx, ts.total * 8, &w);
+    ckks_status st = CKKS_OK;
     // a workspace or a card without the room for several giant steps per launch: fewer of them, down to one
-    while (st == CKKS_ENOMEM && ts.G > 1) {
-        (void)hipGetLastError();
-        clear_error();
-        ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1, ts.G / 2);
-        st = ctx_scratch(ctx, ts.total * 8, &w);
-    }
+    const uint32_t G = most_groups(
+        ctx->arena, ts.G,
+        [&](uint32_t g) { return tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1, g).total * 8; },
+        [&](size_t bytes) {
+            if (st == CKKS_ENOMEM) {   // the runtime's and the library's record of the larger request
+                (void)hipGetLastError();
+                clear_error();
+            }
+            st = ctx_scratch(ctx, bytes, &w);
+            return st != CKKS_ENOMEM;
+        });
     CK_TRY(st);
+    ts = tm_scratch(ctx, L, D, shape->d_in, shape->d_out, n1, G);
     uint64_t *x2 = (uint64_t *)w;  // [n_in][n1][xr, xw][2][L][N]
     uint64_t *acc = x2 + ts.x2_w;
     uint64_t *tot = acc + ts.acc_w;
