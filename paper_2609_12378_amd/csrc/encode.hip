@@ -463,8 +463,9 @@ __global__ __launch_bounds__(512, 4) void ntt_col8_from_fft(const double2 *__res
 #pragma unroll
     for (int k = 0; k < kE8; k++) {
         vd[k] = mt[nttc::u8<0>(t, k) * MT_PITCH + col];
-        big |= fabs(vd[k]) > 4503599627370496.0;
-        wide |= fabs(vd[k]) > smalld;
+        // negated, so that a NaN (no coefficient has one, unless a weight does) takes the conversion of the large ones
+        big |= !(fabs(vd[k]) <= 4503599627370496.0);
+        wide |= !(fabs(vd[k]) <= smalld);
     }
     // every coefficient of the wave below every limb's q/2 (weights at the usual scales): its range reduction is
     // the identity, so the wave skips it for all limbs

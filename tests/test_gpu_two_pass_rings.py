@@ -139,6 +139,26 @@ def test_token_major_weights_beyond_2_52(monkeypatch):
     assert tm.run_case(TOY, TOY.feats, TOY.feats, 16, [0]) <= 2.0 ** (18 - 12)
 
 
+@pytest.mark.parametrize("log_n", [15, 16])
+def test_a_nan_weight_stays_in_its_plaintext(log_n):
+    # its diagonal's transform is all NaN, which the integer conversion of a coefficient takes to zero: as if the diagonal
+    # W[(o + 1) mod D][o] were zero, and canonical residues everywhere
+    require_gpu()
+    from paper_2609_12378_amd import Buf, Context
+    D, n1, L = 4, 2, 2
+    ctx = Context(log_n, 2, 1, 2, q_bits=50)
+    T = ctx.n // 2 // D
+    g = rng(61, 2)
+    W = g.normal(0, 0.02, (D, D))
+    Z = W.copy()
+    Z[(np.arange(D) + 1) % D, np.arange(D)] = 0.0
+    W[2, 1] = np.nan
+    ct = Buf(to_dev(uniform_residues(g, ctx.q[:L], ctx.n, lead=(2,))), 2.0 ** 40)
+    key = to_dev(uniform_residues(g, ctx.primes, ctx.n, lead=(2, 2)))
+    out = [to_host(ctx.linear_project([ct], to_dev(M), T, n1, {T: key, 2 * T: key})[0].data) for M in (W, Z)]
+    assert np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("lazy", [False, True])
 @pytest.mark.parametrize("n1", [16, 24])
 def test_feature_major_giant_step_groups(n1, lazy):
