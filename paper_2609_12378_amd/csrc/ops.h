@@ -112,7 +112,7 @@ ckks_status up_modup(ckks_ctx *ctx, const uint64_t *c1, size_t stride, uint32_t 
 // converts to the level's q limbs and runs the first forward pass into cw ([polys][level+1][N] raw doubles)
 ckks_status up_moddown(ckks_ctx *ctx, uint64_t *up, uint32_t polys, uint32_t level, uint64_t *cw);
 
-// Whole rows per block (ring_block.hip): N = 2^12 .. 2^14, fp64 primes.
+// Whole rows per block (ring_block.hip): fp64 primes, N = 2^12 and 2^13, at 2^14 for launches of many rows.
 // the ring has them and the fp64 arithmetic is not switched off
 bool blk_ring(const ckks_ctx *ctx);
 // they are the faster transform for a launch of `rows` rows, the faster rescale to `rows` rows in all, the faster

@@ -1,9 +1,10 @@
-// The small and medium rings, N = 2^12 .. 2^14 with fp64 arithmetic (every prime below 2^50): every step that
-// transforms a row runs as one launch with one block per row (ntt_block.h), the row's producer and consumer in the
-// same kernel.  A rotation is five launches (digits of c1; converted and transformed digits; key inner products;
+// The small and medium rings with fp64 arithmetic (every prime below 2^50): steps that transform a row run as one launch
+// with one block per row (ntt_block.h), the row's producer and consumer in the same kernel.  For N = 2^12 and 2^13 that
+// is every step: a rotation is five launches (digits of c1; converted and transformed digits; key inner products;
 // digits of their P rows; ModDown), a rescale two, an encryption or decryption one.  At these sizes a two-pass
 // transform with an element-wise kernel on either side is bounded by its launches (about 4-5 us each, whatever the
-// row count up to a few hundred); with many rows it moves each row through HBM four to six times.
+// row count up to a few hundred); with many rows it moves each row through HBM four to six times.  At N = 2^14 it is the
+// transforms, rescales and ModDowns of many rows (blk_rows, blk_rescales, blk_moddowns).
 #include <algorithm>
 
 #include "ckks_internal.h"
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT) void k_blk_encrypt(uint64_t *
     const double *tw = table<LOGN>(tb.twf, l);
     const blk::ColTw<LOGN> cw(tw);
     const size_t row = (size_t)l << LOGN;
-    const Words<LOGN, LOGN <= 13> aw(a + row);
+    const Words<LOGN, true> aw(a + row);
     double x[kE], p[kE];
 #pragma unroll
     for (int k = 0; k < kE; k++) x[k] = (double)s[blk::col_pos<LOGN>(t, k)];
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT) void k_blk_encrypt(uint64_t *
     for (int k = 0; k < kE; k++) p[k] = ar.mul(x[k], A::from_u64(aw.get(k)));
 #pragma unroll
     for (int k = 0; k < kE; k++) x[k] = (double)e[blk::col_pos<LOGN>(t, k)];
-    const Words<LOGN, LOGN <= 13> mw(m + row);
+    const Words<LOGN, true> mw(m + row);
     __syncthreads();
     {
         const blk::RowTw<LOGN> rw(tw);
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT) void k_blk_decrypt(uint64_t *
     const blk::ColTw<LOGN> cw(table<LOGN>(tb.twf, l));
     const blk::RowTw<LOGN> rw(table<LOGN>(tb.twf, l));
     const size_t row = (size_t)l << LOGN;
-    const Words<LOGN, LOGN <= 13> w0(c0 + row), w1(c1 + row);
+    const Words<LOGN, true> w0(c0 + row), w1(c1 + row);
     double x[kE];
 #pragma unroll
     for (int k = 0; k < kE; k++) x[k] = (double)s[blk::col_pos<LOGN>(t, k)];
@@ -525,7 +526,14 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4) void k_blk_fin
 
 Tab tab_of(const ckks_ctx *ctx) { return Tab{ctx->d_mod, ctx->d_twf, ctx->d_itwf}; }
 
-// one launch for the context's ring degree
+// one launch for the context's ring degree; CK_BLK13: of the steps that N = 2^14 does not take
+#define CK_BLK13(KERNEL, GRID, ...)                                                                                \
+    do {                                                                                                           \
+        if (ctx->log_n == 12)                                                                                      \
+            hipLaunchKernelGGL((KERNEL(12)), GRID, dim3(blk::Shape<12>::NT), 0, ctx->stream, __VA_ARGS__);           \
+        else                                                                                                       \
+            hipLaunchKernelGGL((KERNEL(13)), GRID, dim3(blk::Shape<13>::NT), 0, ctx->stream, __VA_ARGS__);           \
+    } while (0)
 #define CK_BLK(KERNEL, GRID, ...)                                                                                  \
     do {                                                                                                           \
         switch (ctx->log_n) {                                                                                      \
@@ -544,6 +552,13 @@ bool early_loads(const ckks_ctx *ctx, size_t blocks) { return ctx->log_n <= 13 &
             CK_BLK(CK_E, GRID, __VA_ARGS__);                                                                       \
         else                                                                                                       \
             CK_BLK(CK_L, GRID, __VA_ARGS__);                                                                       \
+    } while (0)
+#define CK_BLK13_E(BLOCKS, GRID, ...)                                                                              \
+    do {                                                                                                           \
+        if (early_loads(ctx, BLOCKS))                                                                              \
+            CK_BLK13(CK_E, GRID, __VA_ARGS__);                                                                     \
+        else                                                                                                       \
+            CK_BLK13(CK_L, GRID, __VA_ARGS__);                                                                     \
     } while (0)
 
 ckks_status launch_moddown_p(ckks_ctx *ctx, uint64_t *u, uint32_t polys, uint32_t L, uint32_t K, const ConvDev *cd)
@@ -642,7 +657,7 @@ ckks_status blk_ntt_from_i64(ckks_ctx *ctx, const int64_t *m, uint64_t *out, uin
     const double res = (double)batch * limbs * ctx->n;
     prof_begin(ctx, K_NTT_FWD_ROW, 8.0 * batch * ctx->n * (1 + limbs), res * kOpsButterflyF64 * ctx->log_n / 2);
 #define CK_K(LG) k_blk_from_i64<LG>
-    CK_BLK(CK_K, dim3(batch * limbs), m, out, limbs, tab_of(ctx));
+    CK_BLK13(CK_K, dim3(batch * limbs), m, out, limbs, tab_of(ctx));
 #undef CK_K
     prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
@@ -655,7 +670,7 @@ ckks_status blk_encrypt(ckks_ctx *ctx, uint64_t *c0, uint64_t *c1, const uint64_
     const double res = (double)limbs * ctx->n;
     prof_begin(ctx, K_NTT_FWD_ROW, 32.0 * res + 5.0 * ctx->n, res * kOpsButterflyF64 * ctx->log_n);
 #define CK_K(LG) k_blk_encrypt<LG>
-    CK_BLK(CK_K, dim3(limbs), c0, c1, a, s, e, m, tab_of(ctx));
+    CK_BLK13(CK_K, dim3(limbs), c0, c1, a, s, e, m, tab_of(ctx));
 #undef CK_K
     prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
@@ -668,7 +683,7 @@ ckks_status blk_decrypt(ckks_ctx *ctx, uint64_t *pt, const uint64_t *c0, const u
     const double res = (double)limbs * ctx->n;
     prof_begin(ctx, K_NTT_FWD_ROW, 24.0 * res + ctx->n, res * kOpsButterflyF64 * ctx->log_n / 2);
 #define CK_K(LG) k_blk_decrypt<LG>
-    CK_BLK(CK_K, dim3(limbs), pt, c0, c1, s, tab_of(ctx));
+    CK_BLK13(CK_K, dim3(limbs), pt, c0, c1, s, tab_of(ctx));
 #undef CK_K
     prof_end(ctx, K_NTT_FWD_ROW);
     HIP_TRY(hipGetLastError());
@@ -725,23 +740,23 @@ ckks_status blk_modup(ckks_ctx *ctx, const uint64_t *c1, size_t stride, const ui
         double *yr = y + (size_t)r0 * dg.L * N;
         prof_begin(ctx, K_NTT_INV_ROW, 16.0 * cnt * dg.L * N);
 #define CK_K(LG) k_blk_digits<LG, true>
-        if (b) CK_BLK(CK_K, dim3(dg.L, cnt), yr, src, dg, tb);
+        if (b) CK_BLK13(CK_K, dim3(dg.L, cnt), yr, src, dg, tb);
 #undef CK_K
 #define CK_K(LG) k_blk_digits<LG, false>
-        if (!b) CK_BLK(CK_K, dim3(dg.L, cnt), yr, src, dg, tb);
+        if (!b) CK_BLK13(CK_K, dim3(dg.L, cnt), yr, src, dg, tb);
 #undef CK_K
         prof_end(ctx, K_NTT_INV_ROW);
         HIP_TRY(hipGetLastError());
         prof_begin(ctx, K_CONV, 8.0 * cnt * N * (2.0 * dg.L + (double)dg.nd * ext));
         const size_t blocks = (size_t)ext * dg.nd * cnt;
-#define CK_E(LG) k_blk_modup<LG, true, (LG <= 13)>
+#define CK_E(LG) k_blk_modup<LG, true, true>
 #define CK_L(LG) k_blk_modup<LG, true, false>
-        if (b) CK_BLK_E(blocks, dim3(ext, dg.nd, cnt), d, yr, src, dg, tb);
+        if (b) CK_BLK13_E(blocks, dim3(ext, dg.nd, cnt), d, yr, src, dg, tb);
 #undef CK_E
 #undef CK_L
-#define CK_E(LG) k_blk_modup<LG, false, (LG <= 13)>
+#define CK_E(LG) k_blk_modup<LG, false, true>
 #define CK_L(LG) k_blk_modup<LG, false, false>
-        if (!b) CK_BLK_E(blocks, dim3(ext, dg.nd, cnt), d, yr, src, dg, tb);
+        if (!b) CK_BLK13_E(blocks, dim3(ext, dg.nd, cnt), d, yr, src, dg, tb);
 #undef CK_E
 #undef CK_L
         prof_end(ctx, K_CONV);
@@ -762,14 +777,14 @@ ckks_status blk_rotate_batch(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, u
     prof_begin(ctx, K_MODDOWN, 8.0 * count * ctx->n * (2.0 * K + 7.0 * L));
     const dim3 grid(L, 2, count);
     const size_t blocks = (size_t)L * 2 * count;
-#define CK_E(LG) k_blk_finish<LG, ADD_TENSOR, (LG <= 13)>
+#define CK_E(LG) k_blk_finish<LG, ADD_TENSOR, true>
 #define CK_L(LG) k_blk_finish<LG, ADD_TENSOR, false>
-    if (ta) CK_BLK_E(blocks, grid, ra, work, L, K, cd->d_qhat_mod_f, ctx->d_pinv, ta, tb2, tb);
+    if (ta) CK_BLK13_E(blocks, grid, ra, work, L, K, cd->d_qhat_mod_f, ctx->d_pinv, ta, tb2, tb);
 #undef CK_E
 #undef CK_L
-#define CK_E(LG) k_blk_finish<LG, ADD_ROWS, (LG <= 13)>
+#define CK_E(LG) k_blk_finish<LG, ADD_ROWS, true>
 #define CK_L(LG) k_blk_finish<LG, ADD_ROWS, false>
-    if (!ta) CK_BLK_E(blocks, grid, ra, work, L, K, cd->d_qhat_mod_f, ctx->d_pinv, ta, tb2, tb);
+    if (!ta) CK_BLK13_E(blocks, grid, ra, work, L, K, cd->d_qhat_mod_f, ctx->d_pinv, ta, tb2, tb);
 #undef CK_E
 #undef CK_L
     prof_end(ctx, K_MODDOWN);
