@@ -271,13 +271,11 @@ class Context:
     def zeros(self, n_polys: int, n_limbs: int) -> torch.Tensor:
         return torch.zeros((n_polys, n_limbs, self.n), dtype=torch.uint64, device="cuda")
 
-    def _empty(self, n_polys: int, n_limbs: int) -> torch.Tensor:
-        """An output buffer: the call it is for writes every word, so it is not cleared first (a fill of a level-12
-        ciphertext costs 6 us, of the 32 outputs of a hoisted batch a tenth of the batch).  A program that replaced
-        `zeros` by its own allocation gets that."""
-        if "zeros" in self.__dict__ or type(self).zeros is not Context.zeros:
-            return self.zeros(n_polys, n_limbs)
-        return torch.empty((n_polys, n_limbs, self.n), dtype=torch.uint64, device="cuda")
+    def _empty(self, like: torch.Tensor, n_polys: int, n_limbs: int) -> torch.Tensor:
+        """An output buffer on the device of the input `like`: the call it is for writes every word, so it is not
+        cleared first (a fill of a level-12 ciphertext costs 6 us, of the 32 outputs of a hoisted batch a tenth of the
+        batch)."""
+        return torch.empty((n_polys, n_limbs, self.n), dtype=torch.uint64, device=like.device)
 
     # ---------------- transforms ----------------
     def ntt(self, t: torch.Tensor, limb0: int = 0, inverse: bool = False):
@@ -297,13 +295,13 @@ class Context:
     # ---------------- encoding ----------------
     def encode(self, re: torch.Tensor, im: Optional[torch.Tensor], scale: float, n_limbs: int,
                out: Optional[torch.Tensor] = None) -> Buf:
-        out = self._empty(1, n_limbs) if out is None else out
+        pr = _arg(re, "encode re", torch.float64, numel=self.n // 2)
+        pi = None if im is None else _arg(im, "encode im", torch.float64, numel=self.n // 2)
+        out = self._empty(re, 1, n_limbs) if out is None else out
         b = Buf(out, scale)
         cb = b.c(self.n)
         if out.shape[1] != n_limbs or out.shape[0] != 1:
             raise CkksError("encode: output shape %s, expected (1, %d, %d)" % (tuple(out.shape), n_limbs, self.n))
-        pr = _arg(re, "encode re", torch.float64, numel=self.n // 2)
-        pi = None if im is None else _arg(im, "encode im", torch.float64, numel=self.n // 2)
         _check(self.lib.ckks_encode(self.h, pr, pi, float(scale), n_limbs, ctypes.byref(cb)), "ckks_encode")
         return b
 
@@ -320,7 +318,7 @@ class Context:
         ps = _arg(s, "secret", torch.int8, numel=self.n)
         pa = _arg(a, "encryption a", torch.uint64, numel=pt.n_limbs * self.n)
         pe = _arg(e, "encryption error", torch.int32, numel=self.n)
-        out = Buf(self._empty(2, pt.n_limbs), pt.scale)
+        out = Buf(self._empty(pt.data, 2, pt.n_limbs), pt.scale)
         co = out.c(self.n)
         _check(self.lib.ckks_encrypt_sk(self.h, ps, ctypes.byref(cp), pa, pe, ctypes.byref(co)), "ckks_encrypt_sk")
         return out
@@ -328,7 +326,7 @@ class Context:
     def decrypt(self, s: torch.Tensor, ct: Buf) -> Buf:
         ci = ct.c(self.n)
         ps = _arg(s, "secret", torch.int8, numel=self.n)
-        out = Buf(self._empty(1, ct.n_limbs), ct.scale)
+        out = Buf(self._empty(ct.data, 1, ct.n_limbs), ct.scale)
         co = out.c(self.n)
         _check(self.lib.ckks_decrypt(self.h, ps, ctypes.byref(ci), ctypes.byref(co)), "ckks_decrypt")
         return out
@@ -382,7 +380,7 @@ class Context:
         if any(len(sd_) != 2 for sd_ in seeds):
             raise CkksError("a key seed is two 64-bit words")
         if outs is None:
-            outs = [Buf(self._empty(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
+            outs = [Buf(self._empty(ct.data, 2, ct.n_limbs), ct.scale) for _ in range(cnt)]
         st = (ctypes.c_int32 * max(1, cnt))(*steps)
         ob = (_Buf * max(1, cnt))(*[o.c(self.n) for o in outs])
         ci = ct.c(self.n)
@@ -411,7 +409,7 @@ class Context:
     # ---------------- ciphertext operations ----------------
     def _binop(self, name, a: Buf, b: Buf, out_scale: float, out_limbs: int) -> Buf:
         ca, cb = a.c(self.n), b.c(self.n)
-        out = Buf(self._empty(2, out_limbs), out_scale)
+        out = Buf(self._empty(a.data, 2, out_limbs), out_scale)
         co = out.c(self.n)
         _check(getattr(self.lib, name)(self.h, ctypes.byref(ca), ctypes.byref(cb), ctypes.byref(co)), name)
         return out
@@ -424,7 +422,7 @@ class Context:
 
     def mul_relin(self, a: Buf, b: Buf, rlk: torch.Tensor) -> Buf:
         ca, cb, pk = a.c(self.n), b.c(self.n), self._key(rlk, "relinearisation key")
-        out = Buf(self._empty(2, a.n_limbs), a.scale * b.scale)
+        out = Buf(self._empty(a.data, 2, a.n_limbs), a.scale * b.scale)
         co = out.c(self.n)
         _check(self.lib.ckks_mul_relin(self.h, ctypes.byref(ca), ctypes.byref(cb), pk, ctypes.byref(co)),
                "ckks_mul_relin")
@@ -432,14 +430,14 @@ class Context:
 
     def rescale(self, ct: Buf) -> Buf:
         ci = ct.c(self.n)
-        out = Buf(self._empty(2, ct.n_limbs - 1), ct.scale / self.q[ct.level])
+        out = Buf(self._empty(ct.data, 2, ct.n_limbs - 1), ct.scale / self.q[ct.level])
         co = out.c(self.n)
         _check(self.lib.ckks_rescale(self.h, ctypes.byref(ci), ctypes.byref(co)), "ckks_rescale")
         return out
 
     def rotate(self, ct: Buf, steps: int, key: torch.Tensor) -> Buf:
         ci, pk = ct.c(self.n), self._key(key)
-        out = Buf(self._empty(2, ct.n_limbs), ct.scale)
+        out = Buf(self._empty(ct.data, 2, ct.n_limbs), ct.scale)
         co = out.c(self.n)
         _check(self.lib.ckks_rotate(self.h, ctypes.byref(ci), steps, pk, ctypes.byref(co)), "ckks_rotate")
         return out
@@ -463,7 +461,7 @@ class Context:
         kp = (ctypes.c_void_p * cnt)(*[self._key(k).value for k in keys])
         ci = ct.c(self.n)
         if outs is None:
-            outs = [Buf(self._empty(2, ct.n_limbs), ct.scale) for _ in range(cnt)]
+            outs = [Buf(self._empty(ct.data, 2, ct.n_limbs), ct.scale) for _ in range(cnt)]
         ob = (_Buf * cnt)(*[o.c(self.n) for o in outs])
         _check(self.lib.ckks_rotate_hoisted(self.h, ctypes.byref(ci), st, cnt, kp, ob), "ckks_rotate_hoisted")
         return list(outs)
@@ -501,7 +499,7 @@ class Context:
         n_out = d_out // D
         level = cts[0].level
         if outs is None:
-            outs = [Buf(self._empty(2, level), cts[0].scale) for _ in range(n_out)]
+            outs = [Buf(self._empty(cts[0].data, 2, level), cts[0].scale) for _ in range(n_out)]
         # the library reads d_in/D input and d_out/D output descriptors: never hand it shorter arrays
         if D > 0 and d_in % D == 0 and d_out % D == 0 and (len(cts) < d_in // D or len(outs) < n_out):
             raise ValueError("linear_project: %d inputs and %d outputs given, the shape needs %d and %d"
@@ -525,8 +523,8 @@ class Context:
         if len(b_of_a) != len(a_cts):
             raise ValueError("%s: %d ciphertexts but %d indices" % (fn, len(a_cts), len(b_of_a)))
         if outs is None:
-            outs = [Buf(self._empty(2, a_cts[0].n_limbs - (2 if fn == "ckks_attention_scores" else 1)), 0.0)
-                    for _ in a_cts]
+            limbs_off = 2 if fn == "ckks_attention_scores" else 1
+            outs = [Buf(self._empty(a.data, 2, a_cts[0].n_limbs - limbs_off), 0.0) for a in a_cts]
         if len(outs) < len(a_cts):
             raise ValueError("%s: %d outputs for %d inputs" % (fn, len(outs), len(a_cts)))
         ab = (_Buf * len(a_cts))(*[c.c(self.n) for c in a_cts])
