@@ -395,7 +395,8 @@ __global__ __launch_bounds__(512, 4) void ntt_col8_from_fft(const double2 *__res
     constexpr uint32_t log_n = 16, M = 1u << 15, MT_PITCH = 17;
     __shared__ double tws[2][256];
     __shared__ double tr[16][nttc::kTr8];  // also the pass-B exchange buffer (2048 double2 with padding)
-    // the rounded coefficients (integers as doubles) [256][17], then (each thread's in its registers) the second transpose's region
+    // the rounded coefficients (integers as doubles) [256][17], then (each thread's in its registers) the second
+    // transpose's region
     __shared__ double trb[16][nttc::kTr8];
     double *mt = &trb[0][0];
     static_assert(256 * MT_PITCH <= 16 * nttc::kTr8, "the tile fits the transpose region");
@@ -638,13 +639,16 @@ ckks_status fft_passes(ckks_ctx *ctx, double2 *work, uint32_t batch, const FftOu
         const uint32_t hb = logm - logb;
         const dim3 grid(batch * (B / kThreads));
         prof_begin(ctx, K_FFT_B, bytes);
+#define CK_FFT_B(HB)                                                                                               \
+    hipLaunchKernelGGL(k_fft_b<HB>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o)
         switch (hb) {
-        case 1: hipLaunchKernelGGL(k_fft_b<1>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
-        case 2: hipLaunchKernelGGL(k_fft_b<2>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
-        case 3: hipLaunchKernelGGL(k_fft_b<3>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
-        case 4: hipLaunchKernelGGL(k_fft_b<4>, grid, dim3(kThreads), 0, ctx->stream, work, ctx->d_fft_w, logm, logb, o); break;
+        case 1: CK_FFT_B(1); break;
+        case 2: CK_FFT_B(2); break;
+        case 3: CK_FFT_B(3); break;
+        case 4: CK_FFT_B(4); break;
         default: prof_end(ctx, K_FFT_B); return set_error(CKKS_EUNSUPPORTED, "fft: unsupported size");
         }
+#undef CK_FFT_B
         prof_end(ctx, K_FFT_B);
     }
     HIP_TRY(hipGetLastError());

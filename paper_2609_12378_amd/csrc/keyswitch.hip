@@ -481,9 +481,9 @@ __global__ __launch_bounds__(64) void k_key_ip_intt8(RotArgs ra, uint64_t *up, u
     }
 }
 
-// ModDown of a batch of rotations, fused (fp64, 256-point rows)// ModDown of a batch of rotations, fused (fp64, 256-point rows): block (r, q-limb i, two rows h) finishes the
-// forward transform of the converted P part cw[r][k][i] (its first pass already done), computes the q-limb part
-// of the key inner product u_k = sum_j sigma_{g_r}(d_j)[i] * key_r[j][k][i] in registers, and writes
+// ModDown of a batch of rotations, fused (fp64, 256-point rows): block (r, q-limb i, two rows h) finishes the forward
+// transform of the converted P part cw[r][k][i] (its first pass already done), computes the q-limb part of the key
+// inner product u_k = sum_j sigma_{g_r}(d_j)[i] * key_r[j][k][i] in registers, and writes
 //   out_r[k][i] = (u_k - NTT(cw[r][k][i])) * P^-1 (+ sigma_{g_r}(c0)[i] for k = 0, + add1[i] if set for k = 1),
 // so neither the q-limb rows of u nor the transformed conversion ever go to HBM.  Magnitudes (units of q):
 // column-pass outputs <= 4.3 (from inputs reduced to q/2), transform outputs <= 2.6, each product <= 0.875 and the

@@ -93,8 +93,9 @@ __global__ __launch_bounds__(256) void k_up_col(uint64_t *data, Blocks bl, const
     for (int k = 0; k < kE; k++) base[(size_t)(t + TS * k) * 256] = A::to_raw(ar.red(x[k]));
 }
 
-// 3. conversion alone (N1 < 256, or more than 8 sources): thread = one coefficient, blockIdx.y a group of t_per targets, blockIdx.z (entry,
-// block); canonical residues out.  All loads issue before the first is used: short blocks repeat their last source.
+// 3. conversion alone (N1 < 256, or more than 8 sources): thread = one coefficient, blockIdx.y a group of t_per targets,
+// blockIdx.z (entry, block); canonical residues out.  All loads issue before the first is used: short blocks repeat
+// their last source.
 template <int NS>
 __global__ __launch_bounds__(256) void k_up_conv(uint64_t *out, const uint64_t *in, Blocks bl, uint32_t t_per,
                                                  const ModQ *__restrict__ mods)

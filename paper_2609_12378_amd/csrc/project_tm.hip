@@ -341,8 +341,9 @@ __global__ __launch_bounds__(kThreads) void k_xdigits(const uint64_t *__restrict
 // + 0..15) and the tile's jc <= 16 MT outputs (MT 16-row MFMA tiles).  Q ([L][2D][npt], npt = K jc, kappa-major) gives
 // the plaintext values (rows jj >= jc and kappa >= K are zero); Xd the ciphertext digits from kappa_base on (16-byte
 // aligned, rows padded so a block never reads past them).  The digits of up to 64 kKBC kappa of the run's plaintexts
-// (kKBC = NW keeps eight waves on a CU) are laid out in LDS at once, for both polynomials (`polys` of them per block), so the loop over kappa has no barrier:
-// each wave streams its ciphertext digits (1 KB per digit and 64 kappa, loaded one step ahead) against them.
+// (kKBC = NW keeps eight waves on a CU) are laid out in LDS at once, for both polynomials (`polys` of them per block),
+// so the loop over kappa has no barrier: each wave streams its ciphertext digits (1 KB per digit and 64 kappa, loaded
+// two steps ahead) against them.
 // At N = 2^16, 13 limbs, 512 kappa and 16 times 16 rows: 14.1 ms with the digits formed per polynomial and 64 kappa and
 // 32 rows a launch; 12.8 ms so, 1.7 P int8 op/s (14.4 ms with 32 rows a launch, the ciphertext digits then crossing HBM
 // twice as often: bound by the matrix cores now).

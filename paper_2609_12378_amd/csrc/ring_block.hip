@@ -241,9 +241,9 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT) void k_blk_rescale_top(double
 }
 // out_i = (c_i - NTT(top mod q_i)) q_l^-1
 template <int LOGN, bool EARLY>
-__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4) void k_blk_rescale(uint64_t *out, const uint64_t *__restrict__ c,
-                                                                      const double *__restrict__ top, uint32_t l,
-                                                                      const ulonglong2 *__restrict__ qlinv, Tab tb)
+__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4)
+void k_blk_rescale(uint64_t *out, const uint64_t *__restrict__ c, const double *__restrict__ top, uint32_t l,
+                   const ulonglong2 *__restrict__ qlinv, Tab tb)
 {
     __shared__ double lds[blk::Shape<LOGN>::kLds];
     const uint32_t i = blockIdx.x % l, poly = blockIdx.x / l, t = threadIdx.x;
@@ -359,8 +359,8 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT) void k_blk_digits(double *y, 
 // row `row` of digit j of entry r: the conversion of the digit's limbs transformed, or for the digit's own limbs the
 // polynomial itself; grid (ext, nd, count)
 template <int LOGN, bool TENSOR, bool EARLY>
-__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4) void k_blk_modup(uint64_t *digits, const double *__restrict__ y,
-                                                                    Source src, Digits dg, Tab tb)
+__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4)
+void k_blk_modup(uint64_t *digits, const double *__restrict__ y, Source src, Digits dg, Tab tb)
 {
     __shared__ double lds[blk::Shape<LOGN>::kLds];
     const uint32_t row = blockIdx.x, j = blockIdx.y, r = blockIdx.z, t = threadIdx.x, ext = dg.L + dg.K;
@@ -505,17 +505,16 @@ __global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4) void k_blk_mod
 {
     __shared__ double lds[blk::Shape<LOGN>::kLds];
     const uint32_t i = blockIdx.x, k = blockIdx.y;
-    moddown_finish<LOGN, ADD_ROWS, EARLY>(lds, out + (((size_t)k * L + i) << LOGN), u + ((size_t)k * (L + K) << LOGN), i, k,
-                                   k == 0 ? add0 : k == 1 ? add1 : nullptr, k == 0 ? add0_g : 1u, nullptr, nullptr, L,
-                                   K, pmod, pinv, tb);
+    moddown_finish<LOGN, ADD_ROWS, EARLY>(lds, out + (((size_t)k * L + i) << LOGN), u + ((size_t)k * (L + K) << LOGN),
+                                          i, k, k == 0 ? add0 : k == 1 ? add1 : nullptr, k == 0 ? add0_g : 1u, nullptr,
+                                          nullptr, L, K, pmod, pinv, tb);
 }
 // component k of rotation r (grid (L, 2, count)): sigma_g(c0) for the first, add1 (if set) for the second; with
 // ADD_TENSOR the first two components of the tensor product of ta and tb2
 template <int LOGN, int MODE, bool EARLY>
-__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4) void k_blk_finish(RotArgs ra, const uint64_t *u, uint32_t L,
-                                                                     uint32_t K, const double *__restrict__ pmod,
-                                                                     const ulonglong2 *__restrict__ pinv,
-                                                                     const uint64_t *ta, const uint64_t *tb2, Tab tb)
+__global__ __launch_bounds__(blk::Shape<LOGN>::NT, EARLY ? 1 : 4)
+void k_blk_finish(RotArgs ra, const uint64_t *u, uint32_t L, uint32_t K, const double *__restrict__ pmod,
+                  const ulonglong2 *__restrict__ pinv, const uint64_t *ta, const uint64_t *tb2, Tab tb)
 {
     __shared__ double lds[blk::Shape<LOGN>::kLds];
     const uint32_t i = blockIdx.x, k = blockIdx.y, r = blockIdx.z;
