@@ -595,14 +595,16 @@ ckks_status blk_key_product(ckks_ctx *ctx, uint32_t level, const RotArgs &ra, ui
 }  // namespace
 
 // N = 2^14: a block is 1024 threads and all of a CU's LDS, 15 us a row with nothing to hide its waits, so the two
-// passes (about 5 us each while they leave the chip idle) are faster for a few rows.  Forward and inverse: 32 rows
-// 14.9 and 16.3 us here against 12.9 and 12.8, 48 rows 15.7 and 16.6 against 15.2 and 15.1, 64 rows 15.4 and 16.7
-// against 17.3 and 17.0, 192 rows 17 and 18 against 24 and 24, 768 rows 56 and 62 against 79 and 78
-bool blk_rows(const ckks_ctx *ctx, size_t rows) { return blk_ring(ctx) && (ctx->log_n < 14 || rows >= 64); }
+// passes (about 6 us each while they leave the chip idle) are faster for a few rows: up to 128, whose column pass is 512
+// blocks, two a CU.  A forward and an inverse transform as a program calls them: 64 rows 33.8 us here against 26.7, 96
+// rows 34.2 against 30.7, 128 rows 34.6 against 33.4, 129 rows 34.7 against 39.6, 160 rows 35.0 against 41.5, 186 rows
+// 36.9 against 47.2, in whatever groups the rows come
+bool blk_rows(const ckks_ctx *ctx, size_t rows) { return blk_ring(ctx) && (ctx->log_n < 14 || rows > 128); }
 
-// the same for a rescale, two launches here and four there: 96 rows 32.4 against 29.7 us, 160 rows 34.7 against 36.3,
-// 384 rows 53 against 59
-bool blk_rescales(const ckks_ctx *ctx, size_t rows) { return blk_ring(ctx) && (ctx->log_n < 14 || rows >= 128); }
+// the same for a rescale, two launches here and four there, by the rows out: 96 rows 32.4 against 29.7 us, 128 rows 35.3
+// against 34.1 in the kernels alone, 160 rows 34.7 against 36.3, 186 rows 37.3 against 41.1 in the kernels, 384 rows 53
+// against 59
+bool blk_rescales(const ckks_ctx *ctx, size_t rows) { return blk_rows(ctx, rows); }
 
 // the same for the first pass from coefficients, which at N = 2^14 has one plaintext's limbs (64 rows 15.4 against 15.0)
 bool blk_from_i64(const ckks_ctx *ctx) { return blk_ring(ctx) && ctx->log_n < 14; }

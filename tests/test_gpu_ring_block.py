@@ -48,7 +48,7 @@ def env(request):
 
 @pytest.mark.parametrize("rows", [1, 3, 64])
 def test_transforms(env, rows):
-    limbs = min(env.n_q, 5)                      # 64 x 5 rows: past the 64 of N = 2^14
+    limbs = min(env.n_q, 5)                      # 64 x 5 rows: past the 128 of N = 2^14
     idx = list(range(limbs))
     x = uniform_residues(env.g, env.ctx.q[:limbs], env.n, lead=(rows,))
     t = env.ctx.ntt(to_dev(x))
