@@ -615,12 +615,12 @@ bool blk_crypt(const ckks_ctx *ctx, uint32_t limbs)
     return blk_ring(ctx) && ntt_uses_f64(ctx, limbs) && ctx->log_n < 14;
 }
 
-// the same for a ModDown of `polys` polynomials, by the rows it transforms back: 24 + 8 limbs, 1, 4 and 8 polynomials
-// 48, 53 and 54 us here against 30, 49 and 61 in two passes; 12 + 4 limbs, 4, 8 and 16 polynomials 44, 48 and 51
-// against 40, 48 and 60
+// the same for a ModDown of `polys` polynomials, by the rows it transforms back.  Whole rows less two passes, in the time
+// of a projection that ends in one: 24 rows +5 to +14 us (of 330 to 490), 48 rows +9 (24 limbs), 0 (12 and 6 limbs) and
+// -3 (3 limbs), 72 rows -4 to -5, 90 rows -11, 96 to 288 rows -1 to -21
 bool blk_moddowns(const ckks_ctx *ctx, uint32_t level, uint32_t polys)
 {
-    return blk_ring(ctx) && f64_switch(ctx, level) && (ctx->log_n < 14 || (size_t)polys * (level + 1) >= 96);
+    return blk_ring(ctx) && f64_switch(ctx, level) && (ctx->log_n < 14 || (size_t)polys * (level + 1) > 48);
 }
 
 bool blk_ring(const ckks_ctx *ctx) { return ctx->log_n >= blk::kMinLog && ctx->log_n <= blk::kMaxLog && !ctx->int_only; }
@@ -628,7 +628,9 @@ bool blk_ring(const ckks_ctx *ctx) { return ctx->log_n >= blk::kMinLog && ctx->l
 // A ModUp and a batch of rotations: not at N = 2^14, where the two-pass kernels (modup.hip, keyswitch.hip) keep the q
 // rows of the key products on chip and their grids are not bound to whole rows.  24 + 8 limbs, 1, 9 and 32 rotations of
 // 24 limbs 100, 201 and 585 us with the whole-row ModDown against 76, 192 and 465 in two passes, of 8 limbs 85, 117 and
-// 266 against 52, 86 and 184; 12 + 4 limbs, 9 rotations of 8 limbs 96 against 85
+// 266 against 52, 86 and 184; 12 + 4 limbs, 9 rotations of 8 limbs 96 against 85.  The exception is 32 rotations of 1 to
+// 4 limbs under at most 4 special primes: kernels of 81 to 100 us there and 73 to 101 here, but a call bound by its
+// caller's side, for which two launches fewer were 98 us against 104
 bool blk_switch(const ckks_ctx *ctx, uint32_t level)
 {
     return blk_ring(ctx) && ctx->log_n < 14 && f64_switch(ctx, level);
